@@ -177,8 +177,8 @@ def _clusters(feats, k, gen, rounds=3):
     pick = torch.randperm(feats.shape[0], generator=gen, device=DEV)[:k]
     centres, lab = feats[pick], None
     for r in range(rounds + 1):
-        lab = torch.cat([torch.cdist(f, centres, compute_mode="donot_use_mm_for_euclid_dist").argmin(1)
-                         for f in feats.split(max(1, 40_000_000 // k))])
+        c2 = (centres * centres).sum(1)
+        lab = torch.cat([(c2 - 2.0 * f @ centres.T).argmin(1) for f in feats.split(max(1, 40_000_000 // k))])
         lab = torch.unique(lab, return_inverse=True)[1]
         if r < rounds:
             centres = _means(lab, int(lab.max()) + 1, feats).to(DEV)
