@@ -454,7 +454,6 @@ int frame_result(hair_ctx* ctx, hair_ws* ws, int64_t nseg, int T, FrameOut* out)
     ws->last_ntiles = T;
     ws->last_pairs = pairs;
     out->pairs = pairs;
-    out->ctr.fragments = out->ctr.sizes[2];
     out->n_batches = out->ctr.sizes[3];
     // three timing markers only: each costs the stream a few microseconds of idle time
     float t05 = 0, t56 = 0, t06 = 0;
@@ -613,10 +612,15 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     f.item_tab = ws->item_tab.as<uint2>();
     f.item_base = ws->item_base.as<uint32_t>();
     f.pix_cnt = ws->pix_cnt.as<uint32_t>();
+    f.pix_off = ws->pix_off.as<uint32_t>();
     f.pix_kmin = ws->pix_kmin.as<uint32_t>();
     f.pix_kmax = ws->pix_kmax.as<uint32_t>();
-    f.pix_off = ws->pix_off.as<uint32_t>();
     f.pix_thick = lv.kind == 2 ? ws->pix_thick.as<uint8_t>() : nullptr;
+    // (shadow maps and debug dumps need every fragment)
+    f.trim = !dom && !dbg && lv.nseg >= kTrimRows;
+    // (strand levels have opaque fragments only where a strand is wider than a pixel: no pass for them)
+    f.opaque = !dom && !dbg && lv.kind != 0;
+    f.tile_all = ws->tile_cnt.as<uint32_t>();   // (the binning's tile totals are in tile_start by now)
     f.tile_tot = ws->tile_tot.as<uint32_t>();
     f.tile_nb = ws->tile_nb.as<uint32_t>();
     f.batch_mask = ws->batch_mask.as<uint32_t>();
@@ -631,9 +635,8 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
             "k_scatter");
     // (a static-scratch frame clears the image only once every buffer has been carved, so that
     // a frame too large for the scratch fails with the caller's image untouched)
-    HIP_TRY(ctx, launch_fill_pix(f.pix_cnt, f.pix_kmin, f.pix_kmax, f.pix_thick, TP, ws->arena ? nullptr : rgba,
-                                 (size_t)cam->width * cam->height, f.item_start, T, ws->item_tab.as<uint2>(),
-                                 caps.items, st),
+    HIP_TRY(ctx, launch_fill_pix(f, TP, ws->arena ? nullptr : rgba, (size_t)cam->width * cam->height,
+                                 ws->item_tab.as<uint2>(), caps.items, st),
             "fill");
     const uint32_t item_grid = warm ? caps.items : n_items;
     HIP_TRY(ctx, launch_count(f, cc, item_grid, st), "k_count");
@@ -645,10 +648,13 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     } else {
         HIP_TRY(ctx, launch_exscan(f.tile_tot, ws->frag_base.as<uint32_t>(), T, scan_tmp, st), "k_scan");
         HIP_TRY(ctx, launch_exscan(f.tile_nb, ws->batch_start.as<uint32_t>(), T, scan_tmp, st), "k_scan");
+        HIP_TRY(ctx, launch_sum_tiles(f, st), "k_sum_tiles");
     }
     uint32_t n_frags = 0, n_batches = 0;
     if (!warm) {
         uint32_t sizes2[2] = {0, 0};
+        unsigned long long all_frags = 0;
+        HIP_TRY(ctx, hipMemcpyAsync(&all_frags, &f.ctr->fragments, 8, hipMemcpyDeviceToHost, st), "copy");
         HIP_TRY(ctx, hipMemcpyAsync(&sizes2[0], ws->frag_base.as<uint32_t>() + T, 4, hipMemcpyDeviceToHost, st),
                 "copy");
         HIP_TRY(ctx, hipMemcpyAsync(&sizes2[1], ws->batch_start.as<uint32_t>() + T, 4, hipMemcpyDeviceToHost, st),
@@ -657,6 +663,13 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
         n_frags = sizes2[0];
         n_batches = sizes2[1];
         caps.frags = std::max(caps.frags, cap_of(n_frags));
+        // (the static scratch serves the frames whose whole fragment set it can hold)
+        if (ws->arena && all_frags > n_frags) {
+            DevBuf probe;
+            const size_t off = ws->arena_off;
+            if ((rc = arena_take(ws, probe, 8ull * all_frags))) return rc;
+            ws->arena_off = off;
+        }
         caps.batches = std::max(caps.batches, cap_of(n_batches));
     }
     if ((rc = ws_need(ws, ws->frags, 8ull * caps.frags))) return rc;

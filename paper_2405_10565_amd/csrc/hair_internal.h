@@ -142,7 +142,7 @@ struct HierDev {
 
 // Global counters a render accumulates (zeroed at the start of each call).
 struct Counters {
-    unsigned long long fragments;
+    unsigned long long fragments;   // accepted (segment, pixel) fragments, stored or not
     uint32_t visible;
     uint32_t culled_long;
     uint32_t overflow_pixels;
@@ -151,7 +151,7 @@ struct Counters {
     uint32_t deep_pixels;    // pixels deeper than one LDS batch (rendered in depth-key slices)
     uint32_t cap_overflow;   // a frame size exceeded its buffer: the later passes did nothing
     uint32_t split_needed;   // segments culled as too long that pieces can draw (the frame is drawn again)
-    uint32_t sizes[4];       // list entries, work items, fragments, batches of the frame
+    uint32_t sizes[4];       // list entries, work items, stored fragments, batches of the frame
     uint32_t thick_batches;  // mixed frames: batches holding thick-hair fragments (listed in thick_list)
     unsigned long long phase[8];  // per-phase cycle sums (instrumented builds only)
 };
@@ -191,10 +191,14 @@ struct FrameBufs {
     const uint32_t* item_start;   // [T + 1] exclusive scan of per-tile work items
     const uint2* item_tab;        // [items] each work item's (tile, chunk of the tile's list)
     uint32_t* item_base;          // [items][kTilePix] each item's slice of each pixel's range
-    uint32_t* pix_cnt;            // [T][kTilePix] fragments per pixel
+    uint32_t* tile_all;           // [T] all fragments of the tile, stored or not
+    uint32_t* pix_cnt;            // [T][kTilePix] stored fragments per pixel
     uint32_t* pix_kmin;           // [T][kTilePix] smallest depth key per pixel
-    uint32_t* pix_kmax;           // [T][kTilePix] largest depth key per pixel
-    uint32_t* pix_off;            // [T][kTilePix] exclusive prefix of pix_cnt within the tile
+    uint32_t* pix_kmax;           // [T][kTilePix] largest depth key per pixel (until k_tile_prep, in frames
+                                  // with an opaque pass: the smallest key of an opaque fragment, ~0: none)
+    uint32_t* pix_off;            // [T][kTilePix] exclusive prefix of pix_cnt within the tile, with kHidesBit:
+                                  // an opaque fragment hides what lies behind pix_kmax (until
+                                  // k_tile_prep: the pixel's fragments that are not stored)
     uint8_t* pix_thick;           // [T][kTilePix] mixed frames: the pixel holds a thick-hair fragment
                                   // (nullptr in frames of one level)
     uint32_t* thick_list;         // [batches] mixed frames: table positions of the batches holding
@@ -209,7 +213,19 @@ struct FrameBufs {
     Counters* ctr;
     int32_t gid;                  // fragment records hold the global segment id (frames of fewer than
                                   // 2^24 rows, forward passes) instead of the index in the tile's list
+    int32_t trim;                 // fragments whose alpha is exactly 0 are not stored (kTrimRows)
+    int32_t opaque;               // the frame can hold thick hairs: it has an opaque pass (k_opaque)
 };
+// (offsets stay below it: at most 2^24 segments of a tile that are not opaque cover under 2^7
+// of its pixels each, and a pixel behind an opaque fragment stores no more)
+constexpr uint32_t kHidesBit = 0x80000000u;
+// A segment's integer radius ceil(16 hw) + 8 reaches past its footprint hw + 1/2, so 5 to 9% of
+// the fragments of a strand frame have alpha exactly 0.  Leaving them out costs the count pass
+// 14% (each fragment is tested) and saves as large a part of the emit and shading passes as
+// they are: frames of fewer rows than this lose by it (33k x 23 strands, R/TT/D: 306 us without,
+// 310 with), larger ones gain (100k x 32 at 1080p: 1091 us without, 1072 with; 300k x 48 at 4K:
+// 9.46 ms without, 9.0 with).
+constexpr int kTrimRows = 1 << 21;
 
 // Kernel launchers (hair_kernels.hip).
 hipError_t launch_project(const LevelDev& lv, const CamConst& cam, SegRec* seg, ShadeRec* shade, hipStream_t st);
@@ -238,6 +254,7 @@ hipError_t launch_scatter(const SegRec* seg, int32_t nseg, const CamConst& cam, 
 // later pass that would fill a sized buffer does nothing once the flag is set.
 hipError_t launch_check_caps(const FrameBufs& f, const FrameCaps& caps, int stage, hipStream_t st);
 hipError_t launch_tile_items(const uint32_t* tile_start, int T, uint32_t* items, hipStream_t st);
+hipError_t launch_sum_tiles(const FrameBufs& f, hipStream_t st);   // ctr->fragments of larger frames
 // Fused single-block forms for frames of at most kScanOneBlockTiles tiles: the items and their
 // scan with the first capacity check; the fragment and batch offsets with the second.
 constexpr int kScanOneBlockTiles = 1 << 16;
@@ -300,10 +317,10 @@ hipError_t launch_project_light(const LevelDev& lv, const ShadeRec* rows, const 
 hipError_t launch_dom_resolve(const FrameBufs& f, const LevelDev& lv, const ShadeRec* rows, const DomGrid* grid, int32_t K, float delta,
                               int32_t R, uint32_t n_blocks, float4* tex, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t st);
-// The frame's per-pixel counters: n counts set to 0, key minima to ~0, key maxima to 0.
-hipError_t launch_fill_pix(uint32_t* cnt, uint32_t* kmin, uint32_t* kmax, uint8_t* thick, size_t n, float* rgba,
-                           size_t n_rgba4, const uint32_t* item_start, int T, uint2* item_tab, uint32_t cap_items,
-                           hipStream_t st);   // also clears rgba (n_rgba4 pixels) when given
+// The frame's n per-pixel counters, the work-item table and (when given) the image, cleared to
+// transparent black.
+hipError_t launch_fill_pix(const FrameBufs& f, size_t n, float* rgba, size_t n_rgba4, uint2* item_tab,
+                           uint32_t cap_items, hipStream_t st);
 hipError_t launch_fill_f32(float* p, float v, size_t n, hipStream_t st);
 hipError_t launch_probe_rate(int kind, int blocks, int iters, float* out, hipStream_t st);
 
