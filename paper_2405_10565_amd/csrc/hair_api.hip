@@ -485,11 +485,13 @@ struct DomPass {
 
 // Project + bin + tile for one level; the caller holds ws->mu.
 //   k_project                         per-segment records (projection, half-width, culling)
-//   k_bin_count, k_bin_offsets, k_scan per-block tile counts, their column scan, list offsets
-//   k_tile_items, k_scan              work items (list chunks) per tile
-//   k_scatter                         tile lists (per-block LDS cursors)
-//   k_count, k_tile_prep, k_scan x2   per-pixel counts, offsets, batches
-//   k_batch_records, k_emit           batch table, fragment buffer and per-pixel key ranges
+//   k_bin_count, k_bin_offsets        per-block tile counts, their column scan
+//   k_lists_scan                      list offsets and work items (list chunks) per tile
+//   k_scatter                         tile lists (per-block LDS cursors); counters and image cleared
+//   k_opaque                          nearest opaque keys (frames that can hold thick hairs)
+//   k_count, k_tile_prep, k_tile_scans  per-pixel counts, offsets, batches
+//   k_emit                            fragment buffer, per-pixel key ranges, batch table (mixed
+//                                     frames: k_batch_records)
 //   k_batch                           sort, shade, blend (one workgroup per batch)
 // A cold frame reads the frame's sizes back twice (after the work items and after the
 // batches) to size its buffers, with a quarter of headroom that the workspace keeps as its
@@ -534,7 +536,6 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     uint32_t* tile_start = ws->tile_start.as<uint32_t>();
     uint32_t* scan_tmp = ws->scan_tmp.as<uint32_t>();
     HIP_TRY(ctx, hipEventRecord(ws->ev[0], st), "hipEventRecord");
-    HIP_TRY(ctx, launch_fill_u32(ws->ctr.as<uint32_t>(), 0u, sizeof(Counters) / 4, st), "fill");
     if (hier && tess && tess->split)
         HIP_TRY(ctx, launch_project_split_mixed(*hier, sel, tess->rows, lv.nseg, tess->cnt, cc, ws->seg.as<SegRec>(),
                                                 ws->shade.as<ShadeRec>(), st),
@@ -555,16 +556,18 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     else
         HIP_TRY(ctx, launch_project(lv, cc, ws->seg.as<SegRec>(), ws->shade.as<ShadeRec>(), st), "k_project");
     HIP_TRY(ctx, launch_bins(ws->seg.as<SegRec>(), lv.nseg, cc, plan, ws->bin_m.as<uint32_t>(), ws->bin_blk.as<uint4>(),
-                             ws->tile_cnt.as<uint32_t>(), tile_start, ws->ctr.as<Counters>(), scan_tmp, st),
+                             ws->tile_cnt.as<uint32_t>(), ws->ctr.as<Counters>(), st),
             "k_bin_count");
     // frames of up to 2^16 tiles scan and check their sizes in single-block kernels
     const bool fused = T <= kScanOneBlockTiles;
     const uint32_t kNoCap = 0xFFFFFFFFu;   // cold frames size their buffers from the sizes read back
     if (fused) {
-        HIP_TRY(ctx, launch_items_scan(tile_start, T, ws->item_start.as<uint32_t>(), ws->ctr.as<Counters>(),
-                                       warm ? ws->caps.pairs : kNoCap, warm ? ws->caps.items : kNoCap, st),
-                "k_items_scan");
+        HIP_TRY(ctx, launch_lists_scan(ws->tile_cnt.as<uint32_t>(), T, tile_start, ws->item_start.as<uint32_t>(),
+                                       ws->ctr.as<Counters>(), warm ? ws->caps.pairs : kNoCap,
+                                       warm ? ws->caps.items : kNoCap, st),
+                "k_lists_scan");
     } else {
+        HIP_TRY(ctx, launch_exscan(ws->tile_cnt.as<uint32_t>(), tile_start, T, scan_tmp, st), "k_scan");
         HIP_TRY(ctx, launch_tile_items(tile_start, T, ws->items.as<uint32_t>(), st), "k_tile_items");
         HIP_TRY(ctx, launch_exscan(ws->items.as<uint32_t>(), ws->item_start.as<uint32_t>(), T, scan_tmp, st), "k_scan");
     }
@@ -630,14 +633,11 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     // (the backward pass accumulates per list entry, so its records keep list indices)
     f.gid = grad == nullptr && lv.nseg < (1 << 24);
     if (!fused) HIP_TRY(ctx, launch_check_caps(f, caps, 1, st), "k_check_caps");
-    HIP_TRY(ctx, launch_scatter(f.seg, lv.nseg, cc, plan, tile_start, ws->bin_m.as<uint32_t>(), ws->list.as<uint32_t>(),
-                                f.ctr, st),
-            "k_scatter");
     // (a static-scratch frame clears the image only once every buffer has been carved, so that
     // a frame too large for the scratch fails with the caller's image untouched)
-    HIP_TRY(ctx, launch_fill_pix(f, TP, ws->arena ? nullptr : rgba, (size_t)cam->width * cam->height,
-                                 ws->item_tab.as<uint2>(), caps.items, st),
-            "fill");
+    HIP_TRY(ctx, launch_scatter(f, lv.nseg, cc, plan, ws->bin_m.as<uint32_t>(), ws->list.as<uint32_t>(),
+                                ws->arena ? nullptr : rgba, ws->item_tab.as<uint2>(), caps.items, st),
+            "k_scatter");
     const uint32_t item_grid = warm ? caps.items : n_items;
     HIP_TRY(ctx, launch_count(f, cc, item_grid, st), "k_count");
     HIP_TRY(ctx, launch_tile_prep(f, st), "k_tile_prep");

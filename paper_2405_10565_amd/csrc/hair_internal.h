@@ -240,25 +240,25 @@ struct BinPlan {
     int nb, per_block, range;
 };
 BinPlan bin_plan(int32_t nseg, int32_t T);
-// M (nb * T words), blk (nb entries), tot (T words), tile_start (T + 1 words): per-block counts
-// and segment statistics, tile totals and list offsets of the projected segments; ctr receives
-// the visible / culled counts and the largest half-width.
+// M (nb * T words), blk (nb entries), tot (T words): per-block counts and segment statistics and
+// the tiles' list lengths of the projected segments; ctr is cleared and receives the visible /
+// culled counts and the largest half-width.
 hipError_t launch_bins(const SegRec* seg, int32_t nseg, const CamConst& cam, const BinPlan& p, uint32_t* M,
-                       uint4* blk, uint32_t* tot, uint32_t* tile_start, Counters* ctr, uint32_t* scan_tmp,
-                       hipStream_t st);
-hipError_t launch_scatter(const SegRec* seg, int32_t nseg, const CamConst& cam, const BinPlan& p,
-                          const uint32_t* tile_start, const uint32_t* M, uint32_t* list, const Counters* ctr,
-                          hipStream_t st);
+                       uint4* blk, uint32_t* tot, Counters* ctr, hipStream_t st);
+// The tile lists, and everything the later passes expect cleared: the frame's per-pixel counters,
+// the work-item table and (when given) the image, transparent black.
+hipError_t launch_scatter(const FrameBufs& f, int32_t nseg, const CamConst& cam, const BinPlan& p, const uint32_t* M,
+                          uint32_t* list, float* rgba, uint2* item_tab, uint32_t cap_items, hipStream_t st);
 // Record the frame's sizes in ctr->sizes and flag ctr->cap_overflow when one exceeds its
 // capacity (stage 1: list entries and work items; stage 2: fragments and batches).  Every
 // later pass that would fill a sized buffer does nothing once the flag is set.
 hipError_t launch_check_caps(const FrameBufs& f, const FrameCaps& caps, int stage, hipStream_t st);
 hipError_t launch_tile_items(const uint32_t* tile_start, int T, uint32_t* items, hipStream_t st);
 hipError_t launch_sum_tiles(const FrameBufs& f, hipStream_t st);   // ctr->fragments of larger frames
-// Fused single-block forms for frames of at most kScanOneBlockTiles tiles: the items and their
-// scan with the first capacity check; the fragment and batch offsets with the second.
+// Fused single-block forms for frames of at most kScanOneBlockTiles tiles: list offsets and work
+// items with the first capacity check; the fragment and batch offsets with the second.
 constexpr int kScanOneBlockTiles = 1 << 16;
-hipError_t launch_items_scan(const uint32_t* tile_start, int T, uint32_t* item_start, Counters* ctr,
+hipError_t launch_lists_scan(const uint32_t* tot, int T, uint32_t* tile_start, uint32_t* item_start, Counters* ctr,
                              uint32_t cap_pairs, uint32_t cap_items, hipStream_t st);
 hipError_t launch_tile_scans(const FrameBufs& f, uint32_t* frag_base, uint32_t* batch_start, uint32_t cap_frags,
                              uint32_t cap_batches, hipStream_t st);
@@ -317,10 +317,6 @@ hipError_t launch_project_light(const LevelDev& lv, const ShadeRec* rows, const 
 hipError_t launch_dom_resolve(const FrameBufs& f, const LevelDev& lv, const ShadeRec* rows, const DomGrid* grid, int32_t K, float delta,
                               int32_t R, uint32_t n_blocks, float4* tex, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t st);
-// The frame's n per-pixel counters, the work-item table and (when given) the image, cleared to
-// transparent black.
-hipError_t launch_fill_pix(const FrameBufs& f, size_t n, float* rgba, size_t n_rgba4, uint2* item_tab,
-                           uint32_t cap_items, hipStream_t st);
 hipError_t launch_fill_f32(float* p, float v, size_t n, hipStream_t st);
 hipError_t launch_probe_rate(int kind, int blocks, int iters, float* out, hipStream_t st);
 

@@ -5,8 +5,9 @@
 //                    half-width (Sec. 5.2, hair width calculation), culling.
 //   k_bin_count      per block of consecutive segments: tile counts in LDS (no device atomics);
 //   k_bin_offsets    column scan of the per-block count matrix -> each block's place in every list;
-//   k_scan1          exclusive prefix sums (tile list offsets, work items, fragment and batch bases).
-//   k_scatter        per block: append its segments' ids to the overlapped tiles' lists.
+//   k_lists_scan     exclusive prefix sums: tile list offsets and work items.
+//   k_scatter        per block: append its segments' ids to the overlapped tiles' lists, and clear
+//                    what the later passes accumulate into.
 //   k_opaque         frames with thick hairs: per pixel the nearest opaque fragment's depth key.
 //   k_count          per (tile, list chunk): exact integer coverage -> per-pixel fragment counts
 //                    (LDS-aggregated, then one global atomic per pixel).
@@ -491,22 +492,24 @@ __device__ inline uint32_t block_scan_1024(int n, G get, P put, uint32_t* s_w) {
     return carry;
 }
 
-// Work items of the count and emit passes (kNT list entries of a tile each), their exclusive
-// scan, and the first capacity check (list entries and items against their buffers), in one
-// block: the work of k_tile_items, k_scan1 and k_check_caps stage 1 for up to kScanOneBlock tiles.
-__global__ __launch_bounds__(1024) void k_items_scan(const uint32_t* __restrict__ tile_start, int T,
+// The tiles' list offsets (exclusive scan of their list lengths, block 0) and their work items of
+// the count and emit passes (kNT list entries each, scanned by block 1), each with its part of the
+// first capacity check: the work of k_tile_items, k_scan1 twice and k_check_caps stage 1 for up to
+// kScanOneBlock tiles.
+__global__ __launch_bounds__(1024) void k_lists_scan(const uint32_t* __restrict__ tot, int T,
+                                                     uint32_t* __restrict__ tile_start,
                                                      uint32_t* __restrict__ item_start, Counters* ctr, uint32_t cap_pairs,
                                                      uint32_t cap_items) {
     __shared__ uint32_t s_w[16];
-    const uint32_t items = block_scan_1024(
-        T, [&](int i) { return (tile_start[i + 1] - tile_start[i] + kNT - 1) / kNT; },
-        [&](int i, uint32_t v) { item_start[i] = v; }, s_w);
+    const bool items = blockIdx.x == 1;
+    uint32_t* start = items ? item_start : tile_start;
+    const uint32_t n = block_scan_1024(
+        T, [&](int i) { return items ? (tot[i] + kNT - 1) / kNT : tot[i]; },
+        [&](int i, uint32_t v) { start[i] = v; }, s_w);
     if (threadIdx.x == 0) {
-        const uint32_t pairs = tile_start[T];
-        item_start[T] = items;
-        ctr->sizes[0] = pairs;
-        ctr->sizes[1] = items;
-        if (pairs > cap_pairs || items > cap_items) ctr->cap_overflow = 1u;
+        start[T] = n;
+        ctr->sizes[items ? 1 : 0] = n;
+        if (n > (items ? cap_items : cap_pairs)) ctr->cap_overflow = 1u;
     }
 }
 
@@ -550,34 +553,6 @@ __global__ __launch_bounds__(1024) void k_tile_scans(const uint32_t* __restrict_
         start[T] = n;
         ctr->sizes[fr ? 2 : 3] = n;
         if (n > (fr ? cap_frags : cap_batches)) ctr->cap_overflow = 1u;
-    }
-}
-
-// The per-pixel counters of a frame: counts (stored, left out) 0, key minima ~0, key maxima 0
-// (~0 before an opaque pass).
-// ... and the work-item table of the count and emit passes: item i of tile t (its list chunk
-// i - item_start[t]), for the items within the table's capacity.
-__global__ void k_fill_pix(uint32_t* __restrict__ cnt, uint32_t* __restrict__ off, uint32_t* __restrict__ kmin,
-                           uint32_t* __restrict__ kmax, uint32_t kmax0, uint8_t* __restrict__ thick, size_t n,
-                           float4* __restrict__ rgba, size_t n_rgba, const uint32_t* __restrict__ item_start, int T, uint2* __restrict__ item_tab,
-                           uint32_t cap_items) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        cnt[i] = 0u;
-        off[i] = 0u;
-        kmin[i] = 0xFFFFFFFFu;
-        kmax[i] = kmax0;
-        if (thick) thick[i] = 0;
-    }
-    // (and the frame's image, transparent black, when one is given)
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_rgba; i += (size_t)gridDim.x * blockDim.x)
-        rgba[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-    // (one wave per tile, its lanes taking the tile's items in turn: a tile can hold thousands
-    // of items when a whole groom falls into a few tiles)
-    const int lane = threadIdx.x & 63;
-    const int wave = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6), n_waves = (int)((gridDim.x * blockDim.x) >> 6);
-    for (int t = wave; t < T; t += n_waves) {
-        const uint32_t i0 = item_start[t], i1 = min(item_start[t + 1], cap_items);
-        for (uint32_t i = i0 + lane; i < i1; i += 64) item_tab[i] = make_uint2((uint32_t)t, i - i0);
     }
 }
 
@@ -724,7 +699,8 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_count(const SegRec* __restr
 // Column-wise exclusive scan of M: M[b][t] <- sum of M[b'][t] over b' < b, tot[t] = column sum.
 // A block takes 64 tiles (one per lane) and its 16 waves split the rows into 16 ranges: each
 // wave sums its range, the range offsets come from LDS, and a second walk writes the prefixes.
-// Block 0 also reduces the per-block segment statistics into ctr.
+// Block 0 also clears the frame's counters (nothing before uses them) and reduces the per-block
+// segment statistics into them.
 __global__ __launch_bounds__(1024) void k_bin_offsets(uint32_t* __restrict__ M, int nb, int T,
                                                       uint32_t* __restrict__ tot, const uint4* __restrict__ blk,
                                                       Counters* __restrict__ ctr) {
@@ -738,6 +714,8 @@ __global__ __launch_bounds__(1024) void k_bin_offsets(uint32_t* __restrict__ M, 
         for (int b = r0; b < r1; ++b) sum += M[(size_t)b * T + t];
     }
     s_part[w][lane] = sum;
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < (int)(sizeof(Counters) / 4); i += 1024) reinterpret_cast<uint32_t*>(ctr)[i] = 0u;
     __syncthreads();
     uint32_t run = 0, total = 0;
     for (int w2 = 0; w2 < 16; ++w2) {
@@ -778,14 +756,56 @@ __global__ __launch_bounds__(1024) void k_bin_offsets(uint32_t* __restrict__ M, 
     }
 }
 
+// What the passes after the scatter expect cleared: the per-pixel counters (counts, stored and left
+// out, 0; key minima ~0, key maxima 0, or ~0 before an opaque pass), the frame's image (transparent
+// black, when one is given) and the work-item table (item i of tile t: its list chunk
+// i - item_start[t], for the items within the table's capacity).
+struct FillArgs {
+    uint32_t* cnt;
+    uint32_t* off;
+    uint32_t* kmin;
+    uint32_t* kmax;
+    uint32_t kmax0;
+    uint8_t* thick;
+    float4* rgba;
+    size_t n_rgba;
+    const uint32_t* item_start;
+    uint2* item_tab;
+    uint32_t cap_items;
+};
+__device__ inline void fill_frame(const FillArgs& a, int T) {
+    const size_t n = (size_t)T * kTilePix / 4, step = (size_t)gridDim.x * blockDim.x;
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint4 zero = make_uint4(0u, 0u, 0u, 0u), ones = make_uint4(~0u, ~0u, ~0u, ~0u);
+    const uint4 k0 = make_uint4(a.kmax0, a.kmax0, a.kmax0, a.kmax0);
+    for (size_t i = i0; i < n; i += step) {
+        reinterpret_cast<uint4*>(a.cnt)[i] = zero;
+        reinterpret_cast<uint4*>(a.off)[i] = zero;
+        reinterpret_cast<uint4*>(a.kmin)[i] = ones;
+        reinterpret_cast<uint4*>(a.kmax)[i] = k0;
+        if (a.thick) reinterpret_cast<uint32_t*>(a.thick)[i] = 0u;
+    }
+    for (size_t i = i0; i < a.n_rgba; i += step) a.rgba[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    // (one wave per tile, its lanes taking the tile's items in turn: a tile can hold thousands
+    // of items when a whole groom falls into a few tiles)
+    const int lane = threadIdx.x & 63;
+    for (int t = (int)(i0 >> 6); t < T; t += (int)(step >> 6)) {
+        const uint32_t b = a.item_start[t], e = min(a.item_start[t + 1], a.cap_items);
+        for (uint32_t i = b + lane; i < e; i += 64) a.item_tab[i] = make_uint2((uint32_t)t, i - b);
+    }
+}
+
+// The blocks b < nb append their segments; every block (more are launched where the image is large
+// for its segments) then does its share of fill_frame, which saves a launch.
 __global__ __launch_bounds__(kBinThreads) void k_scatter(const SegRec* __restrict__ seg, int nseg, int per_block,
-                                                         int ntx, int nty, int t0, int nt,
+                                                         int nb, int ntx, int nty, int t0, int nt,
                                                          const uint32_t* __restrict__ tile_start,
                                                          const uint32_t* __restrict__ M, uint32_t* __restrict__ list,
-                                                         const Counters* __restrict__ ctr) {
+                                                         const Counters* __restrict__ ctr, FillArgs fill) {
     extern __shared__ uint32_t s_tc[];
-    if (ctr->cap_overflow) return;
     const int T = ntx * nty;
+    if (t0 == 0) fill_frame(fill, T);
+    if (ctr->cap_overflow || (int)blockIdx.x >= nb) return;
     const uint32_t* row = M + (size_t)blockIdx.x * T + t0;
     for (int i = threadIdx.x; i < nt; i += kBinThreads) s_tc[i] = tile_start[t0 + i] + row[i];
     __syncthreads();
@@ -1492,7 +1512,7 @@ __global__ __launch_bounds__(kNT) void k_count(FrameBufs f, CamConst cam) {
 // forms a batch of its own.  Every lane finds, in parallel, the next non-empty pixel at or
 // after it and the end of a batch that would start at it; the chain of batch starts is then
 // followed (by one lane when it is short, by pointer doubling over all lanes when it is long)
-// and marked in a 256-bit mask of the tile.  k_batch_records turns the mask
+// and marked in a 256-bit mask of the tile.  batch_records turns the mask
 // into the batch table in parallel (a batch runs to the next start, or to the tile's end: the
 // pixels in between are empty).
 __global__ __launch_bounds__(kNT) void k_tile_prep(FrameBufs f) {
@@ -1610,10 +1630,9 @@ __global__ __launch_bounds__(kNT) void k_tile_prep(FrameBufs f) {
 
 // The batch table: one record (tile, first pixel, end pixel, oversized) per marked start, in
 // pixel order, at the tile's batch offset.
-__global__ __launch_bounds__(kNT) void k_batch_records(FrameBufs f) {
-    __shared__ uint32_t s_mask[kTilePix / 32], s_thk[kTilePix / 32];
-    if (f.ctr->cap_overflow) return;
-    const int tile = blockIdx.x, t = threadIdx.x;
+// By a block of kNT threads; s_mask and s_thk: kTilePix / 32 words each.
+__device__ inline void batch_records(const FrameBufs& f, int tile, uint32_t* s_mask, uint32_t* s_thk) {
+    const int t = threadIdx.x;
     if (t < kTilePix / 32) s_mask[t] = f.batch_mask[(size_t)tile * (kTilePix / 32) + t];
     // (mixed frames: which pixels hold a thick-hair fragment, as bits)
     const unsigned long long tb = __ballot(f.pix_thick && f.pix_thick[(size_t)tile * kTilePix + t] != 0);
@@ -1651,6 +1670,14 @@ __global__ __launch_bounds__(kNT) void k_batch_records(FrameBufs f) {
     const uint32_t pos = xcd_block_of(f.batch_start[tile] + idx, f.batch_start[f.T]);
     f.batches[pos] = pack_batch(tile, t, end, oversized, f.frag_base[tile] + off0, off1 - off0, thick);
     if (thick) f.thick_list[atomicAdd(&f.ctr->thick_batches, 1u)] = pos;
+}
+
+// Mixed frames, after the emit pass (which marks the thick-hair pixels); in other frames the emit
+// pass writes the records itself.
+__global__ __launch_bounds__(kNT) void k_batch_records(FrameBufs f) {
+    __shared__ uint32_t s_mask[kTilePix / 32], s_thk[kTilePix / 32];
+    if (f.ctr->cap_overflow) return;
+    batch_records(f, blockIdx.x, s_mask, s_thk);
 }
 
 // Emit pass: every fragment into the frame's fragment buffer at
@@ -1722,6 +1749,9 @@ __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
         atomicMax(&f.pix_kmax[q], s_kmax[t]);
         if (MIXED && s_thk[t]) f.pix_thick[q] = 1;
     }
+    // the tile's batch records, by the block of its first chunk (s_id is free once the waves pass the
+    // barrier above)
+    if (!MIXED && it.y == 0) batch_records(f, tile, s_id, s_id + kTilePix / 32);
     PHASE_END(f.ctr, 1);
 }
 
@@ -3467,8 +3497,7 @@ static hipError_t allow_lds(const void* fn, int bytes) {
 }
 
 hipError_t launch_bins(const SegRec* seg, int32_t nseg, const CamConst& cam, const BinPlan& p, uint32_t* M,
-                       uint4* blk, uint32_t* tot, uint32_t* tile_start, Counters* ctr, uint32_t* scan_tmp,
-                       hipStream_t st) {
+                       uint4* blk, uint32_t* tot, Counters* ctr, hipStream_t st) {
     const int ntx = (cam.W + kTile - 1) / kTile, nty = (cam.H + kTile - 1) / kTile, T = ntx * nty;
     hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_bin_count), 4 * p.range);
     if (e != hipSuccess) return e;
@@ -3478,8 +3507,7 @@ hipError_t launch_bins(const SegRec* seg, int32_t nseg, const CamConst& cam, con
                            t0, nt, M, blk);
     }
     hipLaunchKernelGGL(k_bin_offsets, dim3(blocks_for(T, 64)), dim3(1024), 0, st, M, p.nb, T, tot, blk, ctr);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    return launch_exscan(tot, tile_start, T, scan_tmp, st);
+    return hipGetLastError();
 }
 
 hipError_t launch_exscan(const uint32_t* cnt, uint32_t* start, int32_t n, uint32_t* scratch, hipStream_t st) {
@@ -3496,24 +3524,28 @@ hipError_t launch_exscan(const uint32_t* cnt, uint32_t* start, int32_t n, uint32
     return hipGetLastError();
 }
 
-hipError_t launch_scatter(const SegRec* seg, int32_t nseg, const CamConst& cam, const BinPlan& p,
-                          const uint32_t* tile_start, const uint32_t* M, uint32_t* list, const Counters* ctr,
-                          hipStream_t st) {
-    if (nseg == 0) return hipSuccess;
+hipError_t launch_scatter(const FrameBufs& f, int32_t nseg, const CamConst& cam, const BinPlan& p, const uint32_t* M,
+                          uint32_t* list, float* rgba, uint2* item_tab, uint32_t cap_items, hipStream_t st) {
     const int ntx = (cam.W + kTile - 1) / kTile, nty = (cam.H + kTile - 1) / kTile, T = ntx * nty;
     hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_scatter), 4 * p.range);
     if (e != hipSuccess) return e;
+    const FillArgs fill{f.pix_cnt, f.pix_off, f.pix_kmin, f.pix_kmax, f.opaque ? 0xFFFFFFFFu : 0u, f.pix_thick,
+                        reinterpret_cast<float4*>(rgba), rgba ? (size_t)cam.W * cam.H : 0, f.item_start, item_tab,
+                        cap_items};
+    // (a block per 8 tiles keeps the clearing spread over the chip whatever the segment count)
     for (int t0 = 0; t0 < T; t0 += p.range) {
         const int nt = std::min(p.range, T - t0);
-        hipLaunchKernelGGL(k_scatter, dim3(p.nb), dim3(kBinThreads), 4 * nt, st, seg, nseg, p.per_block, ntx, nty, t0,
-                           nt, tile_start, M, list, ctr);
+        const int grid = t0 == 0 ? std::max(p.nb, std::min(256, blocks_for(T, 8))) : p.nb;
+        hipLaunchKernelGGL(k_scatter, dim3(grid), dim3(kBinThreads), 4 * nt, st, f.seg, nseg, p.per_block, p.nb, ntx, nty,
+                           t0, nt, f.tile_start, M, list, f.ctr, fill);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_items_scan(const uint32_t* tile_start, int T, uint32_t* item_start, Counters* ctr,
+hipError_t launch_lists_scan(const uint32_t* tot, int T, uint32_t* tile_start, uint32_t* item_start, Counters* ctr,
                              uint32_t cap_pairs, uint32_t cap_items, hipStream_t st) {
-    hipLaunchKernelGGL(k_items_scan, dim3(1), dim3(1024), 0, st, tile_start, T, item_start, ctr, cap_pairs, cap_items);
+    hipLaunchKernelGGL(k_lists_scan, dim3(2), dim3(1024), 0, st, tot, T, tile_start, item_start, ctr, cap_pairs,
+                       cap_items);
     return hipGetLastError();
 }
 
@@ -3554,6 +3586,7 @@ hipError_t launch_tile_prep(const FrameBufs& f, hipStream_t st) {
 }
 
 hipError_t launch_batch_records(const FrameBufs& f, hipStream_t st) {
+    if (!f.pix_thick) return hipSuccess;   // (k_emit wrote them)
     hipLaunchKernelGGL(k_batch_records, dim3(f.T), dim3(kNT), 0, st, f);
     return hipGetLastError();
 }
@@ -3693,17 +3726,6 @@ hipError_t launch_build_ellipses(const float* vx, const float* vy, const float* 
 
 hipError_t launch_check_caps(const FrameBufs& f, const FrameCaps& caps, int stage, hipStream_t st) {
     hipLaunchKernelGGL(k_check_caps, dim3(1), dim3(64), 0, st, f, caps, stage);
-    return hipGetLastError();
-}
-
-hipError_t launch_fill_pix(const FrameBufs& f, size_t n, float* rgba, size_t n_rgba4, uint2* item_tab,
-                           uint32_t cap_items, hipStream_t st) {
-    const size_t m = std::max(std::max(n, n_rgba4), (size_t)f.T * 64);
-    if (m == 0) return hipSuccess;
-    const int nb = (int)std::min<size_t>((m + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_fill_pix, dim3(nb), dim3(256), 0, st, f.pix_cnt, f.pix_off, f.pix_kmin, f.pix_kmax,
-                       f.opaque ? 0xFFFFFFFFu : 0u, f.pix_thick, n, reinterpret_cast<float4*>(rgba), rgba ? n_rgba4 : 0,
-                       f.item_start, f.T, item_tab, cap_items);
     return hipGetLastError();
 }
 
