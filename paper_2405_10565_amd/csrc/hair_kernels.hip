@@ -21,6 +21,7 @@
 // The integer-deciding steps (projection, snapping, half-width, depth key) are float32 with
 // one rounding per operation and no contraction, so they match a float32 reference bit for bit.
 #include <algorithm>
+#include <type_traits>
 
 #include "hair_internal.h"
 #include "hair_shading.h"
@@ -46,11 +47,15 @@ __device__ inline int wave_max(int v) {
 // by 1, 2, 4 and 8 lanes inside each row of 16 (lanes shifted in from outside the row add 0),
 // then the last lane of rows 0 and 2 added to rows 1 and 3, and lane 31 added to rows 2 and 3.
 // (No LDS permutes: six adds with a moved operand.)
-__device__ inline uint32_t wave_inclusive_sum(uint32_t x) {
+__device__ inline uint32_t row_inclusive_sum(uint32_t x) {   // over each row of 16 lanes
     x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);   // row_shr:1
     x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);   // row_shr:2
     x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);   // row_shr:4
     x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);   // row_shr:8
+    return x;
+}
+__device__ inline uint32_t wave_inclusive_sum(uint32_t x) {
+    x = row_inclusive_sum(x);
     x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);   // row_bcast:15 -> rows 1, 3
     x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);   // row_bcast:31 -> rows 2, 3
     return x;
@@ -596,6 +601,19 @@ __global__ __launch_bounds__(1024) void k_scan_add(uint32_t* __restrict__ out, c
     if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = base[nblocks];
 }
 
+// The largest s with s^2 < R^2 t_den (R^2 t_den >= 64): a square root, corrected in 64-bit
+// integers, so that |cross| <= s_max is exactly cross^2 < R^2 t_den.  Below 2^48 (every
+// strand) the float square root is within 3 of s (relative error under 2^-22 on s < 2^24),
+// above it the double one.
+__device__ inline int strip_smax(int R, int tden) {
+    const unsigned long long lim = (unsigned long long)(unsigned)(R * R) * (unsigned)tden - 1ull;
+    unsigned long long s = lim < (1ull << 48) ? (unsigned long long)__builtin_amdgcn_sqrtf((float)lim)
+                                              : (unsigned long long)sqrt((double)lim);
+    while (s * s > lim) --s;
+    while ((s + 1) * (s + 1) <= lim) ++s;
+    return (int)min(s, 0x7FFFFFFFull);
+}
+
 // Tile binning without device-wide atomics.  Block b owns the contiguous segment range
 // [b per_block, (b + 1) per_block) and counts, in LDS, its segments per tile of the range
 // [t0, t0 + nt) (the whole image unless it has more than kMaxLdsTiles tiles); the counts form
@@ -603,44 +621,96 @@ __global__ __launch_bounds__(1024) void k_scan_add(uint32_t* __restrict__ out, c
 // every tile list, and the scatter pass appends each segment at its block's LDS cursors.
 // A tile of the box of a wide segment (radius above 2 px) is kept only if the rectangle of its
 // pixel centres meets the segment's footprint (the slab 0 <= t_num <= t_den and the strip
-// |cross| <= R sqrt(t_den)): projected on the segment's direction and normal, the four corner
-// centres must overlap both.  Exact in integers (corner offsets below 2^15, products below
-// 2^30, cross^2 and R^2 t_den in 64 bits); for short, wide segments (thick hairs) this drops
-// the many box tiles beyond the segment's ends.  Thin segments keep their box's tiles.
-__device__ inline bool tile_meets_footprint(const SegRec& r, int tx, int ty) {
-    const int R = (r.hwfx & kHwMask) + 8;
-    if (R <= 32) return true;
-    const int dx = r.xb - r.xa, dy = r.yb - r.ya;
-    const int tden = dx * dx + dy * dy;
-    if (tden <= 0) return true;
-    const unsigned long long RR = (unsigned long long)(unsigned)(R * R) * (unsigned)tden;
-    const int ex0 = 16 * kTile * tx + 8 - r.xa, ex1 = ex0 + 16 * (kTile - 1);
-    const int ey0 = 16 * kTile * ty + 8 - r.ya, ey1 = ey0 + 16 * (kTile - 1);
-    int tmin = 0x7FFFFFFF, tmax = -0x7FFFFFFF - 1, cmin = 0x7FFFFFFF, cmax = -0x7FFFFFFF - 1;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int ex = (k & 1) ? ex1 : ex0, ey = (k & 2) ? ey1 : ey0;
-        const int tn = ex * dx + ey * dy, cr = ex * dy - ey * dx;
-        tmin = min(tmin, tn);
-        tmax = max(tmax, tn);
-        cmin = min(cmin, cr);
-        cmax = max(cmax, cr);
+// |cross| <= s_max, the largest s with s^2 < R^2 t_den): projected on the segment's direction and
+// normal, its four corner centres must overlap both.  For short, wide segments (thick hairs) this
+// drops the many box tiles beyond the segment's ends.  Thin segments keep their box's tiles.
+//
+// Along a row of tiles the projections' ends grow by 256 dx and 256 dy per tile, so each of the
+// four conditions bounds the tile's index by an exact floor division, and the row's tiles are one
+// interval: a hair of 75 px half-width, whose box has over a hundred tiles and whose footprint
+// meets a sixth of them, costs a dozen rows instead of a test per tile (64 k such segments at
+// 1080p: count and scatter 68 + 91 -> 32 + 43 us).  Exact in integers (corner offsets below
+// 2^15 + 2^18, products below 2^33: 64 bits; a row has at most 2^10 tiles, so a float quotient,
+// off by at most one, is settled by one exact test).
+struct FootprintRows {
+    bool wide;
+    int xa, ya, dx, dy, smax;
+    int K;                // the box's last tile column, from its first
+    float rdx, rdy;       // reciprocals of 256 |dx|, 256 |dy|
+
+    __device__ FootprintRows(const SegRec& r, const TileRect& rc) {
+        const int R = (r.hwfx & kHwMask) + 8;
+        xa = r.xa; ya = r.ya;
+        dx = r.xb - r.xa; dy = r.yb - r.ya;
+        const int tden = dx * dx + dy * dy;
+        wide = R > 32 && tden > 0;
+        smax = wide ? strip_smax(R, tden) : 0;
+        K = rc.tx1 - rc.tx0;
+        rdx = __builtin_amdgcn_rcpf(256.0f * (float)max(abs(dx), 1));
+        rdy = __builtin_amdgcn_rcpf(256.0f * (float)max(abs(dy), 1));
     }
-    if (tmax < 0 || tmin > tden) return false;
-    if (cmin > 0 && (unsigned long long)((long long)cmin * cmin) >= RR) return false;
-    if (cmax < 0 && (unsigned long long)((long long)cmax * cmax) >= RR) return false;
-    return true;
-}
+    // floor(n / d), clamped to [lo, hi] (|lo|, |hi| <= 2^11; rd = 1 / d)
+    __device__ static int floordiv(long long n, long long d, float rd, int lo, int hi) {
+        int q = (int)floorf(fminf(fmaxf((float)n * rd, (float)lo), (float)hi));
+        const long long p = (long long)q * d;
+        if (p > n) --q;
+        else if (p + d <= n) ++q;
+        return min(max(q, lo), hi);
+    }
+    // the k in [0, K] with c0 <= v + a k and w + a k <= c1, kept from [k0, k1]
+    __device__ void bound(long long v, long long w, long long c0, long long c1, long long a, float ra, int& k0,
+                          int& k1) const {
+        if (a > 0) {          // k >= ceil((c0 - v) / a), k <= floor((c1 - w) / a)
+            k0 = max(k0, -floordiv(v - c0, a, ra, -K - 1, 1));
+            k1 = min(k1, floordiv(c1 - w, a, ra, -1, K + 1));
+        } else if (a < 0) {   // k <= floor((v - c0) / |a|), k >= ceil((w - c1) / |a|)
+            k1 = min(k1, floordiv(v - c0, -a, ra, -1, K + 1));
+            k0 = max(k0, -floordiv(c1 - w, -a, ra, -K - 1, 1));
+        } else if (v < c0 || w > c1) {
+            k1 = -1;
+        }
+    }
+    // the tiles of row ty that meet the footprint, from the box's [lo, hi] = [tx0, tx1]
+    __device__ void clip(int ty, int tx0, int& lo, int& hi) const {
+        if (!wide) return;
+        constexpr int kSpan = 16 * (kTile - 1);
+        const long long ex = 16 * kTile * tx0 + 8 - xa, ey = 16 * kTile * ty + 8 - ya;
+        const long long tden = (long long)dx * dx + (long long)dy * dy;
+        // at the box's first tile: t_num and cross over the corners
+        const long long t = ex * dx + ey * dy, c = ex * dy - ey * dx;
+        const long long tmin = t + min(0, kSpan * dx) + min(0, kSpan * dy);
+        const long long tmax = t + max(0, kSpan * dx) + max(0, kSpan * dy);
+        const long long cmin = c + min(0, kSpan * dy) + min(0, -kSpan * dx);
+        const long long cmax = c + max(0, kSpan * dy) + max(0, -kSpan * dx);
+        int k0 = 0, k1 = K;
+        bound(tmax, tmin, 0, tden, 16ll * kTile * dx, rdx, k0, k1);
+        bound(cmax, cmin, -(long long)smax, smax, 16ll * kTile * dy, rdy, k0, k1);
+        lo = tx0 + k0;
+        hi = tx0 + k1;
+    }
+};
 
 template <class F>
 __device__ inline void for_each_tile_in_range(const SegRec& r, int ntx, int nty, int t0, int nt, F&& f) {
     if (!(r.hwfx & kFlagVisible)) return;
     const TileRect rc = tile_rect(r, ntx, nty);
-    for (int ty = rc.ty0; ty <= rc.ty1; ++ty)
-        for (int tx = rc.tx0; tx <= rc.tx1; ++tx) {
+    if ((r.hwfx & kHwMask) + 8 <= 32) {
+        for (int ty = rc.ty0; ty <= rc.ty1; ++ty)
+            for (int tx = rc.tx0; tx <= rc.tx1; ++tx) {
+                const int l = ty * ntx + tx - t0;
+                if ((unsigned)l < (unsigned)nt) f(l);
+            }
+        return;
+    }
+    const FootprintRows fp(r, rc);
+    for (int ty = rc.ty0; ty <= rc.ty1; ++ty) {
+        int lo = rc.tx0, hi = rc.tx1;
+        fp.clip(ty, rc.tx0, lo, hi);
+        for (int tx = lo; tx <= hi; ++tx) {
             const int l = ty * ntx + tx - t0;
-            if ((unsigned)l < (unsigned)nt && tile_meets_footprint(r, tx, ty)) f(l);
+            if ((unsigned)l < (unsigned)nt) f(l);
         }
+    }
 }
 
 // The first pass also leaves per-block segment statistics in blk[b] = (visible, culled as too
@@ -877,18 +947,6 @@ struct CovSetup {
                  //  bits of 16 |dv| | first pixel (8 bits) << 19 | last minor offset (4 bits) << 27 | steep << 31)
 };
 
-// The largest s with s^2 < R^2 t_den (R^2 t_den >= 64): a square root, corrected in 64-bit
-// integers, so that |cross| <= s_max is exactly cross^2 < R^2 t_den.  Below 2^48 (every
-// strand) the float square root is within 3 of s (relative error under 2^-22 on s < 2^24),
-// above it the double one.
-__device__ inline int strip_smax(int R, int tden) {
-    const unsigned long long lim = (unsigned long long)(unsigned)(R * R) * (unsigned)tden - 1ull;
-    unsigned long long s = lim < (1ull << 48) ? (unsigned long long)__builtin_amdgcn_sqrtf((float)lim)
-                                              : (unsigned long long)sqrt((double)lim);
-    while (s * s > lim) --s;
-    while ((s + 1) * (s + 1) <= lim) ++s;
-    return (int)min(s, 0x7FFFFFFFull);
-}
 constexpr int kCovLinesPerWave = 64 * kTile;   // a segment has at most kTile lines in a tile
 
 // The strip |cross| <= strip_vis holds every fragment whose coverage alpha is not exactly zero
@@ -907,9 +965,10 @@ __device__ inline int strip_opaque(float hw, int tden) {
 }
 // The smallest depth key a segment's fragments can have (its nearer end; 8 ulps of slack for the
 // rounding of the interpolation between the ends).
-__device__ inline uint32_t nearest_key(const SegRec& s) {
-    return 0xFFFFFFFFu - __float_as_uint(fmaxf(s.iza, s.izb)) - 8u;
+__device__ inline uint32_t nearest_key(const float2 iz) {
+    return 0xFFFFFFFFu - __float_as_uint(fmaxf(iz.x, iz.y)) - 8u;
 }
+__device__ inline uint32_t nearest_key(const SegRec& s) { return nearest_key(make_float2(s.iza, s.izb)); }
 
 // floor(n / d) for 1 <= d <= 2^18 where it lies in [-17, 17]; a quotient beyond that range
 // comes back beyond [-17, 16] on its own side.  rd: the hardware reciprocal of d.
@@ -925,10 +984,14 @@ __device__ inline int floordiv_small(int n, int d, float rd) {
 // line count.  Ends with a block barrier (all threads must call it).  BOUND: the strip whose
 // pixels are enumerated: every fragment (kAll), those with coverage (kVisible) or the opaque
 // ones (kOpaque).
+// drop(i0, i1, j0, j1): the segment's box in the tile (pixel columns and rows); true leaves it out.
 enum CovBound { kAll, kVisible, kOpaque };
-template <CovBound BOUND>
+struct KeepAll {
+    __device__ bool operator()(int, int, int, int) const { return false; }
+};
+template <CovBound BOUND, class D = KeepAll>
 __device__ inline uint32_t cov_setup(const SegRec& s, bool valid, int px0, int py0, int W, int H, CovSetup* s_cov,
-                                     uint8_t* s_own) {
+                                     uint8_t* s_own, D&& drop = D{}) {
     const int t = threadIdx.x, lane = t & 63;
     uint32_t nl = 0;
     CovSetup c{};
@@ -936,11 +999,20 @@ __device__ inline uint32_t cov_setup(const SegRec& s, bool valid, int px0, int p
         const int dx = s.xb - s.xa, dy = s.yb - s.ya;
         const int tden = dx * dx + dy * dy;
         const int R = (s.hwfx & kHwMask) + 8;
-        const int i0 = max(px0, ((min(s.xa, s.xb) - R - 8) >> 4) + 1);
-        const int i1 = min(min(px0 + kTile, W) - 1, ((max(s.xa, s.xb) + R - 8 + 15) >> 4) - 1);
-        const int j0 = max(py0, ((min(s.ya, s.yb) - R - 8) >> 4) + 1);
-        const int j1 = min(min(py0 + kTile, H) - 1, ((max(s.ya, s.yb) + R - 8 + 15) >> 4) - 1);
-        if (tden > 0 && i0 <= i1 && j0 <= j1) {
+        int sm = -1, i0 = 0, i1 = -1, j0 = 0, j1 = -1;
+        if (tden > 0) {
+            sm = BOUND == kOpaque ? strip_opaque(s.hw, tden) : strip_smax(R, tden);
+            if (BOUND == kVisible) sm = strip_vis(s.hw, tden, sm);
+            // the footprint's own box: across the segment it reaches sm / sqrt(t_den), which adds
+            // sm |dy| / t_den along x and sm |dx| / t_den along y (rounded up; at most the radius)
+            const float il = __builtin_amdgcn_rcpf((float)tden) * (float)sm;
+            const int rx = min(R, (int)((float)abs(dy) * il) + 2), ry = min(R, (int)((float)abs(dx) * il) + 2);
+            i0 = max(px0, ((min(s.xa, s.xb) - rx - 8) >> 4) + 1);
+            i1 = min(min(px0 + kTile, W) - 1, ((max(s.xa, s.xb) + rx - 8 + 15) >> 4) - 1);
+            j0 = max(py0, ((min(s.ya, s.yb) - ry - 8) >> 4) + 1);
+            j1 = min(min(py0 + kTile, H) - 1, ((max(s.ya, s.yb) + ry - 8 + 15) >> 4) - 1);
+        }
+        if (sm >= 0 && i0 <= i1 && j0 <= j1 && !drop(i0 - px0, i1 - px0, j0 - py0, j1 - py0)) {
             const bool steep = abs(dy) >= abs(dx);
             const int au = steep ? s.ya : s.xa, av = steep ? s.xa : s.ya;
             const int du = steep ? dy : dx, dv = steep ? dx : dy;
@@ -956,8 +1028,6 @@ __device__ inline uint32_t cov_setup(const SegRec& s, bool valid, int px0, int p
             const int lu = u0 - (steep ? py0 : px0), lv = vmin - (steep ? px0 : py0);   // 0..15
             const int pix0 = steep ? lu * kTile + lv : lv * kTile + lu;
             c.g0 = make_int4(sgu * cr, sgv * tn, -16 * sgu * dv, 16 * sgv * du);
-            int sm = BOUND == kOpaque ? strip_opaque(s.hw, tden) : strip_smax(R, tden);
-            if (BOUND == kVisible) sm = strip_vis(s.hw, tden, sm);
             c.g1 = make_int4(sm, dv < 0 ? 1 - tden : 0, dv < 0 ? 0 : tden - 1, 0);
             c.g2 = make_float4(__builtin_amdgcn_rcpf((float)B), __builtin_amdgcn_rcpf((float)max(A, 1)),
                                __int_as_float(B),
@@ -978,9 +1048,14 @@ __device__ inline uint32_t cov_setup(const SegRec& s, bool valid, int px0, int p
 
 // Calls f(p, tnum, tden, owner, cross) for every fragment of the wave's segments in this tile
 // (p: the pixel's index in the tile; owner: the block thread whose segment it is; cross up to
-// its sign).  total and the staging from cov_setup.
-template <class F>
-__device__ inline void wave_coverage(const CovSetup* s_cov, const uint8_t* s_own, uint32_t total, F&& f) {
+// its sign).  total and the staging from cov_setup.  line(owner, p, n, steep) sees each line first
+// (its first pixel and number of pixels, along the row when steep, else along the column) and may
+// take it whole by returning true.
+struct NoLine {
+    __device__ bool operator()(int, int, int, bool) const { return false; }
+};
+template <class F, class L = NoLine>
+__device__ inline void wave_coverage(const CovSetup* s_cov, const uint8_t* s_own, uint32_t total, F&& f, L&& line = L{}) {
     const int t = threadIdx.x, lane = t & 63, wbase = t & ~63;
     const uint8_t* own = s_own + (t >> 6) * kCovLinesPerWave;
     for (uint32_t g = (uint32_t)lane; g < total; g += 64) {
@@ -1011,6 +1086,7 @@ __device__ inline void wave_coverage(const CovSetup* s_cov, const uint8_t* s_own
         const int tden = hi - lo + 1;
         const int sv = bits < 0 ? 1 : kTile;                  // pixel step along the minor axis
         int p = ((bits >> 19) & 0xFF) + __mul24(l, bits < 0 ? kTile : 1) + __mul24(x0, sv);
+        if (line(o, p, x1 - x0 + 1, bits < 0)) continue;
         // t_num itself: the normalised t times the sign of dv (lo < 0 exactly when dv < 0, as
         // then t_den >= 2)
         const int sgn = lo < 0 ? -1 : 1;
@@ -1026,6 +1102,16 @@ __device__ inline uint32_t depth_key_iz(float iza, float izb, int tnum, int tden
     const float iz = iza + t * (izb - iza);
     return 0xFFFFFFFFu - __float_as_uint(iz);
 }
+
+// A cheap upper bound of a fragment's inverse depth, for the tests against the opaque keys: the
+// reciprocal product in place of the division errs by under 2^-21 of the nearer end, and the bound
+// adds 2^-20 of it.  Most fragments of a stack of thick hairs lie clearly behind and need no more.
+__device__ inline float iz_bound(const float2 iz, int tnum, int tden) {
+    const float t = (float)tnum * __builtin_amdgcn_rcpf((float)tden);
+    return (iz.x + t * (iz.y - iz.x)) + fmaxf(iz.x, iz.y) * 0x1p-20f;
+}
+// The inverse depth of an opaque key (0 for none: nothing lies behind it).
+__device__ inline float iz_of_key(uint32_t key) { return __uint_as_float(0xFFFFFFFFu - key); }
 
 // The global segment id of a fragment record's second word (see FrameBufs::gid): the record
 // holds it, or the index of the segment in the tile's list.
@@ -1382,15 +1468,55 @@ __global__ __launch_bounds__(256) void k_tile_items(const uint32_t* __restrict__
     items[t] = (n + kNT - 1) / kNT;
 }
 
-// The largest of the block's values (256 threads).  Ends with a barrier.
-__device__ inline uint32_t block_max_u32(uint32_t v, uint32_t* s_tmp) {
-    for (int off = 32; off >= 1; off >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, off));
-    if ((threadIdx.x & 63) == 0) s_tmp[threadIdx.x >> 6] = v;
+// What is known to hide in a tile: each pixel's opaque key and the largest key of every run of four
+// pixels along the rows and the columns, so that a segment or a line of one that lies behind all it
+// could cover is recognised without a test per pixel.
+struct HideLds {
+    uint32_t z[kTilePix];
+    uint4 row[kTile], col[kTile];   // [line]: its four runs
+    uint4 cell[4];                  // [row of 4 x 4 cells]: its four cells
+};
+struct NoHide {   // (frames without an opaque pass)
+    uint32_t z[1];
+    uint4 row[1], col[1], cell[1];
+};
+template <bool ZC> using HideOf = std::conditional_t<ZC, HideLds, NoHide>;
+// Sets h from the block's pixel keys z0 (0 for pixels off the image).  All threads call it; ends
+// with a barrier.
+__device__ inline void hide_setup(HideLds& h, uint32_t z0) {
+    const int t = threadIdx.x;
+    h.z[t] = z0;
+    const uint32_t a = max(z0, (uint32_t)__shfl_xor((int)z0, 1));
+    const uint32_t r = max(a, (uint32_t)__shfl_xor((int)a, 2));
+    const uint32_t b = max(z0, (uint32_t)__shfl_xor((int)z0, 16));
+    const uint32_t c = max(b, (uint32_t)__shfl_xor((int)b, 32));   // (a wave holds four rows)
+    const uint32_t d = max(r, (uint32_t)__shfl_xor((int)r, 16));
+    const uint32_t e = max(d, (uint32_t)__shfl_xor((int)d, 32));
+    if ((t & 3) == 0) reinterpret_cast<uint32_t*>(h.row)[t >> 2] = r;
+    if ((t & 63) < 16) reinterpret_cast<uint32_t*>(h.col)[4 * (t & 15) + (t >> 6)] = c;
+    if ((t & 0x33) == 0) reinterpret_cast<uint32_t*>(h.cell)[4 * (t >> 6) + ((t >> 2) & 3)] = e;
     __syncthreads();
-    v = s_tmp[0];
-#pragma unroll
-    for (int w = 1; w < kNT / 64; ++w) v = max(v, s_tmp[w]);
-    return v;
+}
+// The largest of a line's four runs (or cells) that its pixels [a, b] touch.
+__device__ inline uint32_t runs_max(const uint4 g, int a, int b) {
+    uint32_t m = a < 4 ? g.x : 0u;
+    m = max(m, a < 8 && b >= 4 ? g.y : 0u);
+    m = max(m, a < 12 && b >= 8 ? g.z : 0u);
+    return max(m, b >= 12 ? g.w : 0u);
+}
+// Whether a box of the tile's pixels lies behind all its cells, with nearest the smallest key its
+// segment can have.
+template <class H>
+__device__ inline bool box_hidden(const H& h, uint32_t nearest, int i0, int i1, int j0, int j1) {
+    uint32_t m = 0u;
+    for (int r = j0 >> 2; r <= j1 >> 2; ++r) m = max(m, runs_max(h.cell[r], i0, i1));
+    return nearest > m;
+}
+// Whether a line of n pixels from p (see wave_coverage) does.
+template <class H>
+__device__ inline bool line_hidden(const H& h, uint32_t nearest, int p, int n, bool steep) {
+    const int a = steep ? p & 15 : p >> 4;
+    return nearest > runs_max(steep ? h.row[p >> 4] : h.col[p & 15], a, a + n - 1);
 }
 
 // Opaque pass (frames that can hold thick hairs): per pixel the smallest depth key among its
@@ -1403,11 +1529,16 @@ __device__ inline uint32_t block_max_u32(uint32_t v, uint32_t* s_tmp) {
 // its farthest one, so its key maximum is that key already, and k_tile_prep clears the others
 // (and flags the pixels in pix_off, kHidesBit, so that the emit pass can tell them apart).
 // 150k x 64 strands as 1000 thick hairs at 1080p: 99.7% of its 43 M fragments are hidden, and the
-// frame takes 0.57 ms instead of 3.49 (this pass 0.14, the shading 0.03 instead of 1.97).  A
+// frame takes 0.32 ms instead of 3.49 (this pass 0.07, the shading 0.03 instead of 1.97).  A
 // combed groom at a middle view, where strands and thick hairs mix and a third of the fragments
-// is hidden: 1.03 instead of 1.16 ms.  Bound by the per-line coverage arithmetic (VALU).
-__global__ __launch_bounds__(kNT) void k_opaque(FrameBufs f, CamConst cam) {
-    __shared__ uint32_t s_z[kTilePix], s_tmp[kNT / 64];
+// is hidden: 1.01 instead of 1.14 ms.  Bound by the per-line coverage arithmetic (VALU).
+// first: only 4 kFirstLanes segments of every tile, spread over its list (a contiguous run of it
+// would hold the segments of a few neighbouring hairs, which may lie at the back).  A block is
+// bound by the latency of its lines' pixels, so this launch is short, and what it finds hides most
+// segments of the second one, which takes them all: 43 M fragments in 5 k chunks, 119 -> 20 + 45 us.
+constexpr int kFirstLanes = 16;
+__global__ __launch_bounds__(kNT) void k_opaque(FrameBufs f, CamConst cam, int first) {
+    __shared__ HideLds s_hide;
     __shared__ CovSetup s_cov[kNT];
     __shared__ uint8_t s_own[kNT / 64 * kCovLinesPerWave];
     __shared__ float2 s_iz[kNT];
@@ -1417,26 +1548,31 @@ __global__ __launch_bounds__(kNT) void k_opaque(FrameBufs f, CamConst cam) {
     const uint32_t item = xcd_contiguous(blockIdx.x, n_items);
     const int t = threadIdx.x;
     const uint2 it = f.item_tab[item];
+    if (first && it.y > 0) return;
     const int tile = (int)it.x;
     const int px0 = (tile % f.ntx) * kTile, py0 = (tile / f.ntx) * kTile;
     const uint32_t lstart = f.tile_start[tile];
     const uint32_t n = f.tile_start[tile + 1] - lstart;
-    const uint32_t j = it.y * kNT + t;
+    const uint32_t j = first && n > (uint32_t)kNT ? (uint32_t)((unsigned long long)t * n / kNT) : it.y * kNT + t;
     SegRec s{};
     if (j < n) s = f.seg[f.list[lstart + j]];
     const size_t q = (size_t)tile * kTilePix + t;
     const int gx = px0 + (t % kTile), gy = py0 + (t / kTile);
-    const uint32_t z0 = f.pix_kmax[q];
-    s_z[t] = z0;
-    const uint32_t zmax = block_max_u32(gx < cam.W && gy < cam.H ? z0 : 0u, s_tmp);
+    const uint32_t z0 = gx < cam.W && gy < cam.H ? f.pix_kmax[q] : 0u;
+    hide_setup(s_hide, z0);
+    uint32_t* s_z = s_hide.z;
     s_iz[t] = make_float2(s.iza, s.izb);
-    const bool valid = j < n && s.hw > 0.5f + kOpaqueMargin && nearest_key(s) <= zmax;
-    const uint32_t total = cov_setup<kOpaque>(s, valid, px0, py0, cam.W, cam.H, s_cov, s_own);
+    const bool valid = j < n && s.hw > 0.5f + kOpaqueMargin && (!first || (t & 63) % (64 / kFirstLanes) == 0);
+    const uint32_t total = cov_setup<kOpaque>(
+        s, valid, px0, py0, cam.W, cam.H, s_cov, s_own,
+        [&](int i0, int i1, int j0, int j1) { return box_hidden(s_hide, nearest_key(s), i0, i1, j0, j1); });
     wave_coverage(s_cov, s_own, total, [&](int p, int tnum, int tden, int o, int) {
         const float2 iz = s_iz[o];
+        const uint32_t z = s_z[p];
+        if (iz_bound(iz, tnum, tden) < iz_of_key(z)) return;
         const uint32_t key = depth_key_iz(iz.x, iz.y, tnum, tden);
-        if (key < s_z[p]) atomicMin(&s_z[p], key);
-    });
+        if (key < z) atomicMin(&s_z[p], key);
+    }, [&](int o, int p, int n, bool steep) { return line_hidden(s_hide, nearest_key(s_iz[o]), p, n, steep); });
     __syncthreads();
     if (s_z[t] < z0) atomicMin(&f.pix_kmax[q], s_z[t]);
 }
@@ -1450,10 +1586,11 @@ __global__ __launch_bounds__(kNT) void k_opaque(FrameBufs f, CamConst cam) {
 template <bool TRIM, bool ZC>
 __global__ __launch_bounds__(kNT) void k_count(FrameBufs f, CamConst cam) {
     __shared__ uint32_t s_cnt[kTilePix];
-    __shared__ uint32_t s_z[ZC ? kTilePix : 1], s_tmp[kNT / 64];
+    __shared__ HideOf<ZC> s_hide[1];
+    __shared__ uint32_t s_dr[ZC ? kTilePix : 1], s_dc[ZC ? kTilePix : 1];   // see below
     __shared__ float2 s_iz[ZC ? kNT : 1];
     __shared__ CovSetup s_cov[kNT];
-    __shared__ int s_vis[TRIM || ZC ? kNT : 1];   // |cross| up to which the segment's fragments are stored
+    __shared__ int s_vis[TRIM ? kNT : 1];   // |cross| up to which the segment's fragments have coverage
     __shared__ uint8_t s_own[kNT / 64 * kCovLinesPerWave];
     PHASE_BEGIN();
     const uint32_t n_items = f.item_start[f.T];
@@ -1470,32 +1607,44 @@ __global__ __launch_bounds__(kNT) void k_count(FrameBufs f, CamConst cam) {
     SegRec s{};
     if (j < n) s = f.seg[f.list[lstart + j]];
     const size_t q = (size_t)tile * kTilePix + t;
-    bool show = true;
     if constexpr (ZC) {
-        const uint32_t z0 = f.pix_kmax[q];
-        s_z[t] = z0;
+        s_dr[t] = s_dc[t] = 0u;
         s_iz[t] = make_float2(s.iza, s.izb);
         const int gx = px0 + (t % kTile), gy = py0 + (t / kTile);
-        const uint32_t zmax = block_max_u32(gx < cam.W && gy < cam.H ? z0 : 0u, s_tmp);
-        show = nearest_key(s) <= zmax;
+        hide_setup(s_hide[0], gx < cam.W && gy < cam.H ? f.pix_kmax[q] : 0u);
     }
-    if constexpr (TRIM || ZC) {
+    if constexpr (TRIM) {
         const int dx = s.xb - s.xa, dy = s.yb - s.ya;
-        s_vis[t] = !show ? -1 : (TRIM ? strip_vis(s.hw, dx * dx + dy * dy, 0x7FFFFFFF) : 0x7FFFFFFF);
+        s_vis[t] = strip_vis(s.hw, dx * dx + dy * dy, 0x7FFFFFFF);
     }
     const uint32_t total = cov_setup<kAll>(s, j < n, px0, py0, cam.W, cam.H, s_cov, s_own);
     wave_coverage(s_cov, s_own, total, [&](int p, int tnum, int tden, int o, int cr) {
         bool stored = true;
-        if constexpr (TRIM || ZC) stored = abs(cr) <= s_vis[o];
+        if constexpr (TRIM) stored = abs(cr) <= s_vis[o];
         if constexpr (ZC) {
             if (stored) {
                 const float2 iz = s_iz[o];
-                stored = depth_key_iz(iz.x, iz.y, tnum, tden) <= s_z[p];
+                stored = depth_key_iz(iz.x, iz.y, tnum, tden) <= s_hide[0].z[p];
             }
         }
         atomicAdd(&s_cnt[p], stored ? 1u : 0x10000u);
+    }, [&](int o, int p, int n, bool steep) {
+        // a line hidden as a whole: its pixels are only counted, as differences along the line (+1
+        // where it begins, -1 behind its end) that two row sums add up below
+        if (!ZC || !line_hidden(s_hide[0], nearest_key(s_iz[ZC ? o : 0]), p, n, steep)) return false;
+        uint32_t* d = steep ? s_dr : s_dc;
+        const int i = steep ? p : ((p & 15) << 4 | p >> 4);   // (columns are kept transposed)
+        atomicAdd(&d[ZC ? i : 0], 1u);
+        if ((i & 15) + n < kTile) atomicSub(&d[ZC ? i + n : 0], 1u);
+        return true;
     });
     __syncthreads();
+    if constexpr (ZC) {
+        const uint32_t r = row_inclusive_sum(s_dr[t]), v = row_inclusive_sum(s_dc[t]);
+        if (r) atomicAdd(&s_cnt[t], r << 16);
+        if (v) atomicAdd(&s_cnt[(t & 15) << 4 | t >> 4], v << 16);
+        __syncthreads();
+    }
     uint32_t c = s_cnt[t];
     uint32_t base = 0;
     if (TRIM || ZC) {
@@ -1712,7 +1861,7 @@ __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
     __shared__ CovSetup s_cov[kNT];
     __shared__ uint8_t s_own[kNT / 64 * kCovLinesPerWave];
     __shared__ float2 s_iz[kNT];
-    __shared__ uint32_t s_z[ZC ? kTilePix : 1], s_tmp[kNT / 64];
+    __shared__ HideOf<ZC> s_hide[1];
     PHASE_BEGIN();
     const uint32_t n_items = f.item_start[f.T];
     if (blockIdx.x >= n_items || f.ctr->cap_overflow) return;
@@ -1740,26 +1889,29 @@ __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
     }
     s_iz[t] = make_float2(s.iza, s.izb);
     s_id[t] = (f.gid ? gseg : j) | (MIXED && (s.hwfx & kFlagThick) ? 0x80000000u : 0u);
-    bool valid = j < n;
+    const bool valid = j < n;
     if constexpr (ZC) {
         const uint32_t z0 = off & kHidesBit ? f.pix_kmax[q] : 0xFFFFFFFFu;
-        s_z[t] = z0;
         const int gx = px0 + (t % kTile), gy = py0 + (t / kTile);
-        const uint32_t zmax = block_max_u32(gx < cam.W && gy < cam.H ? z0 : 0u, s_tmp);   // (a barrier: every lane)
-        valid = valid && nearest_key(s) <= zmax;
+        hide_setup(s_hide[0], gx < cam.W && gy < cam.H ? z0 : 0u);
     }
-    const uint32_t total = f.trim ? cov_setup<kVisible>(s, valid, px0, py0, cam.W, cam.H, s_cov, s_own)
-                                  : cov_setup<kAll>(s, valid, px0, py0, cam.W, cam.H, s_cov, s_own);
+    auto drop = [&](int i0, int i1, int j0, int j1) {
+        return ZC && box_hidden(s_hide[0], nearest_key(s), i0, i1, j0, j1);
+    };
+    const uint32_t total = f.trim ? cov_setup<kVisible>(s, valid, px0, py0, cam.W, cam.H, s_cov, s_own, drop)
+                                  : cov_setup<kAll>(s, valid, px0, py0, cam.W, cam.H, s_cov, s_own, drop);
     wave_coverage(s_cov, s_own, total, [&](int p, int tnum, int tden, int o, int) {
         const float2 iz = s_iz[o];
         const uint32_t key = depth_key_iz(iz.x, iz.y, tnum, tden);
-        if (ZC && key > s_z[p]) return;
+        if (ZC && key > s_hide[0].z[ZC ? p : 0]) return;
         const uint32_t slot = atomicAdd(&s_cur[p], 1u);
         atomicMin(&s_kmin[p], key);
         atomicMax(&s_kmax[p], key);
         const uint32_t id = s_id[o];
         if (MIXED && (id >> 31)) s_thk[p] = 1;
         f.frags[s_pos[p] + slot] = make_uint2(key, (id & 0xFFFFFFu) | ((uint32_t)p << 24));
+    }, [&](int o, int p, int n, bool steep) {
+        return ZC && line_hidden(s_hide[0], nearest_key(s_iz[o]), p, n, steep);
     });
     __syncthreads();
     if (s_cur[t]) {
@@ -3587,7 +3739,8 @@ hipError_t launch_tile_items(const uint32_t* tile_start, int T, uint32_t* items,
 hipError_t launch_count(const FrameBufs& f, const CamConst& cam, uint32_t grid, hipStream_t st) {
     if (grid == 0) return hipSuccess;
     if (f.opaque) {
-        hipLaunchKernelGGL(k_opaque, dim3(grid), dim3(kNT), 0, st, f, cam);
+        hipLaunchKernelGGL(k_opaque, dim3(grid), dim3(kNT), 0, st, f, cam, 1);
+        hipLaunchKernelGGL(k_opaque, dim3(grid), dim3(kNT), 0, st, f, cam, 0);
         if (f.trim) hipLaunchKernelGGL((k_count<true, true>), dim3(grid), dim3(kNT), 0, st, f, cam);
         else hipLaunchKernelGGL((k_count<false, true>), dim3(grid), dim3(kNT), 0, st, f, cam);
     } else if (f.trim) {
