@@ -1,12 +1,15 @@
 """Writes hair_fastmath_coef.h: polynomial coefficients of the shading kernels' arcsine and
-arctangent, and the 8-point Gauss-Legendre rule with the refraction constants of its nodes.
+arctangent and hyperbolic tangent, and the 8-point Gauss-Legendre rule with the refraction constants of its nodes.
 
     python paper_2405_10565_amd/csrc/gen_fastmath.py [--check]
 
 Fits (float64, Lawson's iteratively reweighted least squares toward the minimax fit, on
 Chebyshev nodes):
   asin(z) = z + z^3 P(z^2)     z in [0, 1/2], P of degree 4, relative error of asin < 1e-8
+  asin(z) = z + z^3 W(z^2)     z in [0, 0.68], W of degree 7, relative error of asin < 1e-8
   atan(a) = a Q(a^2)           a in [0, 1],   Q of degree 8, absolute error < 1e-8
+                               (also as Q / 2 and as Q / 2 pi: the angle in turns)
+  tanh(x) = x + x^3 H(x^2)     x in [0, 5/8], H of degree 4, relative error of tanh < 1e-8
 The kernels reduce |x| > 1/2 by asin(x) = pi/2 - 2 asin(sqrt((1 - x) / 2)) and atan2 to
 [0, 1] by octant symmetry.  --check only verifies that the header on disk is current.
 """
@@ -39,13 +42,16 @@ def lawson(f, lo, hi, deg, weight, iters=60, n=4000):
 def coefficients():
     p, ep = lawson(lambda t: (np.arcsin(np.sqrt(t)) - np.sqrt(t)) / t ** 1.5, 1e-12, 0.25, 4, lambda t: t)
     q, eq = lawson(lambda t: np.arctan(np.sqrt(t)) / np.sqrt(t), 1e-12, 1.0, 8, np.sqrt)
-    x, w = np.polynomial.legendre.leggauss(8)
-    return {"asin_p": p, "asin_err": ep, "atan_q": q, "atan_err": eq, "gl_x": x, "gl_w": w,
+    aw, eaw = lawson(lambda t: (np.arcsin(np.sqrt(t)) - np.sqrt(t)) / t ** 1.5, 1e-12, 0.68 ** 2, 7, lambda t: t)
+    h, eh = lawson(lambda t: (np.tanh(np.sqrt(t)) - np.sqrt(t)) / t ** 1.5, 1e-12, 0.625 ** 2, 4, lambda t: t)
+    x, w = (v[4:] for v in np.polynomial.legendre.leggauss(8))
+    return {"asin_p": p, "asin_err": ep, "atan_q": q, "atan_err": eq, "asin_w": aw, "asin_w_err": eaw,
+            "tanh_h": h, "tanh_err": eh, "gl_x": x, "gl_w": w,
             "gl_gamma_o": np.arcsin(x), "gl_cos_gamma_o": np.sqrt((1 - x) * (1 + x))}
 
 
-def fmt(v):
-    return ", ".join(f"{float(c):.17g}f" for c in v)
+def fmt(v, suffix="f"):
+    return ", ".join(f"{float(c):.17g}{suffix}" for c in v)
 
 
 def render() -> str:
@@ -59,13 +65,19 @@ namespace hair {{
 constexpr float kAsinP[5] = {{{fmt(c['asin_p'])}}};
 // atan(a) = a Q(a^2) on [0, 1]; Q ascending, absolute error {c['atan_err']:.1e}
 constexpr float kAtanQ[9] = {{{fmt(c['atan_q'])}}};
+constexpr float kAtanHalfQ[9] = {{{fmt(c['atan_q'] / 2)}}};
+constexpr float kAtanTurnsQ[9] = {{{fmt(c['atan_q'] / (2 * np.pi))}}};
+// asin(z) = z + z^3 W(z^2) on [0, 0.68]; W ascending, relative error {c['asin_w_err']:.1e}
+constexpr float kAsinW[8] = {{{fmt(c['asin_w'])}}};
+// tanh(x) = x + x^3 H(x^2) on [0, 5/8]; H ascending, relative error {c['tanh_err']:.1e}
+constexpr float kTanhH[5] = {{{fmt(c['tanh_h'])}}};
 
-// 8-point Gauss-Legendre rule on [-1, 1], and at each node h_k the incidence angle
-// gamma_o = asin(h_k) and cos(gamma_o) = sqrt(1 - h_k^2).
-__constant__ static const float kGLx[8] = {{{fmt(c['gl_x'])}}};
-__constant__ static const float kGLw[8] = {{{fmt(c['gl_w'])}}};
-__constant__ static const float kGLgo[8] = {{{fmt(c['gl_gamma_o'])}}};
-__constant__ static const float kGLcgo[8] = {{{fmt(c['gl_cos_gamma_o'])}}};
+// 8-point Gauss-Legendre rule on [-1, 1]: its nodes h_k > 0 (the rule is symmetric), weights, and at
+// each node the incidence angle gamma_o = asin(h_k) and cos(gamma_o) = sqrt(1 - h_k^2).
+constexpr float kGLx[4] = {{{fmt(c['gl_x'])}}};
+constexpr float kGLw[4] = {{{fmt(c['gl_w'])}}};
+constexpr double kGLgo[4] = {{{fmt(c['gl_gamma_o'], '')}}};
+constexpr float kGLcgo[4] = {{{fmt(c['gl_cos_gamma_o'])}}};
 
 }}  // namespace hair
 """

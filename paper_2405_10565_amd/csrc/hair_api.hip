@@ -13,6 +13,7 @@
 #include <string>
 #include <vector>
 
+#include "hair_fastmath_coef.h"
 #include "hair_internal.h"
 
 using namespace hair;
@@ -340,21 +341,24 @@ MatConst mat_const(const hair_material& m) {
     k.beta_p[0] = m.beta_m; k.beta_p[1] = 0.5f * m.beta_m; k.beta_p[2] = 2.0f * m.beta_m;
     for (int p = 0; p < 3; ++p) {
         const double b = k.beta_p[p];
-        k.g_amp[p] = (float)(0.5 / (b * std::sqrt(2.0 * M_PI)));
-        k.g_k[p] = (float)(1.0 / (2.0 * b * b));
         k.g_k2[p] = (float)(M_LOG2E / (2.0 * b * b));
     }
     k.beta_n = m.beta_n;
     const double s = std::sqrt(3.0) * (double)m.beta_n / M_PI;
-    k.s = (float)s;
-    k.inv_s = (float)(1.0 / s);
-    k.inv_s_l2 = (float)(M_LOG2E / s);
-    k.n_norm = (float)(1.0 / (s * std::tanh(M_PI / (2.0 * s))));
+    k.n_k2 = (float)(2.0 * M_PI * M_LOG2E / s);
     for (int p = 0; p < 3; ++p)
         k.mn_amp[p] = (float)(0.5 / ((double)k.beta_p[p] * std::sqrt(2.0 * M_PI)) / (s * std::tanh(M_PI / (2.0 * s))));
-    const double lo = 1.0 / (1.0 + std::exp(M_PI / s)), hi = 1.0 / (1.0 + std::exp(-M_PI / s));
-    k.cdf_lo = (float)lo;
-    k.cdf_scale = (float)(1.0 / (hi - lo));
+    // the R lobe leaves at -2 gamma_o, whatever the light: its back mass at the nodes is a constant
+    const double K = std::exp(-M_PI / s);
+    k.one_k = (float)(1.0 + K);
+    for (int j = 0; j < 4; ++j) {
+        const double r = std::fabs(std::remainder(2.0 * kGLgo[j], 2.0 * M_PI));
+        const double a = std::fabs(r - 0.5 * M_PI);
+        const double outer = std::exp(-a / s) + std::exp((a - M_PI) / s);
+        const double in = (1.0 + K) / (1.0 + K + outer), out = outer / (1.0 + K + outer);
+        k.r_back[j] = (float)(r <= 0.5 * M_PI ? in : out);
+        k.r_front[j] = (float)(r <= 0.5 * M_PI ? out : in);
+    }
     k.model = m.model;
     if (m.model == HAIR_MODEL_RTTD) {
         const double bR = m.beta_r, bT = m.beta_tt, g = m.gamma_tt;
@@ -364,8 +368,8 @@ MatConst mat_const(const hair_material& m) {
             k.d_k2[p] = (float)(M_LOG2E / (2.0 * b[p] * b[p]));
             k.d_beta2[p] = (float)(b[p] * b[p]);
         }
-        k.n_amp = (float)(1.0 / (g * std::sqrt(2.0 * M_PI)));
-        k.n_k2 = (float)(M_LOG2E / (2.0 * g * g));
+        k.tt_amp = (float)(1.0 / (g * std::sqrt(2.0 * M_PI)));
+        k.tt_k2 = (float)(M_LOG2E / (2.0 * g * g));
         k.gamma2 = (float)(g * g);
         // hemisphere masses: R and D split evenly; TT (about phi = pi) puts erf(pi / (2 sqrt2 g))
         // in front (|phi| > pi/2), the rest of its wrapped mass behind

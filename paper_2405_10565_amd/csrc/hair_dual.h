@@ -1,5 +1,5 @@
 // Forward-mode dual numbers for the backward pass: a value and N partial derivatives.
-// Provides the same scalar function set as the float path in hair_shading.h (m_exp, m_sqrt,
+// Provides the same scalar function set as the float path in hair_shading.h (m_exp2, m_sqrt,
 // ...), so the scattering functions, written once as templates, differentiate themselves.
 #pragma once
 
@@ -86,28 +86,34 @@ template <int N> __device__ inline Dual<N> operator*(float a, const Dual<N>& b) 
 template <int N> __device__ inline Dual<N> operator/(const Dual<N>& a, float b) { return a * (1.0f / b); }
 template <int N> __device__ inline Dual<N> operator/(float a, const Dual<N>& b) { return Dual<N>(a) / b; }
 
-template <int N> __device__ inline Dual<N> m_exp(const Dual<N>& x) {
-    const float e = expf(x.v);
-    return chain(x, e, e);
-}
 template <int N> __device__ inline Dual<N> m_exp2(const Dual<N>& x) {
     const float e = exp2f(x.v);
     return chain(x, e, e * 0.69314718055994530942f);
+}
+template <int N> __device__ inline Dual<N> m_exp_half(const Dual<N>& x) {
+    const float e = expf(-0.5f * x.v);
+    return chain(x, e, -0.5f * e);
 }
 template <int N> __device__ inline Dual<N> m_sqrt(const Dual<N>& x) {
     const float s = sqrtf(x.v);
     return chain(x, s, s > 0.0f ? 0.5f / s : 0.0f);
 }
+template <int N> __device__ inline Dual<N> m_rsqrt(const Dual<N>& x) {
+    const float r = 1.0f / sqrtf(x.v);
+    return chain(x, r, -0.5f * r / x.v);
+}
+template <int N> __device__ inline Dual<N> m_div(const Dual<N>& a, const Dual<N>& b) { return a / b; }
 template <int N> __device__ inline Dual<N> m_asin(const Dual<N>& x) {
     const float c = sqrtf(fmaxf((1.0f - x.v) * (1.0f + x.v), 0.0f));
     return chain(x, asinf(x.v), c > 0.0f ? 1.0f / c : 0.0f);
 }
+// (accurate in the half-angle range as well: no variant for refracted offsets)
+struct MatConst;
+template <int N> __device__ inline Dual<N> m_asin_refracted(const Dual<N>& x, const MatConst&) { return m_asin(x); }
 template <int N> __device__ inline Dual<N> m_rcp(const Dual<N>& x) {
     const float r = 1.0f / x.v;
     return chain(x, r, -r * r);
 }
-template <int N> __device__ inline Dual<N> m_sin(const Dual<N>& x) { return chain(x, sinf(x.v), cosf(x.v)); }
-template <int N> __device__ inline Dual<N> m_cos(const Dual<N>& x) { return chain(x, cosf(x.v), -sinf(x.v)); }
 template <int N> __device__ inline Dual<N> m_tanh(const Dual<N>& x) {
     const float t = tanhf(x.v);
     return chain(x, t, 1.0f - t * t);
@@ -123,14 +129,6 @@ template <int N> __device__ inline Dual<N> m_pow(const Dual<N>& x, const Dual<N>
     r.v = p;
 #pragma unroll
     for (int i = 0; i < N; ++i) r.d[i] = p * (y.d[i] * lx + y.v * x.d[i] / x.v);
-    return r;
-}
-template <int N> __device__ inline Dual<N> m_atan2(const Dual<N>& y, const Dual<N>& x) {
-    const float r2 = x.v * x.v + y.v * y.v;
-    Dual<N> r;
-    r.v = atan2f(y.v, x.v);
-#pragma unroll
-    for (int i = 0; i < N; ++i) r.d[i] = r2 > 0.0f ? (x.v * y.d[i] - y.v * x.d[i]) / r2 : 0.0f;
     return r;
 }
 template <int N> __device__ inline float m_val(const Dual<N>& x) { return x.v; }

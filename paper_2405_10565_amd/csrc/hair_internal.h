@@ -90,22 +90,19 @@ struct MatConst {
     float inv_eta2;          // 1 / eta^2
     float alpha_p[3];        // longitudinal shifts of R, TT, TRT
     float beta_p[3];         // longitudinal standard deviations of R, TT, TRT
-    float g_amp[3];          // M_p = g_amp exp(-g_k x^2): 1 / (2 beta_p sqrt(2 pi))
-    float g_k[3];            //                            1 / (2 beta_p^2)
-    float g_k2[3];           // g_k log2(e)
+    float g_k2[3];           // M_p = 1 / (2 beta_p sqrt(2 pi)) exp2(-g_k2 x^2): log2(e) / (2 beta_p^2)
     float beta_n;            // azimuthal standard deviation
-    float s;                 // logistic scale sqrt(3) beta_n / pi
-    float inv_s;             // 1 / s
-    float inv_s_l2;          // log2(e) / s
-    float n_norm;            // trimmed-logistic normaliser 1 / (s tanh(pi / 2s))
-    float mn_amp[3];         // g_amp[p] n_norm: the amplitude of M_p N_p
-    float cdf_lo, cdf_scale; // trimmed CDF: (sigmoid(x / s) - cdf_lo) * cdf_scale on [-pi, pi]
+    float n_k2;              // logistic of scale s = sqrt(3) beta_n / pi: 2 pi log2(e) / s (per turn)
+    float mn_amp[3];         // amplitude of M_p N_p (with the trimmed logistic's 1 / (s tanh(pi / 2s)))
+    float one_k;             // 1 + exp(-pi / s)
+    float r_back[4];         // R lobe's mass toward |phi| < pi/2 and its complement, at the
+    float r_front[4];        // hemisphere rule's nodes h > 0
     // R / TT / D model (model == 1); the fields above serve model 0
     int32_t model;
     float d_amp[2];          // M_R, M_TT = d_amp exp2(-d_k2 theta_h^2): 1 / (2 beta sqrt(2 pi))
     float d_k2[2];           //                                     log2(e) / (2 beta^2)
     float d_beta2[2];        // beta_R^2, beta_TT^2
-    float n_amp, n_k2;       // N_TT = n_amp exp2(-n_k2 psi^2): 1 / (gamma sqrt(2 pi)), log2(e) / (2 gamma^2)
+    float tt_amp, tt_k2;     // N_TT = tt_amp exp2(-tt_k2 psi^2): 1 / (gamma sqrt(2 pi)), log2(e) / (2 gamma^2)
     float gamma2;            // gamma_TT^2
     float A[3][3];           // [R, TT, D][channel] attenuations
     float aF[3], aB[3];      // front / back hemisphere albedos

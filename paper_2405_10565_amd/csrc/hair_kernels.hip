@@ -1350,7 +1350,7 @@ __device__ inline void shade_core(const ShadeArgs& a, const SegRec& s, const flo
             }
             const T kappa = m_sqrt(n_total * (1.0f / kPi) * (ia * ib));
             const T lF = m_max(s_star, T(0.0f)), lB = m_max(-s_star, T(0.0f));
-            const bool back = fabsf(v.phi) < 0.5f * kPi;
+            const bool back = fabsf(v.phi) < 0.25f;
             cf.n_F = (back || n_total < 2.0f) ? T(1.0f) : m_max(cf.rho * kappa * lF, T(1.0f));
             cf.n_B = m_max(cf.rho * kappa * lB, T(1.0f));
             if (SHADOW) cf.n_F = cf.n_F + ns;
