@@ -479,6 +479,8 @@ struct TessPass {
     bool split = false;
 };
 
+float rcp_of(float b) { return b >= 0x1p-100f && b <= 0x1p100f ? 1.0f / b : 0.0f; }   // see div_by
+
 struct DomPass {
     const DomGrid* grid;
     int32_t K;
@@ -1534,7 +1536,7 @@ static int shadow_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const Level
         if (fd.ctr.list_overflow) return fail(HAIR_ERANGE, "shadow map: %u tiles hold more than 2^24 segments",
                                               fd.ctr.list_overflow);
         *ms += fd.ms[0];
-        views[i] = DomView{grid, tex, K, shadow->layer_depth};
+        views[i] = DomView{grid, tex, K, shadow->layer_depth, rcp_of(shadow->layer_depth)};
         ws->dom_light[i] = m++;
     }
     ws->dom_R = R;

@@ -67,6 +67,7 @@ struct DomBasis {
 struct DomGrid {
     DomBasis b;
     float u0, v0, s, k16, z_ref;    // texel (i, j) covers u0 + s [i, i+1) x v0 + s [j, j+1)
+    float rs;                       // 1 / s (0: s out of range, see div_by)
     int32_t R;
 };
 constexpr int kDomMaxLayers = 7;
@@ -76,6 +77,7 @@ struct DomView {
     const float4* tex;              // [R * R][2]: (iz0, C_0, C_1, C_2), (C_3 .. C_6); iz0 = 0: no hair
     int32_t K;
     float delta;                    // layer depth (world units)
+    float rdelta;                   // 1 / delta (0: delta out of range, see div_by)
 };
 
 struct LightsConst {

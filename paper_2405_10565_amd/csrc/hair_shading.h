@@ -35,6 +35,8 @@
 // nearest whole number, and the multiples of pi in the exit azimuths are exact.
 #pragma once
 
+#include <type_traits>
+
 #include "hair_internal.h"
 #include "hair_fastmath_coef.h"
 
@@ -297,26 +299,24 @@ __device__ inline void f_single(const LightView& v, T h, T gamma_o, T cgo, const
 // and the R lobe's masses, which no light changes, are host constants.  Bound by VALU issue: per node
 // two lobes' masses, one Fresnel term and three exponentials instead of three lobes' differences of
 // CDFs and nine products of attenuation and mass.  100k shadowed strands at 1080p: k_batch 1543 ->
-// 1375 us; the fitting step's backward pass (500 thick hairs at 512 x 512) 124 -> 109 us.
+// 1375 us, and with the nodes in a loop (no spills in the thick-hair kernels, 88 bytes instead of 124
+// here) 1235 -> 1209; the fitting step's backward pass (500 thick hairs at 512 x 512) 124 -> 109 us.
+__constant__ static const float kGLgof[4] = {(float)kGLgo[0], (float)kGLgo[1], (float)kGLgo[2], (float)kGLgo[3]};
 template <class T>
 __device__ inline void hemisphere_stats(const LightView& v, const T sigl[3], const MatConst& m, T aF[3], T aB[3],
                                         T& var_f, T& var_b) {
-    float gt[4];
-    if (m.eta < 1.4706f) {
-        for (int k = 0; k < 4; ++k) gt[k] = m_asin(kGLx[k] * v.inv_eta_p);
-    } else {
-        for (int k = 0; k < 4; ++k) gt[k] = m_asin_refracted(kGLx[k] * v.inv_eta_p, m);
-    }
     float f0 = 0.0f, b0 = 0.0f;                          // the R lobe's sums, equal in all channels
     T f1(0.0f), f2(0.0f), b1(0.0f), b2(0.0f);            // TT and TRT, summed over the channels
     for (int c = 0; c < 3; ++c) aF[c] = aB[c] = T(0.0f);
-#pragma unroll
+    constexpr int kUnroll = std::is_same<T, float>::value ? 1 : 4;   // (unrolled, the float path spills)
+#pragma unroll kUnroll
     for (int k = 0; k < 4; ++k) {
-        const Refraction<float> rf = refraction(v, kGLx[k] * v.inv_eta_p, kGLcgo[k], m);
-        const float go = (float)kGLgo[k];
+        const float sgt = kGLx[k] * v.inv_eta_p;
+        const Refraction<float> rf = refraction(v, sgt, kGLcgo[k], m);
+        const float go = kGLgof[k], gt = m_asin_refracted(sgt, m);
         float B1, F1, B2, F2;
-        hemisphere_masses(0.5f - kInvPi * (go - gt[k]), m, B1, F1);
-        hemisphere_masses(kInvPi * (2.0f * gt[k] - go), m, B2, F2);
+        hemisphere_masses(0.5f - kInvPi * (go - gt), m, B1, F1);
+        hemisphere_masses(kInvPi * (2.0f * gt - go), m, B2, F2);
         // (weights: 2 x (1/2 of the node weight on [-1, 1]))
         const float g0 = kGLw[k] * rf.g[0], g1 = kGLw[k] * rf.g[1], g2 = kGLw[k] * rf.g[2];
         const float uF1 = g1 * F1, uB1 = g1 * B1, uF2 = g2 * F2, uB2 = g2 * B2;
