@@ -113,7 +113,8 @@ struct hair_ws {
     DevBuf pieces;                            // rows of a frame drawn with long segments as pieces
     DevBuf items, item_start, item_tab, item_base, pix_cnt, pix_kmin, pix_kmax, pix_off, pix_thick, thick_list;
     DevBuf tile_tot, frag_base, tile_nb, batch_mask, batch_start, batches, frags;
-    DevBuf dom_tex, dom_grid, dom_part;      // shadow pass: texels, grids, bounds partials
+    DevBuf dom_tex, dom_grid, dom_part;      // shadow pass: texels, grids, bounds partials,
+    DevBuf dom_acc;                          // layer sums [tile][layer][texel]
     int32_t dom_R = 0, dom_K = 0, dom_n = 0;  // last shadowed render: resolution, layers, maps
     int32_t dom_light[HAIR_MAX_LIGHTS] = {};  // map index of each light, -1 if unshadowed
     FrameCaps caps = {};                      // buffer capacities of warm frames (0: none yet)
@@ -192,12 +193,12 @@ void ctx_free(hair_ctx* ctx, DevBuf& b, hair_ws* ws = nullptr) {
 }
 
 // Every device buffer a workspace can hold.
-std::array<DevBuf*, 34> ws_buffers(hair_ws* ws) {
+std::array<DevBuf*, 35> ws_buffers(hair_ws* ws) {
     return {{&ws->seg, &ws->shade, &ws->scan_tmp, &ws->tile_cnt, &ws->tile_start, &ws->bin_m, &ws->bin_blk,
             &ws->sel_cnt, &ws->sel_start, &ws->sel, &ws->sel_tmp, &ws->list, &ws->ctr, &ws->items,
             &ws->item_start, &ws->item_tab, &ws->item_base, &ws->pix_cnt, &ws->pix_kmin, &ws->pix_kmax, &ws->pix_off, &ws->pix_thick, &ws->thick_list,
             &ws->tile_tot, &ws->frag_base, &ws->tile_nb, &ws->batch_mask, &ws->batch_start, &ws->batches,
-            &ws->frags, &ws->dom_tex, &ws->dom_grid, &ws->dom_part, &ws->pieces}};
+            &ws->frags, &ws->dom_tex, &ws->dom_grid, &ws->dom_part, &ws->dom_acc, &ws->pieces}};
 }
 
 // A buffer carved from a static-scratch workspace (256-byte aligned, no headroom).
@@ -525,7 +526,8 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
         ws->arena_off = 0;
         ws->caps = FrameCaps{};
     }
-    const bool warm = tiles_too && !cold && !ws->arena && ws->caps.items > 0 && ws->caps.batches > 0;
+    // (a shadow map's frame has neither fragment records nor batches)
+    const bool warm = tiles_too && !cold && !ws->arena && ws->caps.items > 0 && (dom || ws->caps.batches > 0);
     // with_headroom for buffers a workspace keeps; exact sizes in the static scratch
     auto cap_of = [&](uint32_t n) { return ws->arena ? n : with_headroom(n); };
     if ((rc = ws_events(ws))) return rc;
@@ -599,16 +601,21 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
         caps.items = std::max(caps.items, cap_of(n_items));
     }
     if ((rc = ws_need(ws, ws->list, 4ull * caps.pairs))) return rc;
-    if ((rc = ws_need(ws, ws->item_base, 4ull * kTilePix * caps.items))) return rc;
-    if ((rc = ws_need(ws, ws->item_tab, 8ull * caps.items))) return rc;
-    for (DevBuf* b : {&ws->pix_cnt, &ws->pix_kmin, &ws->pix_kmax, &ws->pix_off})
-        if ((rc = ws_need(ws, *b, 4 * TP))) return rc;
-    if (lv.kind == 2 && (rc = ws_need(ws, ws->pix_thick, TP))) return rc;
-    for (DevBuf* b : {&ws->tile_tot, &ws->tile_nb})
-        if ((rc = ws_need(ws, *b, 4ull * T))) return rc;
-    if ((rc = ws_need(ws, ws->batch_mask, 4ull * T * (kTilePix / 32)))) return rc;
-    for (DevBuf* b : {&ws->frag_base, &ws->batch_start})
-        if ((rc = ws_need(ws, *b, 4ull * (T + 1)))) return rc;
+    if ((rc = ws_need(ws, ws->item_tab, 8ull * caps.items)) || (rc = ws_need(ws, ws->pix_kmin, 4 * TP))) return rc;
+    const size_t n_acc = dom ? (size_t)dom->K * TP : 0;
+    if (dom) {
+        if ((rc = ws_need(ws, ws->dom_acc, 8 * n_acc))) return rc;
+    } else {
+        if ((rc = ws_need(ws, ws->item_base, 4ull * kTilePix * caps.items))) return rc;
+        for (DevBuf* b : {&ws->pix_cnt, &ws->pix_kmax, &ws->pix_off})
+            if ((rc = ws_need(ws, *b, 4 * TP))) return rc;
+        if (lv.kind == 2 && (rc = ws_need(ws, ws->pix_thick, TP))) return rc;
+        for (DevBuf* b : {&ws->tile_tot, &ws->tile_nb})
+            if ((rc = ws_need(ws, *b, 4ull * T))) return rc;
+        if ((rc = ws_need(ws, ws->batch_mask, 4ull * T * (kTilePix / 32)))) return rc;
+        for (DevBuf* b : {&ws->frag_base, &ws->batch_start})
+            if ((rc = ws_need(ws, *b, 4ull * (T + 1)))) return rc;
+    }
     FrameBufs f;
     memset(&f, 0, sizeof(f));
     f.T = T;
@@ -619,12 +626,14 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     f.list = ws->list.as<uint32_t>();
     f.item_start = ws->item_start.as<uint32_t>();
     f.item_tab = ws->item_tab.as<uint2>();
-    f.item_base = ws->item_base.as<uint32_t>();
-    f.pix_cnt = ws->pix_cnt.as<uint32_t>();
-    f.pix_off = ws->pix_off.as<uint32_t>();
     f.pix_kmin = ws->pix_kmin.as<uint32_t>();
-    f.pix_kmax = ws->pix_kmax.as<uint32_t>();
-    f.pix_thick = lv.kind == 2 ? ws->pix_thick.as<uint8_t>() : nullptr;
+    if (!dom) {
+        f.item_base = ws->item_base.as<uint32_t>();
+        f.pix_cnt = ws->pix_cnt.as<uint32_t>();
+        f.pix_off = ws->pix_off.as<uint32_t>();
+        f.pix_kmax = ws->pix_kmax.as<uint32_t>();
+        f.pix_thick = lv.kind == 2 ? ws->pix_thick.as<uint8_t>() : nullptr;
+    }
     // (shadow maps and debug dumps need every fragment)
     f.trim = !dom && !dbg && lv.nseg >= kTrimRows;
     // (strand levels have opaque fragments only where a strand is wider than a pixel: no pass for them)
@@ -642,62 +651,67 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     // (a static-scratch frame clears the image only once every buffer has been carved, so that
     // a frame too large for the scratch fails with the caller's image untouched)
     HIP_TRY(ctx, launch_scatter(f, lv.nseg, cc, plan, ws->bin_m.as<uint32_t>(), ws->list.as<uint32_t>(),
-                                ws->arena ? nullptr : rgba, ws->item_tab.as<uint2>(), caps.items, st),
+                                ws->arena ? nullptr : rgba, dom ? ws->dom_acc.as<unsigned long long>() : nullptr, n_acc,
+                                ws->item_tab.as<uint2>(), caps.items, st),
             "k_scatter");
     const uint32_t item_grid = warm ? caps.items : n_items;
-    HIP_TRY(ctx, launch_count(f, cc, item_grid, st), "k_count");
-    HIP_TRY(ctx, launch_tile_prep(f, st), "k_tile_prep");
-    if (fused) {
-        HIP_TRY(ctx, launch_tile_scans(f, ws->frag_base.as<uint32_t>(), ws->batch_start.as<uint32_t>(),
-                                       warm ? caps.frags : kNoCap, warm ? caps.batches : kNoCap, st),
-                "k_tile_scans");
-    } else {
-        HIP_TRY(ctx, launch_exscan(f.tile_tot, ws->frag_base.as<uint32_t>(), T, scan_tmp, st), "k_scan");
-        HIP_TRY(ctx, launch_exscan(f.tile_nb, ws->batch_start.as<uint32_t>(), T, scan_tmp, st), "k_scan");
-        HIP_TRY(ctx, launch_sum_tiles(f, st), "k_sum_tiles");
-    }
-    uint32_t n_frags = 0, n_batches = 0;
-    if (!warm) {
-        uint32_t sizes2[2] = {0, 0};
-        unsigned long long all_frags = 0;
-        HIP_TRY(ctx, hipMemcpyAsync(&all_frags, &f.ctr->fragments, 8, hipMemcpyDeviceToHost, st), "copy");
-        HIP_TRY(ctx, hipMemcpyAsync(&sizes2[0], ws->frag_base.as<uint32_t>() + T, 4, hipMemcpyDeviceToHost, st),
-                "copy");
-        HIP_TRY(ctx, hipMemcpyAsync(&sizes2[1], ws->batch_start.as<uint32_t>() + T, 4, hipMemcpyDeviceToHost, st),
-                "copy");
-        HIP_TRY(ctx, hipStreamSynchronize(st), "sync");
-        n_frags = sizes2[0];
-        n_batches = sizes2[1];
-        caps.frags = std::max(caps.frags, cap_of(n_frags));
-        // (the static scratch serves the frames whose whole fragment set it can hold)
-        if (ws->arena && all_frags > n_frags) {
-            DevBuf probe;
-            const size_t off = ws->arena_off;
-            if ((rc = arena_take(ws, probe, 8ull * all_frags))) return rc;
-            ws->arena_off = off;
+    uint32_t n_batches = 0, batch_grid = 0;
+    if (!dom) {
+        HIP_TRY(ctx, launch_count(f, cc, item_grid, st), "k_count");
+        HIP_TRY(ctx, launch_tile_prep(f, st), "k_tile_prep");
+        if (fused) {
+            HIP_TRY(ctx, launch_tile_scans(f, ws->frag_base.as<uint32_t>(), ws->batch_start.as<uint32_t>(),
+                                           warm ? caps.frags : kNoCap, warm ? caps.batches : kNoCap, st),
+                    "k_tile_scans");
+        } else {
+            HIP_TRY(ctx, launch_exscan(f.tile_tot, ws->frag_base.as<uint32_t>(), T, scan_tmp, st), "k_scan");
+            HIP_TRY(ctx, launch_exscan(f.tile_nb, ws->batch_start.as<uint32_t>(), T, scan_tmp, st), "k_scan");
+            HIP_TRY(ctx, launch_sum_tiles(f, st), "k_sum_tiles");
         }
-        caps.batches = std::max(caps.batches, cap_of(n_batches));
+        uint32_t n_frags = 0;
+        if (!warm) {
+            uint32_t sizes2[2] = {0, 0};
+            unsigned long long all_frags = 0;
+            HIP_TRY(ctx, hipMemcpyAsync(&all_frags, &f.ctr->fragments, 8, hipMemcpyDeviceToHost, st), "copy");
+            HIP_TRY(ctx, hipMemcpyAsync(&sizes2[0], ws->frag_base.as<uint32_t>() + T, 4, hipMemcpyDeviceToHost, st),
+                    "copy");
+            HIP_TRY(ctx, hipMemcpyAsync(&sizes2[1], ws->batch_start.as<uint32_t>() + T, 4, hipMemcpyDeviceToHost, st),
+                    "copy");
+            HIP_TRY(ctx, hipStreamSynchronize(st), "sync");
+            n_frags = sizes2[0];
+            n_batches = sizes2[1];
+            caps.frags = std::max(caps.frags, cap_of(n_frags));
+            // (the static scratch serves the frames whose whole fragment set it can hold)
+            if (ws->arena && all_frags > n_frags) {
+                DevBuf probe;
+                const size_t off = ws->arena_off;
+                if ((rc = arena_take(ws, probe, 8ull * all_frags))) return rc;
+                ws->arena_off = off;
+            }
+            caps.batches = std::max(caps.batches, cap_of(n_batches));
+        }
+        if ((rc = ws_need(ws, ws->frags, 8ull * caps.frags))) return rc;
+        if ((rc = ws_need(ws, ws->batches, 16ull * caps.batches))) return rc;
+        if (lv.kind == 2 && (rc = ws_need(ws, ws->thick_list, 4ull * caps.batches))) return rc;
+        f.frags = ws->frags.as<uint2>();
+        f.batches = ws->batches.as<uint4>();
+        f.thick_list = lv.kind == 2 ? ws->thick_list.as<uint32_t>() : nullptr;
+        if (ws->arena && rgba)
+            HIP_TRY(ctx, launch_fill_f32(rgba, 0.0f, 4ull * cam->width * cam->height, st), "fill");
+        if (!fused) HIP_TRY(ctx, launch_check_caps(f, caps, 2, st), "k_check_caps");
+        batch_grid = warm ? caps.batches : n_batches;
+        // (the batch records follow the emit pass, which marks a mixed frame's thick-hair pixels)
+        HIP_TRY(ctx, launch_emit(f, cc, item_grid, st), "k_emit");
+        HIP_TRY(ctx, launch_batch_records(f, st), "k_batch_records");
     }
-    if ((rc = ws_need(ws, ws->frags, 8ull * caps.frags))) return rc;
-    if ((rc = ws_need(ws, ws->batches, 16ull * caps.batches))) return rc;
-    if (lv.kind == 2 && (rc = ws_need(ws, ws->thick_list, 4ull * caps.batches))) return rc;
-    f.frags = ws->frags.as<uint2>();
-    f.batches = ws->batches.as<uint4>();
-    f.thick_list = lv.kind == 2 ? ws->thick_list.as<uint32_t>() : nullptr;
-    if (ws->arena && rgba)
-        HIP_TRY(ctx, launch_fill_f32(rgba, 0.0f, 4ull * cam->width * cam->height, st), "fill");
-    if (!fused) HIP_TRY(ctx, launch_check_caps(f, caps, 2, st), "k_check_caps");
-    const uint32_t batch_grid = warm ? caps.batches : n_batches;
-    // (the batch records follow the emit pass, which marks a mixed frame's thick-hair pixels)
-    HIP_TRY(ctx, launch_emit(f, cc, item_grid, st), "k_emit");
-    HIP_TRY(ctx, launch_batch_records(f, st), "k_batch_records");
     HIP_TRY(ctx, hipEventRecord(ws->ev[5], st), "hipEventRecord");
     LightsConst lc = lights_const(lights, n_lights);
     if (views)
         for (int i = 0; i < n_lights; ++i) lc.dom[i] = views[i];
     if (dom) {
-        HIP_TRY(ctx, launch_dom_resolve(f, lv, dom->rows, dom->grid, dom->K, dom->delta, cam->width, batch_grid, dom->tex, st),
-                "k_dom_resolve");
+        HIP_TRY(ctx, launch_dom_map(f, cc, lv, dom->rows, dom->grid, dom->K, dom->delta, rcp_of(dom->delta), item_grid,
+                                    ws->dom_acc.as<unsigned long long>(), dom->tex, st),
+                "k_dom_first");
     } else if (grad) {
         HIP_TRY(ctx, launch_fill_f32(grad->d_axes, 0.0f, 2ull * (tess ? tess->base.nseg : lv.nseg), st), "fill");
         HIP_TRY(ctx, launch_fill_f32(grad->d_r, 0.0f, (size_t)lv.n_owner, st), "fill");

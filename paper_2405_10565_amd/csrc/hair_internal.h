@@ -247,7 +247,8 @@ hipError_t launch_bins(const SegRec* seg, int32_t nseg, const CamConst& cam, con
 // The tile lists, and everything the later passes expect cleared: the frame's per-pixel counters,
 // the work-item table and (when given) the image, transparent black.
 hipError_t launch_scatter(const FrameBufs& f, int32_t nseg, const CamConst& cam, const BinPlan& p, const uint32_t* M,
-                          uint32_t* list, float* rgba, uint2* item_tab, uint32_t cap_items, hipStream_t st);
+                          uint32_t* list, float* rgba, unsigned long long* acc, size_t n_acc, uint2* item_tab,
+                          uint32_t cap_items, hipStream_t st);
 // Record the frame's sizes in ctr->sizes and flag ctr->cap_overflow when one exceeds its
 // capacity (stage 1: list entries and work items; stage 2: fragments and batches).  Every
 // later pass that would fill a sized buffer does nothing once the flag is set.
@@ -313,8 +314,9 @@ hipError_t launch_dom_grid(const LevelDev& lv, const ShadeRec* rows, const DomBa
                            hipStream_t st);
 hipError_t launch_project_light(const LevelDev& lv, const ShadeRec* rows, const DomGrid* grid, SegRec* seg,
                                 hipStream_t st);
-hipError_t launch_dom_resolve(const FrameBufs& f, const LevelDev& lv, const ShadeRec* rows, const DomGrid* grid, int32_t K, float delta,
-                              int32_t R, uint32_t n_blocks, float4* tex, hipStream_t st);
+hipError_t launch_dom_map(const FrameBufs& f, const CamConst& cam, const LevelDev& lv, const ShadeRec* rows,
+                          const DomGrid* grid, int32_t K, float delta, float rdelta, uint32_t n_items,
+                          unsigned long long* acc, float4* tex, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t st);
 hipError_t launch_fill_f32(float* p, float v, size_t n, hipStream_t st);
 hipError_t launch_probe_rate(int kind, int blocks, int iters, float* out, hipStream_t st);

@@ -839,6 +839,8 @@ struct FillArgs {
     uint8_t* thick;
     float4* rgba;
     size_t n_rgba;
+    uint4* acc;               // a shadow map's layer sums (its frame has no other per-pixel table than kmin)
+    size_t n_acc;
     const uint32_t* item_start;
     uint2* item_tab;
     uint32_t cap_items;
@@ -848,10 +850,12 @@ __device__ inline void fill_frame(const FillArgs& a, int T) {
     const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const uint4 zero = make_uint4(0u, 0u, 0u, 0u), ones = make_uint4(~0u, ~0u, ~0u, ~0u);
     const uint4 k0 = make_uint4(a.kmax0, a.kmax0, a.kmax0, a.kmax0);
+    for (size_t i = i0; i < a.n_acc; i += step) a.acc[i] = zero;
     for (size_t i = i0; i < n; i += step) {
+        reinterpret_cast<uint4*>(a.kmin)[i] = ones;
+        if (!a.cnt) continue;
         reinterpret_cast<uint4*>(a.cnt)[i] = zero;
         reinterpret_cast<uint4*>(a.off)[i] = zero;
-        reinterpret_cast<uint4*>(a.kmin)[i] = ones;
         reinterpret_cast<uint4*>(a.kmax)[i] = k0;
         if (a.thick) reinterpret_cast<uint32_t*>(a.thick)[i] = 0u;
     }
@@ -1145,12 +1149,12 @@ __device__ inline void dom_point(const SegRec& s, const float4& q0, const float4
 // fragments share (Markstein: a quotient within one ulp, which the first correction gives, and one
 // more step with the exact remainder): 5 instructions instead of the general division's 11.  rb = 0
 // (a divisor outside [2^-100, 2^100]) takes the general one.
-__device__ inline float div_by(float a, float b, float rb) {
-    if (rb == 0.0f) return a / b;
+__device__ inline float div_rcp(float a, float b, float rb) {
     float q = a * rb;
     q = __builtin_fmaf(__builtin_fmaf(-q, b, a), rb, q);
     return __builtin_fmaf(__builtin_fmaf(-q, b, a), rb, q);
 }
+__device__ inline float div_by(float a, float b, float rb) { return rb == 0.0f ? a / b : div_rcp(a, b, rb); }
 
 // delta = |cross| / (16 sqrt(t_den)), the pixel centre's distance from the centre line in pixels,
 // in double: the hardware reciprocal square root refined by one Newton step (relative error
@@ -3441,109 +3445,156 @@ __global__ __launch_bounds__(256) void k_project_light(LevelDev lv, const ShadeR
     seg[g] = r;
 }
 
-__device__ inline float dom_fragment_count(const SegRec& s, const LevelDev& lv, const ShadeRec* rows, float s_tex,
-                                           uint32_t g, int px, int py);
-
-// Per texel (one block per 16 x 16 tile): the first hit iz0 (the pixel's smallest key), then
-// every fragment's expected hair count into its layer floor((iz0 - iz) / delta) (clamped to
-// K - 1): a strand its box coverage alpha, a thick hair alpha rho kappa l_max sqrt(1 - h^2)
-// (Sec. 4, hair number; the chord along the light at the texel's offset h = delta / hw).
-// One block per batch of whole texels (the camera pass's batches), one lane per fragment; the
-// counts are summed per (texel, layer) in LDS.  Texels in no batch hold no hair (cleared).
-// Output: (iz0, C_0 .. C_{K-1}) with C the cumulative counts; iz0 = 0 marks a texel without hair.
-__device__ inline float dom_fragment_count(const SegRec& s, const LevelDev& lv, const ShadeRec* rows, float s_tex,
-                                           uint32_t g, int px, int py) {
-    const int ex = 16 * px + 8 - s.xa, ey = 16 * py + 8 - s.ya;
-    const int dx = s.xb - s.xa, dy = s.yb - s.ya;
-    const int tden = dx * dx + dy * dy, cr = ex * dy - ey * dx;
-    const float dl = fabsf((float)cr) / sqrtf((float)tden) * (1.0f / 16.0f);
-    const float hw = s.hw;
-    float c = fminf(fmaxf(fminf(dl + hw, 0.5f) - fmaxf(dl - hw, -0.5f), 0.0f), 1.0f);
-    const bool thick = rows ? !row_is_strand(rows[g]) : lv.kind != 0;
-    if (thick && !(hw > 0.0f)) {
-        c = 0.0f;   // a degenerate (zero-width) thick hair holds no hairs across the light
-    } else if (thick) {
-        const int owner = g / lv.S;
-        const float a = rows ? rows[g].q3.x : lv.axes[2 * g], b = rows ? rows[g].q3.y : lv.axes[2 * g + 1];
-        const float n = rows ? rows[g].q3.z : (float)lv.n_total[owner], r = rows ? rows[g].q3.w : lv.r[owner];
-        const float h = fminf(dl / hw, 1.0f);
-        const float rho = fminf(fmaxf(n * r * r / (a * b), 0.0f), 1.0f);
-        const float kappa = sqrtf(n / (3.14159265358979f * a * b));
-        c = c * rho * kappa * (2.0f * a * b / (hw * s_tex)) * sqrtf((1.0f - h) * (1.0f + h));
+// The shadow map of a light view is two passes over the tiles' lists, with no fragment stored:
+// k_dom_first finds per texel the first hit iz0 (the smallest depth key), k_dom_layers adds every
+// fragment's expected hair count to its layer floor((iz0 - iz) / delta) (clamped to K - 1): a strand
+// its box coverage alpha, a thick hair alpha rho kappa l_max sqrt(1 - h^2) (Sec. 4, hair number; the
+// chord along the light at the texel's offset h = delta / hw).  The counts are 32.32 fixed-point
+// sums (they commute, so the atomics give the same sums in any order; counts are far below 2^31
+// hairs), in LDS for `group` chunks of a tile's list and added to the texels' sums in acc
+// ([tile][layer][texel]) once.  k_dom_texels writes (iz0, C_0 .. C_6) with C the cumulative counts;
+// iz0 = 0 marks a texel without hair.  Bound by the coverage arithmetic (VALU), done twice; storing
+// the fragments in between cost more (100k strands, 1024^2 map, 34 M fragments: count + emit +
+// resolve 145 + 280 + 305 us -> 230 + 356).  A pass over a
+// sample of each list, so that the first one could skip what lies behind, gained nothing.
+__global__ __launch_bounds__(kNT) void k_dom_first(FrameBufs f, CamConst cam, int group) {
+    __shared__ uint32_t s_z[kTilePix];
+    __shared__ float2 s_iz[kNT];
+    __shared__ CovSetup s_cov[kNT];
+    __shared__ uint8_t s_own[kNT / 64 * kCovLinesPerWave];
+    const uint32_t n_items = f.item_start[f.T];
+    if (blockIdx.x >= n_items || f.ctr->cap_overflow) return;
+    const uint2 it = f.item_tab[xcd_contiguous(blockIdx.x, n_items)];
+    if (it.y % (uint32_t)group) return;
+    const int t = threadIdx.x, tile = (int)it.x;
+    const int px0 = (tile % f.ntx) * kTile, py0 = (tile / f.ntx) * kTile;
+    const uint32_t lstart = f.tile_start[tile], n = f.tile_start[tile + 1] - lstart;
+    const size_t q = (size_t)tile * kTilePix + t;
+    const uint32_t z0 = f.pix_kmin[q];
+    s_z[t] = z0;
+    for (uint32_t k = it.y; k < it.y + (uint32_t)group && k * kNT < n; ++k) {
+        const uint32_t j = k * kNT + t;
+        SegRec s{};
+        if (j < n) s = f.seg[f.list[lstart + j]];
+        s_iz[t] = make_float2(s.iza, s.izb);
+        const uint32_t total = cov_setup<kAll>(s, j < n, px0, py0, cam.W, cam.H, s_cov, s_own);
+        float2 iz;   // (the line's segment)
+        wave_coverage(s_cov, s_own, total, [&](int p, int tnum, int tden, int, int) {
+            const uint32_t z = s_z[p];
+            if (iz_bound(iz, tnum, tden) < iz_of_key(z)) return;
+            const uint32_t key = depth_key_iz(iz.x, iz.y, tnum, tden);
+            if (key < z) atomicMin(&s_z[p], key);
+        }, [&](int o, int, int, bool) {
+            iz = s_iz[o];
+            return false;
+        });
+        __syncthreads();
     }
-    return c;
+    if (s_z[t] < z0) atomicMin(&f.pix_kmin[q], s_z[t]);
 }
 
-__global__ __launch_bounds__(kNT) void k_dom_resolve(FrameBufs f, LevelDev lv, const ShadeRec* __restrict__ rows,
-                                                     const DomGrid* __restrict__ grid, int K, float delta,
-                                                     float4* __restrict__ tex) {
-    // per (texel, layer) sums in 32.32 fixed point: integer adds commute, so the LDS atomics
-    // give the same sums in any order (counts are far below 2^31 hairs; resolution 2^-32)
-    __shared__ unsigned long long s_acc[kDomMaxLayers][kTilePix];
+// THICK: the level can hold thick hairs.  Dynamic LDS: K x kTilePix sums.
+template <bool THICK>
+__global__ __launch_bounds__(kNT) void k_dom_layers(FrameBufs f, CamConst cam, LevelDev lv,
+                                                    const ShadeRec* __restrict__ rows,
+                                                    const DomGrid* __restrict__ grid, int K, float delta, float rdelta,
+                                                    unsigned long long* __restrict__ acc, int group) {
+    extern __shared__ unsigned long long s_acc[];
     __shared__ float s_iz0[kTilePix];
-    const uint32_t n_batches = f.batch_start[f.T];
-    const uint4 br = f.batches[blockIdx.x];
-    if (blockIdx.x >= n_batches || f.ctr->cap_overflow) return;
-    const BatchRec b = unpack_batch(br);
-    const int tile = b.tile, p0 = b.p0, p1 = b.p1;
-    const int t = threadIdx.x;
-    const int R = grid->R;
-    const float s_tex = grid->s;
-    const int tx0 = (tile % f.ntx) * kTile, ty0 = (tile / f.ntx) * kTile;
-    const size_t q = (size_t)tile * kTilePix + t;
-    const bool mine = t >= p0 && t < p1;
-    s_iz0[t] = (mine && f.pix_cnt[q]) ? __uint_as_float(0xFFFFFFFFu - f.pix_kmin[q]) : 0.0f;
-#pragma unroll
-    for (int k = 0; k < kDomMaxLayers; ++k) s_acc[k][t] = 0ull;
-    __syncthreads();
-    const uint2* fr = f.frags + b.frag0;
-    const uint32_t* list = f.list + f.tile_start[tile];
-    // kU records per lane in flight: the record, list and segment gathers of one round are
-    // issued together instead of one dependent chain per record
-    constexpr int kU = 4;
-    for (uint32_t i0 = 0; i0 < b.nfrag; i0 += kU * kNT) {
-        uint2 rec[kU];
-        uint32_t g[kU];
-        SegRec sg[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const uint32_t i = i0 + t + u * kNT;
-            rec[u] = i < b.nfrag ? fr[i] : make_uint2(0u, 0u);
+    __shared__ float4 s_seg[kNT];                  // (iza, izb, hw, sqrt(t_den))
+    __shared__ float2 s_rcp[kNT];                  // (1 / sqrt(t_den), 1 / t_den)
+    __shared__ float4 s_thk[THICK ? kNT : 1];      // (rho, kappa, 2 |a| |b| / (hw s), 0: strand, 1: thick hair)
+    __shared__ CovSetup s_cov[kNT];
+    __shared__ uint8_t s_own[kNT / 64 * kCovLinesPerWave];
+    const uint32_t n_items = f.item_start[f.T];
+    if (blockIdx.x >= n_items || f.ctr->cap_overflow) return;
+    const uint2 it = f.item_tab[xcd_contiguous(blockIdx.x, n_items)];
+    if (it.y % (uint32_t)group) return;
+    const int t = threadIdx.x, tile = (int)it.x;
+    const int px0 = (tile % f.ntx) * kTile, py0 = (tile / f.ntx) * kTile;
+    const uint32_t lstart = f.tile_start[tile], n = f.tile_start[tile + 1] - lstart;
+    s_iz0[t] = iz_of_key(f.pix_kmin[(size_t)tile * kTilePix + t]);
+    for (int k = 0; k < K; ++k) s_acc[k * kTilePix + t] = 0ull;
+    for (uint32_t k = it.y; k < it.y + (uint32_t)group && k * kNT < n; ++k) {
+        const uint32_t j = k * kNT + t;
+        SegRec s{};
+        if (j < n) {
+            const uint32_t g = f.list[lstart + j];
+            s = f.seg[g];
+            if constexpr (THICK) {
+                float4 th = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (rows ? !row_is_strand(rows[g]) : lv.kind != 0) {
+                    const int owner = g / lv.S;
+                    const float a = rows ? rows[g].q3.x : lv.axes[2 * g], b = rows ? rows[g].q3.y : lv.axes[2 * g + 1];
+                    const float m = rows ? rows[g].q3.z : (float)lv.n_total[owner], r = rows ? rows[g].q3.w : lv.r[owner];
+                    th.x = fminf(fmaxf(m * r * r / (a * b), 0.0f), 1.0f);
+                    th.y = sqrtf(m / (3.14159265358979f * a * b));
+                    th.z = 2.0f * a * b / (s.hw * grid->s);
+                    th.w = 1.0f;
+                }
+                s_thk[t] = th;
+            }
         }
+        const int dx = s.xb - s.xa, dy = s.yb - s.ya;
+        const float td = (float)(dx * dx + dy * dy), sq = sqrtf(td);
+        s_seg[t] = make_float4(s.iza, s.izb, s.hw, sq);
+        s_rcp[t] = make_float2(1.0f / sq, 1.0f / td);
+        const uint32_t total = cov_setup<kAll>(s, j < n, px0, py0, cam.W, cam.H, s_cov, s_own);
+        float4 e, th;   // (the line's segment)
+        float2 rc;
+        wave_coverage(s_cov, s_own, total, [&](int p, int tnum, int tden, int, int cr) {
+            // (rounded like the keys of k_dom_first, so that the first hit itself lies in layer 0)
+            const float tt = div_rcp((float)tnum, (float)tden, rc.y);
+            const float iz = e.x + tt * (e.y - e.x);
+            const int layer = min(K - 1, (int)floorf(div_by(s_iz0[p] - iz, delta, rdelta)));
+            const float dl = div_rcp(fabsf((float)cr), e.w, rc.x) * (1.0f / 16.0f);
+            const float hw = e.z;
+            float c = fminf(fmaxf(fminf(dl + hw, 0.5f) - fmaxf(dl - hw, -0.5f), 0.0f), 1.0f);
+            if constexpr (THICK) {
+                if (th.w > 0.0f) {
+                    const float h = fminf(dl / hw, 1.0f);
+                    // (a degenerate, zero-width thick hair holds no hairs across the light)
+                    c = hw > 0.0f ? c * th.x * th.y * th.z * sqrtf((1.0f - h) * (1.0f + h)) : 0.0f;
+                }
+            }
+            // 32.32 fixed point, rounded: whole part, then the exact rest in 2^-32
+            const uint32_t hi = (uint32_t)c;
+            const uint32_t lo = (uint32_t)((double)(c - (float)hi) * 4294967296.0 + 0.5);
+            const unsigned long long fx = (unsigned long long)hi << 32 | lo;
+            if (fx) atomicAdd(&s_acc[layer * kTilePix + p], fx);
+        }, [&](int o, int, int, bool) {
+            e = s_seg[o];
+            rc = s_rcp[o];
+            if constexpr (THICK) th = s_thk[o];
+            return false;
+        });
+        __syncthreads();
+    }
+    for (int k = 0; k < K; ++k) {
+        const unsigned long long v = s_acc[k * kTilePix + t];
+        if (v) atomicAdd(&acc[((size_t)tile * K + k) * kTilePix + t], v);
+    }
+}
+
+__global__ __launch_bounds__(kNT) void k_dom_texels(FrameBufs f, int R, int K, const unsigned long long* __restrict__ acc,
+                                                    float4* __restrict__ tex) {
+    if (f.ctr->cap_overflow) return;
+    const int tile = blockIdx.x, t = threadIdx.x;
+    const int px = (tile % f.ntx) * kTile + t % kTile, py = (tile / f.ntx) * kTile + t / kTile;
+    float C[kDomMaxLayers] = {};
+    float iz0 = 0.0f;
+    if (f.tile_start[tile + 1] > f.tile_start[tile]) {
+        iz0 = iz_of_key(f.pix_kmin[(size_t)tile * kTilePix + t]);
+        unsigned long long run = 0;
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const uint32_t i = i0 + t + u * kNT;
-            g[u] = i < b.nfrag ? seg_of(rec[u].y, list, f.gid != 0) : 0u;
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const uint32_t i = i0 + t + u * kNT;
-            if (i < b.nfrag) sg[u] = f.seg[g[u]];
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const uint32_t i = i0 + t + u * kNT;
-            if (i >= b.nfrag) continue;
-            const uint32_t p = rec[u].y >> 24;
-            const float iz = __uint_as_float(0xFFFFFFFFu - rec[u].x);
-            const int layer = min(K - 1, (int)floorf((s_iz0[p] - iz) / delta));
-            const float c = dom_fragment_count(sg[u], lv, rows, s_tex, g[u], tx0 + (int)(p % kTile), ty0 + (int)(p / kTile));
-            const unsigned long long fx = (unsigned long long)((double)c * 4294967296.0 + 0.5);
-            if (fx) atomicAdd(&s_acc[layer][p], fx);
+        for (int k = 0; k < kDomMaxLayers; ++k) {
+            if (k < K) run += acc[((size_t)tile * K + k) * kTilePix + t];
+            C[k] = (float)((double)run * (1.0 / 4294967296.0));
         }
     }
-    __syncthreads();
-    const int px = tx0 + (t % kTile), py = ty0 + (t / kTile);
-    if (!mine || px >= R || py >= R) return;
-    float C[kDomMaxLayers];
-    unsigned long long run = 0;
-#pragma unroll
-    for (int k = 0; k < kDomMaxLayers; ++k) {
-        run += s_acc[k][t];
-        C[k] = (float)((double)run * (1.0 / 4294967296.0));
-    }
+    if (px >= R || py >= R) return;
     const size_t o = 2 * ((size_t)py * R + px);
-    tex[o] = make_float4(s_iz0[t], C[0], C[1], C[2]);
+    tex[o] = make_float4(iz0, C[0], C[1], C[2]);
     tex[o + 1] = make_float4(C[3], C[4], C[5], C[6]);
 }
 }  // namespace
@@ -3641,12 +3692,24 @@ hipError_t launch_project_light(const LevelDev& lv, const ShadeRec* rows, const 
     return hipGetLastError();
 }
 
-hipError_t launch_dom_resolve(const FrameBufs& f, const LevelDev& lv, const ShadeRec* rows, const DomGrid* grid,
-                              int32_t K, float delta, int32_t R, uint32_t n_batches, float4* tex, hipStream_t st) {
-    // n_batches: the grid (at least the frame's batch count, which the kernel reads)
-    hipError_t e = launch_fill_f32(reinterpret_cast<float*>(tex), 0.0f, 8ull * R * R, st);
-    if (e != hipSuccess || n_batches == 0) return e;
-    hipLaunchKernelGGL(k_dom_resolve, dim3(n_batches), dim3(kNT), 0, st, f, lv, rows, grid, K, delta, tex);
+hipError_t launch_dom_map(const FrameBufs& f, const CamConst& cam, const LevelDev& lv, const ShadeRec* rows,
+                          const DomGrid* grid, int32_t K, float delta, float rdelta, uint32_t n_items,
+                          unsigned long long* acc, float4* tex, hipStream_t st) {
+    // a block takes four chunks of a tile's list, which saves three of four rounds of global atomics,
+    // where that leaves the chip's 2048 block slots filled
+    const int group = n_items >= 8192 ? 4 : 1;
+    const bool thick = rows || lv.kind != 0;
+    const int lds = 8 * kTilePix * K;
+    if (n_items) {
+        hipLaunchKernelGGL(k_dom_first, dim3(n_items), dim3(kNT), 0, st, f, cam, group);
+        if (thick)
+            hipLaunchKernelGGL(k_dom_layers<true>, dim3(n_items), dim3(kNT), lds, st, f, cam, lv, rows, grid, K, delta,
+                               rdelta, acc, group);
+        else
+            hipLaunchKernelGGL(k_dom_layers<false>, dim3(n_items), dim3(kNT), lds, st, f, cam, lv, rows, grid, K, delta,
+                               rdelta, acc, group);
+    }
+    hipLaunchKernelGGL(k_dom_texels, dim3(f.T), dim3(kNT), 0, st, f, cam.W, K, acc, tex);
     return hipGetLastError();
 }
 
@@ -3700,13 +3763,14 @@ hipError_t launch_exscan(const uint32_t* cnt, uint32_t* start, int32_t n, uint32
 }
 
 hipError_t launch_scatter(const FrameBufs& f, int32_t nseg, const CamConst& cam, const BinPlan& p, const uint32_t* M,
-                          uint32_t* list, float* rgba, uint2* item_tab, uint32_t cap_items, hipStream_t st) {
+                          uint32_t* list, float* rgba, unsigned long long* acc, size_t n_acc, uint2* item_tab,
+                          uint32_t cap_items, hipStream_t st) {
     const int ntx = (cam.W + kTile - 1) / kTile, nty = (cam.H + kTile - 1) / kTile, T = ntx * nty;
     hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_scatter), 4 * p.range);
     if (e != hipSuccess) return e;
     const FillArgs fill{f.pix_cnt, f.pix_off, f.pix_kmin, f.pix_kmax, f.opaque ? 0xFFFFFFFFu : 0u, f.pix_thick,
-                        reinterpret_cast<float4*>(rgba), rgba ? (size_t)cam.W * cam.H : 0, f.item_start, item_tab,
-                        cap_items};
+                        reinterpret_cast<float4*>(rgba), rgba ? (size_t)cam.W * cam.H : 0,
+                        reinterpret_cast<uint4*>(acc), n_acc / 2, f.item_start, item_tab, cap_items};
     // (a block per 8 tiles keeps the clearing spread over the chip whatever the segment count)
     for (int t0 = 0; t0 < T; t0 += p.range) {
         const int nt = std::min(p.range, T - t0);
