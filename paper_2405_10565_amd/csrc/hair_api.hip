@@ -1690,17 +1690,15 @@ static int render_mixed(hair_ctx* ctx, hair_ws* ws, int32_t asset, const hair_ca
     std::lock_guard<std::mutex> g(ws->mu);
     hipStream_t st = (hipStream_t)stream;
     const int GS = h.G * h.S;
-    if ((rc = ws_need(ws, ws->sel_cnt, 4ull * (GS + 1))) || (rc = ws_need(ws, ws->sel_start, 4ull * (GS + 1))) ||
+    if ((rc = ws_need(ws, ws->sel_cnt, 4ull * (GS + 1))) || (rc = ws_need(ws, ws->sel_start, 4ull * (GS + 2))) ||
         (rc = ws_need(ws, ws->sel_tmp, 4 * exscan_scratch_words(GS))))
         return rc;
-    uint32_t* cnt = ws->sel_cnt.as<uint32_t>();
-    HIP_TRY(ctx, launch_fill_u32(cnt + GS, 0u, 1, st), "fill");
-    HIP_TRY(ctx, launch_select(h, levels, cnt, ws->sel_start.as<uint32_t>(), ws->sel_tmp.as<uint32_t>(), st),
+    HIP_TRY(ctx, launch_select(h, levels, ws->sel_cnt.as<uint32_t>(), ws->sel_start.as<uint32_t>(), ws->sel_tmp.as<uint32_t>(), st),
             "k_sel_count");
-    uint32_t nsel = 0, bad = 0;
-    HIP_TRY(ctx, hipMemcpyAsync(&nsel, ws->sel_start.as<uint32_t>() + GS, 4, hipMemcpyDeviceToHost, st), "copy");
-    HIP_TRY(ctx, hipMemcpyAsync(&bad, cnt + GS, 4, hipMemcpyDeviceToHost, st), "copy");
+    uint32_t sizes[2] = {0, 0};
+    HIP_TRY(ctx, hipMemcpyAsync(sizes, ws->sel_start.as<uint32_t>() + GS, 8, hipMemcpyDeviceToHost, st), "copy");
     HIP_TRY(ctx, hipStreamSynchronize(st), "sync");
+    const uint32_t nsel = sizes[0], bad = sizes[1];
     if (bad) return fail(HAIR_EINVAL, "%u entries of levels lie outside [0, %d]", bad, h.n_levels);
     if ((rc = ws_need(ws, ws->sel, 4ull * std::max<uint32_t>(nsel, 1)))) return rc;
     HIP_TRY(ctx, launch_select_fill(h, levels, ws->sel_start.as<uint32_t>(), ws->sel.as<uint32_t>(), st), "k_sel_fill");

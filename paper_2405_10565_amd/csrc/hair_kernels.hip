@@ -314,8 +314,8 @@ __global__ __launch_bounds__(256) void k_project(LevelDev lv, CamConst cam, SegR
 // level l is the largest 2 hw over the visible k-th segments of level l's owners in g (0 if
 // none is visible).  One wave per (g, k).
 
-// Level of (g, k); levels outside [0, n_levels] are read as 0 (k_sel_count counts them in
-// cnt[G S], which the caller zeroes and checks before rendering).
+// Level of (g, k); levels outside [0, n_levels] are read as 0 (the selection counts them in
+// start[G S + 1], which the caller checks before rendering).
 __device__ inline int level_at(const HierDev& h, const int32_t* levels, int gk) {
     const int L = levels[gk];
     return (L < 0 || L > h.n_levels) ? 0 : L;
@@ -334,16 +334,47 @@ __device__ inline uint32_t group_width_bits(const HierDev& h, int l, int g, int 
     return w;
 }
 
-// Initial levels: the coarsest l >= 1 whose width is <= eps_w, else 0 (the strands).
+// Initial levels: the coarsest l >= 1 whose width is <= eps_w, else 0 (the strands).  The wave's
+// lanes take the owners of all levels, coarsest first, 64 at a time, and stop at the level that
+// passes: a coarse level has one owner per group or a few, and one after the other the levels are a
+// chain of gathers (bound by their latency: 150k strands, 3 levels 30 -> 21 us).
 __global__ __launch_bounds__(256) void k_lod_init(HierDev h, CamConst cam, float eps_w, int32_t* __restrict__ levels) {
     const int gk = (int)(blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6));
     if (gk >= h.G * h.S) return;
     const int g = gk / h.S, k = gk - g * h.S;
-    int pick = 0;
-    for (int l = h.n_levels; l >= 1; --l) {
-        if (__uint_as_float(group_width_bits(h, l, g, k, cam)) <= eps_w) {
-            pick = l;
-            break;
+    auto owners = [&](int l) { return h.grp_start[l][g + 1] - h.grp_start[l][g]; };
+    int pick = 0, l = h.n_levels, done = 0;   // the first unfinished level and its owners already seen
+    uint32_t w_l = 0;                         // their width
+    while (l >= 1 && pick == 0) {
+        int mine = 0, x = (int)__lane_id() + done;
+        uint32_t w = 0;
+        for (int q = l; q >= 1 && mine == 0; --q) {
+            const int c = owners(q);
+            if (x < c) mine = q;
+            else x -= c;
+        }
+        if (mine) {
+            const LevelDev& lv = h.lv[mine];
+            const SegRec r = project_segment(lv, h.grp_owner[mine][h.grp_start[mine][g] + x] * lv.S + k, cam, nullptr);
+            if (r.hwfx & kFlagVisible) w = __float_as_uint(2.0f * r.hw);
+        }
+        for (int left = 64; l >= 1;) {        // the levels of this round
+            uint32_t m = mine == l ? w : 0u;
+            for (int off = 32; off >= 1; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
+            w_l = max(w_l, m);
+            const int c = owners(l) - done;
+            if (c > left) {
+                done += left;
+                break;
+            }
+            left -= c;
+            if (__uint_as_float(w_l) <= eps_w) {
+                pick = l;
+                break;
+            }
+            --l;
+            done = 0;
+            w_l = 0;
         }
     }
     if (__lane_id() == 0) levels[gk] = pick;
@@ -368,14 +399,21 @@ __global__ __launch_bounds__(256) void k_lod_update(HierDev h, CamConst cam, flo
 }
 
 // Selection of a mixed frame: for every (g, k) the k-th segments of the owners of level
-// L(g, k) in g, in (g, k, owner) order; entry = level << 28 | segment id of that level.
+// L(g, k) in g, in (g, k, owner) order; entry = level << 28 | segment id of that level.  start[G S] is
+// the number of rows, start[G S + 1] that of entries of levels out of range.
+__device__ inline uint32_t selected(const HierDev& h, const int32_t* levels, int gk, uint32_t& bad) {
+    const int g = gk / h.S, raw = levels[gk], L = level_at(h, levels, gk);
+    if (raw != L) ++bad;
+    return (uint32_t)(h.grp_start[L][g + 1] - h.grp_start[L][g]);
+}
+// (more than kScanOneBlock (g, k): *bad is zeroed before)
 __global__ __launch_bounds__(256) void k_sel_count(HierDev h, const int32_t* __restrict__ levels,
-                                                   uint32_t* __restrict__ cnt) {
+                                                   uint32_t* __restrict__ cnt, uint32_t* __restrict__ bad) {
     const int gk = blockIdx.x * blockDim.x + threadIdx.x;
     if (gk >= h.G * h.S) return;
-    const int g = gk / h.S, raw = levels[gk], L = level_at(h, levels, gk);
-    if (raw != L) atomicAdd(&cnt[h.G * h.S], 1u);
-    cnt[gk] = (uint32_t)(h.grp_start[L][g + 1] - h.grp_start[L][g]);
+    uint32_t b = 0;
+    cnt[gk] = selected(h, levels, gk, b);
+    if (b) atomicAdd(bad, 1u);
 }
 
 __global__ __launch_bounds__(256) void k_sel_fill(HierDev h, const int32_t* __restrict__ levels,
@@ -495,6 +533,25 @@ __device__ inline uint32_t block_scan_1024(int n, G get, P put, uint32_t* s_w) {
         __syncthreads();
     }
     return carry;
+}
+
+// The selection's counts and their scan in one block (up to kScanOneBlock (g, k)): one launch
+// instead of a clear, a count and a scan, and one 8-byte readback instead of two.
+__global__ __launch_bounds__(1024) void k_select(HierDev h, const int32_t* __restrict__ levels,
+                                                 uint32_t* __restrict__ start) {
+    __shared__ uint32_t s_w[16], s_bad;
+    if (threadIdx.x == 0) s_bad = 0u;
+    __syncthreads();
+    const int n = h.G * h.S;
+    uint32_t bad = 0;
+    const uint32_t total = block_scan_1024(
+        n, [&](int i) { return selected(h, levels, i, bad); }, [&](int i, uint32_t x) { start[i] = x; }, s_w);
+    if (bad) atomicAdd(&s_bad, bad);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        start[n] = total;
+        start[n + 1] = s_bad;
+    }
 }
 
 // The tiles' list offsets (exclusive scan of their list lengths, block 0) and their work items of
@@ -3911,9 +3968,14 @@ hipError_t launch_lod_update(const HierDev& h, const CamConst& cam, float eps_w,
 hipError_t launch_select(const HierDev& h, const int32_t* levels, uint32_t* cnt, uint32_t* sel_start,
                          uint32_t* scan_tmp, hipStream_t st) {
     const int gk = h.G * h.S;
-    hipLaunchKernelGGL(k_sel_count, dim3(blocks_for(gk, 256)), dim3(256), 0, st, h, levels, cnt);
-    hipError_t e = hipGetLastError();
+    if (gk <= kScanOneBlock) {
+        hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, st, h, levels, sel_start);
+        return hipGetLastError();
+    }
+    hipError_t e = launch_fill_u32(sel_start + gk + 1, 0u, 1, st);
     if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_sel_count, dim3(blocks_for(gk, 256)), dim3(256), 0, st, h, levels, cnt, sel_start + gk + 1);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     return launch_exscan(cnt, sel_start, gk, scan_tmp, st);
 }
 
