@@ -520,7 +520,8 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     const int ntx = (cam->width + kTile - 1) / kTile, nty = (cam->height + kTile - 1) / kTile;
     const int T = ntx * nty;
     const size_t TP = (size_t)T * kTilePix;
-    const BinPlan plan = bin_plan(lv.nseg, T);
+    // (workspaces of a given size keep the smaller count matrix)
+    const BinPlan plan = bin_plan(lv.nseg, T, lv.kind == 1 && !ws->arena && ws->max_bytes == 0);
     if (ws->arena) {   // static scratch: every frame is sized afresh from its own counts
         for (DevBuf* b : ws_buffers(ws)) *b = DevBuf{};
         ws->arena_off = 0;

@@ -18,6 +18,7 @@ constexpr int kSplitLen = 16000;                 // a longer segment is drawn as
 constexpr int kMaxPieces = 64;                   // pieces per segment (row = segment << 6 | piece)
 constexpr int kMaxListLen = (1 << 24) - 1;       // per-tile list limit (24-bit local index)
 constexpr int kBinThreads = 512;                 // threads per binning block
+constexpr int kBinLanes = 8;                     // lanes per segment where segments are wide (thick hairs)
 constexpr int kMaxLdsTiles = 36864;              // per-tile LDS counters of one binning pass (144 KiB)
 
 // Projected segment, one per segment of the rendered level (32 bytes, AoS for gathers).
@@ -234,11 +235,12 @@ hipError_t launch_exscan(const uint32_t* cnt, uint32_t* start, int32_t n, uint32
 constexpr int kScanChunk = 4096;
 inline size_t exscan_scratch_words(size_t n) { return 2 * ((n + kScanChunk - 1) / kScanChunk) + 2; }
 // Binning blocks: nb blocks of kBinThreads own per_block consecutive segments each; tiles are
-// counted in passes of `range` tiles.  The per-block count matrix M holds nb * T words.
+// counted in passes of `range` tiles, `lanes` threads per segment.  The per-block count matrix M
+// holds nb * T words.  wide: a thick-hair level (more blocks and a larger M for few segments).
 struct BinPlan {
-    int nb, per_block, range;
+    int nb, per_block, range, lanes;
 };
-BinPlan bin_plan(int32_t nseg, int32_t T);
+BinPlan bin_plan(int32_t nseg, int32_t T, bool wide = false);
 // M (nb * T words), blk (nb entries), tot (T words): per-block counts and segment statistics and
 // the tiles' list lengths of the projected segments; ctr is cleared and receives the visible /
 // culled counts and the largest half-width.

@@ -337,7 +337,7 @@ __device__ inline uint32_t group_width_bits(const HierDev& h, int l, int g, int 
 // Initial levels: the coarsest l >= 1 whose width is <= eps_w, else 0 (the strands).  The wave's
 // lanes take the owners of all levels, coarsest first, 64 at a time, and stop at the level that
 // passes: a coarse level has one owner per group or a few, and one after the other the levels are a
-// chain of gathers (bound by their latency: 150k strands, 3 levels 30 -> 21 us).
+// chain of gathers (bound by their latency: 100k strands, three levels, 30 -> 21 us).
 __global__ __launch_bounds__(256) void k_lod_init(HierDev h, CamConst cam, float eps_w, int32_t* __restrict__ levels) {
     const int gk = (int)(blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6));
     if (gk >= h.G * h.S) return;
@@ -747,12 +747,14 @@ struct FootprintRows {
     }
 };
 
+// (row0, step: the tile rows ty0 + row0, ty0 + row0 + step, ... of the segment)
 template <class F>
-__device__ inline void for_each_tile_in_range(const SegRec& r, int ntx, int nty, int t0, int nt, F&& f) {
+__device__ inline void for_each_tile_in_range(const SegRec& r, int ntx, int nty, int t0, int nt, int row0, int step,
+                                              F&& f) {
     if (!(r.hwfx & kFlagVisible)) return;
     const TileRect rc = tile_rect(r, ntx, nty);
     if ((r.hwfx & kHwMask) + 8 <= 32) {
-        for (int ty = rc.ty0; ty <= rc.ty1; ++ty)
+        for (int ty = rc.ty0 + row0; ty <= rc.ty1; ty += step)
             for (int tx = rc.tx0; tx <= rc.tx1; ++tx) {
                 const int l = ty * ntx + tx - t0;
                 if ((unsigned)l < (unsigned)nt) f(l);
@@ -760,7 +762,7 @@ __device__ inline void for_each_tile_in_range(const SegRec& r, int ntx, int nty,
         return;
     }
     const FootprintRows fp(r, rc);
-    for (int ty = rc.ty0; ty <= rc.ty1; ++ty) {
+    for (int ty = rc.ty0 + row0; ty <= rc.ty1; ty += step) {
         int lo = rc.tx0, hi = rc.tx1;
         fp.clip(ty, rc.tx0, lo, hi);
         for (int tx = lo; tx <= hi; ++tx) {
@@ -772,6 +774,12 @@ __device__ inline void for_each_tile_in_range(const SegRec& r, int ntx, int nty,
 
 // The first pass also leaves per-block segment statistics in blk[b] = (visible, culled as too
 // long, bits of the largest visible half-width) for k_bin_offsets to reduce.
+//
+// LANES: lanes that share a segment, one tile row each in turn.  One for strands (a strand's box has
+// a row or two).  A thick-hair level has few segments of many rows: with one lane each, 16 k of them
+// fill 32 blocks, and each lane walks a dozen rows (count and scatter of 1000 hairs of 64 segments at
+// 1080p with one and with eight lanes: 32 + 43 -> 20 + 30 us, k_bin_offsets 6 -> 12).
+template <int LANES>
 __global__ __launch_bounds__(kBinThreads) void k_bin_count(const SegRec* __restrict__ seg, int nseg, int per_block,
                                                            int ntx, int nty, int t0, int nt,
                                                            uint32_t* __restrict__ M, uint4* __restrict__ blk) {
@@ -783,15 +791,18 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_count(const SegRec* __restr
     __syncthreads();
     const int g0 = blockIdx.x * per_block, g1 = min(nseg, g0 + per_block);
     uint32_t nvis = 0, nlong = 0, nsplit = 0, maxhw = 0;
-    for (int g = g0 + (int)threadIdx.x; g < g1; g += kBinThreads) {
+    const int row0 = (int)threadIdx.x % LANES;
+    for (int g = g0 + (int)threadIdx.x / LANES; g < g1; g += kBinThreads / LANES) {
         const SegRec r = seg[g];
-        if (r.hwfx & kFlagVisible) {
-            ++nvis;
-            maxhw = max(maxhw, __float_as_uint(r.hw));
+        if (LANES == 1 || row0 == 0) {
+            if (r.hwfx & kFlagVisible) {
+                ++nvis;
+                maxhw = max(maxhw, __float_as_uint(r.hw));
+            }
+            nlong += (r.hwfx & kFlagCulledLong) ? 1u : 0u;
+            nsplit += (r.hwfx & kFlagSplit) ? 1u : 0u;
         }
-        nlong += (r.hwfx & kFlagCulledLong) ? 1u : 0u;
-        nsplit += (r.hwfx & kFlagSplit) ? 1u : 0u;
-        for_each_tile_in_range(r, ntx, nty, t0, nt, [&](int l) { atomicAdd(&s_tc[l], 1u); });
+        for_each_tile_in_range(r, ntx, nty, t0, nt, row0, LANES, [&](int l) { atomicAdd(&s_tc[l], 1u); });
     }
     if (t0 == 0) {
         if (maxhw) atomicMax(&s_maxhw, maxhw);
@@ -928,6 +939,7 @@ __device__ inline void fill_frame(const FillArgs& a, int T) {
 
 // The blocks b < nb append their segments; every block (more are launched where the image is large
 // for its segments) then does its share of fill_frame, which saves a launch.
+template <int LANES>
 __global__ __launch_bounds__(kBinThreads) void k_scatter(const SegRec* __restrict__ seg, int nseg, int per_block,
                                                          int nb, int ntx, int nty, int t0, int nt,
                                                          const uint32_t* __restrict__ tile_start,
@@ -941,8 +953,9 @@ __global__ __launch_bounds__(kBinThreads) void k_scatter(const SegRec* __restric
     for (int i = threadIdx.x; i < nt; i += kBinThreads) s_tc[i] = tile_start[t0 + i] + row[i];
     __syncthreads();
     const int g0 = blockIdx.x * per_block, g1 = min(nseg, g0 + per_block);
-    for (int g = g0 + (int)threadIdx.x; g < g1; g += kBinThreads)
-        for_each_tile_in_range(seg[g], ntx, nty, t0, nt, [&](int l) { list[atomicAdd(&s_tc[l], 1u)] = (uint32_t)g; });
+    for (int g = g0 + (int)threadIdx.x / LANES; g < g1; g += kBinThreads / LANES)
+        for_each_tile_in_range(seg[g], ntx, nty, t0, nt, (int)threadIdx.x % LANES, LANES,
+                               [&](int l) { list[atomicAdd(&s_tc[l], 1u)] = (uint32_t)g; });
 }
 
 // The frame's sizes against the buffers' capacities (one thread).
@@ -3770,14 +3783,15 @@ hipError_t launch_dom_map(const FrameBufs& f, const CamConst& cam, const LevelDe
     return hipGetLastError();
 }
 
-BinPlan bin_plan(int32_t nseg, int32_t T) {
+BinPlan bin_plan(int32_t nseg, int32_t T, bool wide) {
     BinPlan p;
+    p.lanes = wide ? kBinLanes : 1;
     p.range = std::min(T, kMaxLdsTiles);
     const int bytes = 4 * p.range;
     const int per_cu = std::max(1, std::min(2, (160 * 1024) / (bytes + 2048)));
     long nb = 256L * per_cu;
     nb = std::min(nb, std::max(32L, (long)((1 << 24) / std::max(T, 1))));
-    nb = std::min(nb, std::max(1L, (long)((nseg + kBinThreads - 1) / kBinThreads)));
+    nb = std::min(nb, std::max(1L, ((long)nseg * p.lanes + kBinThreads - 1) / kBinThreads));
     p.nb = (int)std::max(1L, nb);
     p.per_block = (nseg + p.nb - 1) / p.nb;
     return p;
@@ -3794,11 +3808,12 @@ static hipError_t allow_lds(const void* fn, int bytes) {
 hipError_t launch_bins(const SegRec* seg, int32_t nseg, const CamConst& cam, const BinPlan& p, uint32_t* M,
                        uint4* blk, uint32_t* tot, Counters* ctr, hipStream_t st) {
     const int ntx = (cam.W + kTile - 1) / kTile, nty = (cam.H + kTile - 1) / kTile, T = ntx * nty;
-    hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_bin_count), 4 * p.range);
+    auto kernel = p.lanes > 1 ? &k_bin_count<kBinLanes> : &k_bin_count<1>;
+    hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), 4 * p.range);
     if (e != hipSuccess) return e;
     for (int t0 = 0; t0 < T; t0 += p.range) {
         const int nt = std::min(p.range, T - t0);
-        hipLaunchKernelGGL(k_bin_count, dim3(p.nb), dim3(kBinThreads), 4 * nt, st, seg, nseg, p.per_block, ntx, nty,
+        hipLaunchKernelGGL(kernel, dim3(p.nb), dim3(kBinThreads), 4 * nt, st, seg, nseg, p.per_block, ntx, nty,
                            t0, nt, M, blk);
     }
     hipLaunchKernelGGL(k_bin_offsets, dim3(blocks_for(T, 64)), dim3(1024), 0, st, M, p.nb, T, tot, blk, ctr);
@@ -3823,7 +3838,8 @@ hipError_t launch_scatter(const FrameBufs& f, int32_t nseg, const CamConst& cam,
                           uint32_t* list, float* rgba, unsigned long long* acc, size_t n_acc, uint2* item_tab,
                           uint32_t cap_items, hipStream_t st) {
     const int ntx = (cam.W + kTile - 1) / kTile, nty = (cam.H + kTile - 1) / kTile, T = ntx * nty;
-    hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_scatter), 4 * p.range);
+    auto kernel = p.lanes > 1 ? &k_scatter<kBinLanes> : &k_scatter<1>;
+    hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), 4 * p.range);
     if (e != hipSuccess) return e;
     const FillArgs fill{f.pix_cnt, f.pix_off, f.pix_kmin, f.pix_kmax, f.opaque ? 0xFFFFFFFFu : 0u, f.pix_thick,
                         reinterpret_cast<float4*>(rgba), rgba ? (size_t)cam.W * cam.H : 0,
@@ -3832,7 +3848,7 @@ hipError_t launch_scatter(const FrameBufs& f, int32_t nseg, const CamConst& cam,
     for (int t0 = 0; t0 < T; t0 += p.range) {
         const int nt = std::min(p.range, T - t0);
         const int grid = t0 == 0 ? std::max(p.nb, std::min(256, blocks_for(T, 8))) : p.nb;
-        hipLaunchKernelGGL(k_scatter, dim3(grid), dim3(kBinThreads), 4 * nt, st, f.seg, nseg, p.per_block, p.nb, ntx, nty,
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBinThreads), 4 * nt, st, f.seg, nseg, p.per_block, p.nb, ntx, nty,
                            t0, nt, f.tile_start, M, list, f.ctr, fill);
     }
     return hipGetLastError();
