@@ -714,9 +714,9 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
                                     ws->dom_acc.as<unsigned long long>(), dom->tex, st),
                 "k_dom_first");
     } else if (grad) {
-        HIP_TRY(ctx, launch_fill_f32(grad->d_axes, 0.0f, 2ull * (tess ? tess->base.nseg : lv.nseg), st), "fill");
-        HIP_TRY(ctx, launch_fill_f32(grad->d_r, 0.0f, (size_t)lv.n_owner, st), "fill");
-        HIP_TRY(ctx, launch_fill_f32(grad->d_sig, 0.0f, 3ull * lv.n_owner, st), "fill");
+        const Arrays3 zero{{grad->d_axes, grad->d_r, grad->d_sig}, {},
+                           {2ull * (tess ? tess->base.nseg : lv.nseg), (size_t)lv.n_owner, 3ull * lv.n_owner}};
+        HIP_TRY(ctx, launch_set3(zero, st), "fill");
         HIP_TRY(ctx, launch_batches_bwd(f, lv, cc, lc, mat_const(a.mat), batch_grid, *grad, st), "k_batch_bwd");
     } else if (rgba) {
         HIP_TRY(ctx, launch_batches(f, lv, cc, lc, mat_const(a.mat), batch_grid, rgba, dbg, st), "k_batch");
@@ -1279,6 +1279,19 @@ int hair_set_cluster_params(hair_ctx* ctx, int32_t asset, int32_t level, const f
     if ((rc = need_device(ctx))) return rc;
     Level& L = a.levels[level - 1];
     hipStream_t st = (hipStream_t)stream;
+    const Arrays3 copy{{L.axes.as<float>(), L.r.as<float>(), L.sig.as<float>()}, {axes, r, sigma_a},
+                       {axes ? 2ull * L.K * L.S : 0, r ? (size_t)L.K : 0, sigma_a ? 3ull * L.K : 0}};
+    bool ours = true;   // arrays of this device; others (a peer's, the host's) are left to the runtime
+    for (const float* p : copy.src) {
+        hipPointerAttribute_t at;
+        if (!p || !ours) continue;
+        ours = hipPointerGetAttributes(&at, p) == hipSuccess && at.type == hipMemoryTypeDevice && at.device == ctx->device;
+        if (!ours) (void)hipGetLastError();
+    }
+    if (ours) {
+        HIP_TRY(ctx, launch_set3(copy, st), "set_cluster_params");
+        return HAIR_OK;
+    }
     hipError_t e = hipSuccess;
     if (axes) e = hipMemcpyAsync(L.axes.p, axes, 8ull * L.K * L.S, hipMemcpyDeviceToDevice, st);
     if (e == hipSuccess && r) e = hipMemcpyAsync(L.r.p, r, 4ull * L.K, hipMemcpyDeviceToDevice, st);

@@ -320,6 +320,12 @@ hipError_t launch_dom_map(const FrameBufs& f, const CamConst& cam, const LevelDe
                           const DomGrid* grid, int32_t K, float delta, float rdelta, uint32_t n_items,
                           unsigned long long* acc, float4* tex, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t st);
+struct Arrays3 {
+    float* dst[3];
+    const float* src[3];   // nullptr: the array is cleared
+    size_t n[3];
+};
+hipError_t launch_set3(const Arrays3& a, hipStream_t st);
 hipError_t launch_fill_f32(float* p, float v, size_t n, hipStream_t st);
 hipError_t launch_probe_rate(int kind, int blocks, int iters, float* out, hipStream_t st);
 

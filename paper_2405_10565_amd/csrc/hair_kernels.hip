@@ -982,6 +982,14 @@ __global__ void k_fill_u32(uint32_t* p, uint32_t v, size_t n) {
 __global__ void k_fill_f32(float* p, float v, size_t n) {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
 }
+// Three arrays copied (src set) or cleared in one launch: a fitting step's parameters and gradients
+// are small, and each copy or clear of its own costs the host and the stream more than its bytes.
+__global__ void k_set3(Arrays3 a) {
+    const size_t i0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        for (size_t i = i0; i < a.n[k]; i += step) a.dst[k][i] = a.src[k] ? a.src[k][i] : 0.0f;
+}
 
 // ---------------------------------------------------------------------------------------
 // Coverage: every fragment of a tile's segments, with the work shared across a wave.  A
@@ -4093,6 +4101,13 @@ hipError_t launch_probe_rate(int kind, int blocks, int iters, float* out, hipStr
         case 4: hipLaunchKernelGGL(k_probe_rate<4>, dim3(blocks), dim3(256), 0, st, out, iters); break;
         default: hipLaunchKernelGGL(k_probe_rate<5>, dim3(blocks), dim3(256), 0, st, out, iters); break;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_set3(const Arrays3& a, hipStream_t st) {
+    const size_t n = std::max(a.n[0], std::max(a.n[1], a.n[2]));
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_set3, dim3(min(blocks_for(n, 256), 4096)), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
