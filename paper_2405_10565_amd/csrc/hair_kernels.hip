@@ -1047,10 +1047,10 @@ __device__ inline int strip_opaque(float hw, int tden) {
 }
 // The smallest depth key a segment's fragments can have (its nearer end; 8 ulps of slack for the
 // rounding of the interpolation between the ends).
-__device__ inline uint32_t nearest_key(const float2 iz) {
+__device__ inline uint32_t nearest_key(const float4 iz) {
     return 0xFFFFFFFFu - __float_as_uint(fmaxf(iz.x, iz.y)) - 8u;
 }
-__device__ inline uint32_t nearest_key(const SegRec& s) { return nearest_key(make_float2(s.iza, s.izb)); }
+__device__ inline uint32_t nearest_key(const SegRec& s) { return nearest_key(make_float4(s.iza, s.izb, 0.0f, 0.0f)); }
 
 // floor(n / d) for 1 <= d <= 2^18 where it lies in [-17, 17]; a quotient beyond that range
 // comes back beyond [-17, 16] on its own side.  rd: the hardware reciprocal of d.
@@ -1179,17 +1179,35 @@ __device__ inline void wave_coverage(const CovSetup* s_cov, const uint8_t* s_own
     }
 }
 
-__device__ inline uint32_t depth_key_iz(float iza, float izb, int tnum, int tden) {
-    const float t = (float)tnum / (float)tden;
+// a / b, correctly rounded, from the correctly rounded reciprocal rb of a divisor that many
+// fragments share (Markstein: a quotient within one ulp, which the first correction gives, and one
+// more step with the exact remainder): 5 instructions instead of the general division's 11.  rb = 0
+// (a divisor outside [2^-100, 2^100]) takes the general one.
+__device__ inline float div_rcp(float a, float b, float rb) {
+    float q = a * rb;
+    q = __builtin_fmaf(__builtin_fmaf(-q, b, a), rb, q);
+    return __builtin_fmaf(__builtin_fmaf(-q, b, a), rb, q);
+}
+__device__ inline float div_by(float a, float b, float rb) { return rb == 0.0f ? a / b : div_rcp(a, b, rb); }
+
+// A fragment's depth key: its inverse depth, affine on screen, as descending float bits.  rtd: 1 / t_den
+// correctly rounded (once per segment; the quotient is that of the plain division).
+__device__ inline uint32_t depth_key_iz(float iza, float izb, int tnum, int tden, float rtd) {
+    const float t = div_rcp((float)tnum, (float)tden, rtd);
     const float iz = iza + t * (izb - iza);
     return 0xFFFFFFFFu - __float_as_uint(iz);
+}
+// What the passes that need keys stage of a segment: (izA, izB, 1 / t_den, 0)
+__device__ inline float4 key_inputs(const SegRec& s) {
+    const int dx = s.xb - s.xa, dy = s.yb - s.ya;
+    return make_float4(s.iza, s.izb, 1.0f / (float)(dx * dx + dy * dy), 0.0f);
 }
 
 // A cheap upper bound of a fragment's inverse depth, for the tests against the opaque keys: the
 // reciprocal product in place of the division errs by under 2^-21 of the nearer end, and the bound
 // adds 2^-20 of it.  Most fragments of a stack of thick hairs lie clearly behind and need no more.
-__device__ inline float iz_bound(const float2 iz, int tnum, int tden) {
-    const float t = (float)tnum * __builtin_amdgcn_rcpf((float)tden);
+__device__ inline float iz_bound(const float4 iz, int tnum) {
+    const float t = (float)tnum * iz.z;
     return (iz.x + t * (iz.y - iz.x)) + fmaxf(iz.x, iz.y) * 0x1p-20f;
 }
 // The inverse depth of an opaque key (0 for none: nothing lies behind it).
@@ -1222,17 +1240,6 @@ __device__ inline void dom_point(const SegRec& s, const float4& q0, const float4
     y = q0.y + tw * (q1.y - q0.y);
     z = q0.z + tw * (q1.z - q0.z);
 }
-
-// a / b, correctly rounded, from the correctly rounded reciprocal rb of a divisor that many
-// fragments share (Markstein: a quotient within one ulp, which the first correction gives, and one
-// more step with the exact remainder): 5 instructions instead of the general division's 11.  rb = 0
-// (a divisor outside [2^-100, 2^100]) takes the general one.
-__device__ inline float div_rcp(float a, float b, float rb) {
-    float q = a * rb;
-    q = __builtin_fmaf(__builtin_fmaf(-q, b, a), rb, q);
-    return __builtin_fmaf(__builtin_fmaf(-q, b, a), rb, q);
-}
-__device__ inline float div_by(float a, float b, float rb) { return rb == 0.0f ? a / b : div_rcp(a, b, rb); }
 
 // delta = |cross| / (16 sqrt(t_den)), the pixel centre's distance from the centre line in pixels,
 // in double: the hardware reciprocal square root refined by one Newton step (relative error
@@ -1626,7 +1633,7 @@ __global__ __launch_bounds__(kNT) void k_opaque(FrameBufs f, CamConst cam, int f
     __shared__ HideLds s_hide;
     __shared__ CovSetup s_cov[kNT];
     __shared__ uint8_t s_own[kNT / 64 * kCovLinesPerWave];
-    __shared__ float2 s_iz[kNT];
+    __shared__ float4 s_iz[kNT];
     const uint32_t n_items = f.item_start[f.T];
     if (blockIdx.x >= n_items || f.ctr->cap_overflow) return;
     if (!(__uint_as_float(f.ctr->max_hw_bits) > 0.5f + kOpaqueMargin)) return;
@@ -1646,18 +1653,21 @@ __global__ __launch_bounds__(kNT) void k_opaque(FrameBufs f, CamConst cam, int f
     const uint32_t z0 = gx < cam.W && gy < cam.H ? f.pix_kmax[q] : 0u;
     hide_setup(s_hide, z0);
     uint32_t* s_z = s_hide.z;
-    s_iz[t] = make_float2(s.iza, s.izb);
+    s_iz[t] = key_inputs(s);
     const bool valid = j < n && s.hw > 0.5f + kOpaqueMargin && (!first || (t & 63) % (64 / kFirstLanes) == 0);
     const uint32_t total = cov_setup<kOpaque>(
         s, valid, px0, py0, cam.W, cam.H, s_cov, s_own,
         [&](int i0, int i1, int j0, int j1) { return box_hidden(s_hide, nearest_key(s), i0, i1, j0, j1); });
-    wave_coverage(s_cov, s_own, total, [&](int p, int tnum, int tden, int o, int) {
-        const float2 iz = s_iz[o];
+    float4 iz;   // (the line's segment)
+    wave_coverage(s_cov, s_own, total, [&](int p, int tnum, int tden, int, int) {
         const uint32_t z = s_z[p];
-        if (iz_bound(iz, tnum, tden) < iz_of_key(z)) return;
-        const uint32_t key = depth_key_iz(iz.x, iz.y, tnum, tden);
+        if (iz_bound(iz, tnum) < iz_of_key(z)) return;
+        const uint32_t key = depth_key_iz(iz.x, iz.y, tnum, tden, iz.z);
         if (key < z) atomicMin(&s_z[p], key);
-    }, [&](int o, int p, int n, bool steep) { return line_hidden(s_hide, nearest_key(s_iz[o]), p, n, steep); });
+    }, [&](int o, int p, int n, bool steep) {
+        iz = s_iz[o];
+        return line_hidden(s_hide, nearest_key(iz), p, n, steep);
+    });
     __syncthreads();
     if (s_z[t] < z0) atomicMin(&f.pix_kmax[q], s_z[t]);
 }
@@ -1673,7 +1683,7 @@ __global__ __launch_bounds__(kNT) void k_count(FrameBufs f, CamConst cam) {
     __shared__ uint32_t s_cnt[kTilePix];
     __shared__ HideOf<ZC> s_hide[1];
     __shared__ uint32_t s_dr[ZC ? kTilePix : 1], s_dc[ZC ? kTilePix : 1];   // see below
-    __shared__ float2 s_iz[ZC ? kNT : 1];
+    __shared__ float4 s_iz[ZC ? kNT : 1];
     __shared__ CovSetup s_cov[kNT];
     __shared__ int s_vis[TRIM ? kNT : 1];   // |cross| up to which the segment's fragments have coverage
     __shared__ uint8_t s_own[kNT / 64 * kCovLinesPerWave];
@@ -1694,7 +1704,7 @@ __global__ __launch_bounds__(kNT) void k_count(FrameBufs f, CamConst cam) {
     const size_t q = (size_t)tile * kTilePix + t;
     if constexpr (ZC) {
         s_dr[t] = s_dc[t] = 0u;
-        s_iz[t] = make_float2(s.iza, s.izb);
+        s_iz[t] = key_inputs(s);
         const int gx = px0 + (t % kTile), gy = py0 + (t / kTile);
         hide_setup(s_hide[0], gx < cam.W && gy < cam.H ? f.pix_kmax[q] : 0u);
     }
@@ -1703,20 +1713,21 @@ __global__ __launch_bounds__(kNT) void k_count(FrameBufs f, CamConst cam) {
         s_vis[t] = strip_vis(s.hw, dx * dx + dy * dy, 0x7FFFFFFF);
     }
     const uint32_t total = cov_setup<kAll>(s, j < n, px0, py0, cam.W, cam.H, s_cov, s_own);
-    wave_coverage(s_cov, s_own, total, [&](int p, int tnum, int tden, int o, int cr) {
+    float4 iz;   // (the line's segment)
+    int vis = 0;
+    wave_coverage(s_cov, s_own, total, [&](int p, int tnum, int tden, int, int cr) {
         bool stored = true;
-        if constexpr (TRIM) stored = abs(cr) <= s_vis[o];
+        if constexpr (TRIM) stored = abs(cr) <= vis;
         if constexpr (ZC) {
-            if (stored) {
-                const float2 iz = s_iz[o];
-                stored = depth_key_iz(iz.x, iz.y, tnum, tden) <= s_hide[0].z[p];
-            }
+            if (stored) stored = depth_key_iz(iz.x, iz.y, tnum, tden, iz.z) <= s_hide[0].z[p];
         }
         atomicAdd(&s_cnt[p], stored ? 1u : 0x10000u);
     }, [&](int o, int p, int n, bool steep) {
         // a line hidden as a whole: its pixels are only counted, as differences along the line (+1
         // where it begins, -1 behind its end) that two row sums add up below
-        if (!ZC || !line_hidden(s_hide[0], nearest_key(s_iz[ZC ? o : 0]), p, n, steep)) return false;
+        if constexpr (ZC) iz = s_iz[o];
+        if constexpr (TRIM) vis = s_vis[o];
+        if (!ZC || !line_hidden(s_hide[0], nearest_key(iz), p, n, steep)) return false;
         uint32_t* d = steep ? s_dr : s_dc;
         const int i = steep ? p : ((p & 15) << 4 | p >> 4);   // (columns are kept transposed)
         atomicAdd(&d[ZC ? i : 0], 1u);
@@ -1940,12 +1951,10 @@ __global__ __launch_bounds__(kNT) void k_batch_records(FrameBufs f) {
 template <bool MIXED, bool ZC>
 __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
     __shared__ uint32_t s_cur[kTilePix], s_pos[kTilePix], s_kmin[kTilePix], s_kmax[kTilePix];
-    __shared__ uint32_t s_id[kNT];   // each owner's record word: global segment id or list index,
-                                     // bit 31: a thick hair of a mixed frame
     __shared__ uint8_t s_thk[kTilePix];   // mixed frames: the pixel holds a thick-hair fragment
     __shared__ CovSetup s_cov[kNT];
     __shared__ uint8_t s_own[kNT / 64 * kCovLinesPerWave];
-    __shared__ float2 s_iz[kNT];
+    __shared__ float4 s_iz[kNT];
     __shared__ HideOf<ZC> s_hide[1];
     PHASE_BEGIN();
     const uint32_t n_items = f.item_start[f.T];
@@ -1972,8 +1981,10 @@ __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
         gseg = f.list[lstart + j];
         s = f.seg[gseg];
     }
-    s_iz[t] = make_float2(s.iza, s.izb);
-    s_id[t] = (f.gid ? gseg : j) | (MIXED && (s.hwfx & kFlagThick) ? 0x80000000u : 0u);
+    // (w: each owner's record word, the global segment id or list index; bit 31: a thick hair of a
+    // mixed frame)
+    s_iz[t] = key_inputs(s);
+    s_iz[t].w = __uint_as_float((f.gid ? gseg : j) | (MIXED && (s.hwfx & kFlagThick) ? 0x80000000u : 0u));
     const bool valid = j < n;
     if constexpr (ZC) {
         const uint32_t z0 = off & kHidesBit ? f.pix_kmax[q] : 0xFFFFFFFFu;
@@ -1985,18 +1996,19 @@ __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
     };
     const uint32_t total = f.trim ? cov_setup<kVisible>(s, valid, px0, py0, cam.W, cam.H, s_cov, s_own, drop)
                                   : cov_setup<kAll>(s, valid, px0, py0, cam.W, cam.H, s_cov, s_own, drop);
-    wave_coverage(s_cov, s_own, total, [&](int p, int tnum, int tden, int o, int) {
-        const float2 iz = s_iz[o];
-        const uint32_t key = depth_key_iz(iz.x, iz.y, tnum, tden);
+    float4 iz;   // (the line's segment)
+    wave_coverage(s_cov, s_own, total, [&](int p, int tnum, int tden, int, int) {
+        const uint32_t key = depth_key_iz(iz.x, iz.y, tnum, tden, iz.z);
         if (ZC && key > s_hide[0].z[ZC ? p : 0]) return;
         const uint32_t slot = atomicAdd(&s_cur[p], 1u);
         atomicMin(&s_kmin[p], key);
         atomicMax(&s_kmax[p], key);
-        const uint32_t id = s_id[o];
+        const uint32_t id = __float_as_uint(iz.w);
         if (MIXED && (id >> 31)) s_thk[p] = 1;
         f.frags[s_pos[p] + slot] = make_uint2(key, (id & 0xFFFFFFu) | ((uint32_t)p << 24));
     }, [&](int o, int p, int n, bool steep) {
-        return ZC && line_hidden(s_hide[0], nearest_key(s_iz[o]), p, n, steep);
+        iz = s_iz[o];
+        return ZC && line_hidden(s_hide[0], nearest_key(iz), p, n, steep);
     });
     __syncthreads();
     if (s_cur[t]) {
@@ -2004,9 +2016,9 @@ __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
         atomicMax(&f.pix_kmax[q], s_kmax[t]);
         if (MIXED && s_thk[t]) f.pix_thick[q] = 1;
     }
-    // the tile's batch records, by the block of its first chunk (s_id is free once the waves pass the
+    // the tile's batch records, by the block of its first chunk (s_pos is free once the waves pass the
     // barrier above)
-    if (!MIXED && it.y == 0) batch_records(f, tile, s_id, s_id + kTilePix / 32);
+    if (!MIXED && it.y == 0) batch_records(f, tile, s_pos, s_pos + kTilePix / 32);
     PHASE_END(f.ctr, 1);
 }
 
@@ -3537,7 +3549,7 @@ __global__ __launch_bounds__(256) void k_project_light(LevelDev lv, const ShadeR
 // sample of each list, so that the first one could skip what lies behind, gained nothing.
 __global__ __launch_bounds__(kNT) void k_dom_first(FrameBufs f, CamConst cam, int group) {
     __shared__ uint32_t s_z[kTilePix];
-    __shared__ float2 s_iz[kNT];
+    __shared__ float4 s_iz[kNT];
     __shared__ CovSetup s_cov[kNT];
     __shared__ uint8_t s_own[kNT / 64 * kCovLinesPerWave];
     const uint32_t n_items = f.item_start[f.T];
@@ -3554,13 +3566,13 @@ __global__ __launch_bounds__(kNT) void k_dom_first(FrameBufs f, CamConst cam, in
         const uint32_t j = k * kNT + t;
         SegRec s{};
         if (j < n) s = f.seg[f.list[lstart + j]];
-        s_iz[t] = make_float2(s.iza, s.izb);
+        s_iz[t] = key_inputs(s);
         const uint32_t total = cov_setup<kAll>(s, j < n, px0, py0, cam.W, cam.H, s_cov, s_own);
-        float2 iz;   // (the line's segment)
+        float4 iz;   // (the line's segment)
         wave_coverage(s_cov, s_own, total, [&](int p, int tnum, int tden, int, int) {
             const uint32_t z = s_z[p];
-            if (iz_bound(iz, tnum, tden) < iz_of_key(z)) return;
-            const uint32_t key = depth_key_iz(iz.x, iz.y, tnum, tden);
+            if (iz_bound(iz, tnum) < iz_of_key(z)) return;
+            const uint32_t key = depth_key_iz(iz.x, iz.y, tnum, tden, iz.z);
             if (key < z) atomicMin(&s_z[p], key);
         }, [&](int o, int, int, bool) {
             iz = s_iz[o];
