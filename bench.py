@@ -46,7 +46,9 @@ METRIC = "Mfragments/s + frame ms (100k strands, 1080p); served p50/p99 latency"
 # published FP32 vector rate, 157.3 TFLOP/s = 256 CUs x 128 FP32 lanes x 2.4 GHz x 2 (FMA), i.e.
 # 78.6 T lane-operations per second.  (Measured on the device with --rate-probe: unpacked
 # v_fma_f32 issues at ~56 T/s, v_exp/v_rcp/v_sqrt at ~18 T/s.)  A kernel that fuses
-# multiply-adds issues fewer lane-operations than counted, so the fraction credits fusion.
+# multiply-adds issues fewer lane-operations than counted, so the fraction credits fusion.  The
+# strand frame's count includes its fragments without coverage (alpha exactly 0, about one in
+# twenty), which the definition evaluates and the kernel leaves out: the fraction credits that too.
 OPS_FILE = os.path.join(ROOT, "tests", "golden", "ops_per_fragment.json")
 TRANS_WEIGHT = 4                                # transcendental unit issues at 1/4 rate
 PEAK_LANE_OPS = 256 * 128 * 2.4e9               # 256 CUs x 128 FP32 lanes x 2.4 GHz = 157.3 TFLOP/s / 2
@@ -188,8 +190,7 @@ def rttd_frame(ctx, asset, cam, lights, ws, frames: int = 20):
 
 def thick_frame(ctx, ws, clusters: int = 1000, frames: int = 20):
     """A thick-hair frame of the level sweep (150k strands x 64 segments, seeded k-means to 1k
-    thick hairs, 1920 x 1080, directional + point light) with the roofline of its shading
-    kernel k_batch<1, 0, false> (outside the timed region)."""
+    thick hairs, 1920 x 1080, directional + point light; outside the timed region)."""
     import numpy as np
     import hairsynth as hs
     t0 = time.perf_counter()
@@ -208,7 +209,9 @@ def thick_frame(ctx, ws, clusters: int = 1000, frames: int = 20):
     return {"workload": f"hair-150k-strands-64seg-{clusters}-thick-hairs-1920x1080-2lights",
             "gpu_mean": round(float(np.mean(ms)), 4), "gpu_p50": round(float(np.percentile(ms, 50)), 4),
             "fragments": int(st["fragments"]), "k_batch_ms": round(t * 1e3, 4),
-            "roofline": roofline(int(st["fragments"]), lights, t, "thick_1080p", "k_batch<1, 0, false>")}
+            # (the kernel shades only what no opaque fragment hides, under 1% of the counted fragments
+            # here, so operations per counted fragment say nothing about its rate)
+            "roofline": None}
 
 
 def shadowed_frame(ctx, aid, cam, lights, ws, shadow=(1024, 4, 0.02), frames: int = 20):
