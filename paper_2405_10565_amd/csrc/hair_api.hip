@@ -134,7 +134,9 @@ struct hair_ws {
         uint32_t pairs = 0, n_batches = 0;
         float ms[4] = {};
     } pending;
-    Counters* ctr_host = nullptr;   // pinned copy of a deferred frame's counters
+    // pinned: a frame's counters, and the sizes read back before (a copy into pageable memory costs a
+    // frame some 20 us more)
+    Counters* ctr_host = nullptr;
     // A workspace over the device's static scratch (hair_render_noalloc): its buffers are
     // carved from [arena, arena + arena_bytes) afresh for every frame and never allocated.
     unsigned char* arena = nullptr;
@@ -440,7 +442,21 @@ int ws_events(hair_ws* ws) {
     for (int i = 0; i < 7; ++i)
         HIP_TRY(ws->ctx, i == 1 ? hipEventCreateWithFlags(&ws->ev[i], hipEventDisableTiming) : hipEventCreate(&ws->ev[i]),
                 "hipEventCreate");
+    if (!ws->ctr_host)
+        HIP_TRY(ws->ctx, hipHostMalloc((void**)&ws->ctr_host, sizeof(Counters), hipHostMallocDefault), "hipHostMalloc");
     ws->events = true;
+    return HAIR_OK;
+}
+
+// A few words of device memory, by way of the workspace's pinned ones.  Synchronises st.
+int read_words(hair_ctx* ctx, hair_ws* ws, const uint32_t* src, int n, hipStream_t st, uint32_t* out) {
+    int rc;
+    if (ws->pending.active)
+        return fail(HAIR_EINVAL, "the workspace holds a frame of hair_render_async: call hair_ws_finish first");
+    if ((rc = ws_events(ws))) return rc;
+    HIP_TRY(ctx, hipMemcpyAsync(ws->ctr_host, src, 4 * n, hipMemcpyDeviceToHost, st), "copy");
+    HIP_TRY(ctx, hipStreamSynchronize(st), "sync");
+    memcpy(out, ws->ctr_host, 4 * n);
     return HAIR_OK;
 }
 
@@ -583,7 +599,7 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     FrameCaps caps = ws->caps;
     uint32_t pairs = 0, n_items = 0;
     if (!warm) {
-        uint32_t sizes1[2] = {0, 0};
+        uint32_t* sizes1 = reinterpret_cast<uint32_t*>(ws->ctr_host);
         HIP_TRY(ctx, hipMemcpyAsync(&sizes1[0], tile_start + T, 4, hipMemcpyDeviceToHost, st), "copy");
         HIP_TRY(ctx, hipMemcpyAsync(&sizes1[1], ws->item_start.as<uint32_t>() + T, 4, hipMemcpyDeviceToHost, st),
                 "copy");
@@ -671,9 +687,10 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
         }
         uint32_t n_frags = 0;
         if (!warm) {
-            uint32_t sizes2[2] = {0, 0};
-            unsigned long long all_frags = 0;
-            HIP_TRY(ctx, hipMemcpyAsync(&all_frags, &f.ctr->fragments, 8, hipMemcpyDeviceToHost, st), "copy");
+            uint32_t* sizes2 = reinterpret_cast<uint32_t*>(ws->ctr_host);
+            unsigned long long* frags2 = reinterpret_cast<unsigned long long*>(ws->ctr_host) + 1;
+            static_assert(sizeof(Counters) >= 16, "");
+            HIP_TRY(ctx, hipMemcpyAsync(frags2, &f.ctr->fragments, 8, hipMemcpyDeviceToHost, st), "copy");
             HIP_TRY(ctx, hipMemcpyAsync(&sizes2[0], ws->frag_base.as<uint32_t>() + T, 4, hipMemcpyDeviceToHost, st),
                     "copy");
             HIP_TRY(ctx, hipMemcpyAsync(&sizes2[1], ws->batch_start.as<uint32_t>() + T, 4, hipMemcpyDeviceToHost, st),
@@ -681,6 +698,7 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
             HIP_TRY(ctx, hipStreamSynchronize(st), "sync");
             n_frags = sizes2[0];
             n_batches = sizes2[1];
+            const unsigned long long all_frags = *frags2;
             caps.frags = std::max(caps.frags, cap_of(n_frags));
             // (the static scratch serves the frames whose whole fragment set it can hold)
             if (ws->arena && all_frags > n_frags) {
@@ -723,15 +741,14 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     }
     HIP_TRY(ctx, hipEventRecord(ws->ev[6], st), "hipEventRecord");
     if (defer && warm) {   // no host synchronisation: the counters land in pinned memory
-        if (!ws->ctr_host)
-            HIP_TRY(ctx, hipHostMalloc((void**)&ws->ctr_host, sizeof(Counters), hipHostMallocDefault), "hipHostMalloc");
         HIP_TRY(ctx, hipMemcpyAsync(ws->ctr_host, ws->ctr.p, sizeof(Counters), hipMemcpyDeviceToHost, st), "copy");
         HIP_TRY(ctx, hipEventRecord(ws->ev[1], st), "hipEventRecord");
         out->deferred = true;
         return HAIR_OK;
     }
-    HIP_TRY(ctx, hipMemcpyAsync(&out->ctr, ws->ctr.p, sizeof(Counters), hipMemcpyDeviceToHost, st), "copy");
+    HIP_TRY(ctx, hipMemcpyAsync(ws->ctr_host, ws->ctr.p, sizeof(Counters), hipMemcpyDeviceToHost, st), "copy");
     HIP_TRY(ctx, hipStreamSynchronize(st), "sync");
+    out->ctr = *ws->ctr_host;
     if (out->ctr.cap_overflow) {
         if (!warm) return fail(HAIR_EDEVICE, "frame sizes exceeded the capacities read for them");
         return run_frame(ctx, ws, a, lv, cam, lights, n_lights, rgba, dbg, st, out, tiles_too, grad, hier, sel, dom, views,
@@ -767,8 +784,7 @@ int split_rows(hair_ctx* ctx, hair_ws* ws, const LevelDev& lv, const hair_camera
     else
         HIP_TRY(ctx, launch_split(lv, cam_const(cam), cnt, start, ws->sel_tmp.as<uint32_t>(), st), "k_split_count");
     uint32_t nrows = 0;
-    HIP_TRY(ctx, hipMemcpyAsync(&nrows, start + n, 4, hipMemcpyDeviceToHost, st), "copy");
-    HIP_TRY(ctx, hipStreamSynchronize(st), "sync");
+    if ((rc = read_words(ctx, ws, start + n, 1, st, &nrows))) return rc;
     if (nrows >= (1u << 26)) return fail(HAIR_ERANGE, "%u pieces: the frame has 2^26 rows or more", nrows);
     if ((rc = ws_need(ws, ws->pieces, 4ull * std::max<uint32_t>(nrows, 1)))) return rc;
     HIP_TRY(ctx, launch_split_fill(cnt, start, n, ws->pieces.as<uint32_t>(), st), "k_split_fill");
@@ -1709,9 +1725,8 @@ static int render_mixed(hair_ctx* ctx, hair_ws* ws, int32_t asset, const hair_ca
         return rc;
     HIP_TRY(ctx, launch_select(h, levels, ws->sel_cnt.as<uint32_t>(), ws->sel_start.as<uint32_t>(), ws->sel_tmp.as<uint32_t>(), st),
             "k_sel_count");
-    uint32_t sizes[2] = {0, 0};
-    HIP_TRY(ctx, hipMemcpyAsync(sizes, ws->sel_start.as<uint32_t>() + GS, 8, hipMemcpyDeviceToHost, st), "copy");
-    HIP_TRY(ctx, hipStreamSynchronize(st), "sync");
+    uint32_t sizes[2];
+    if ((rc = read_words(ctx, ws, ws->sel_start.as<uint32_t>() + GS, 2, st, sizes))) return rc;
     const uint32_t nsel = sizes[0], bad = sizes[1];
     if (bad) return fail(HAIR_EINVAL, "%u entries of levels lie outside [0, %d]", bad, h.n_levels);
     if ((rc = ws_need(ws, ws->sel, 4ull * std::max<uint32_t>(nsel, 1)))) return rc;
@@ -1797,8 +1812,7 @@ int hair_render_curved(hair_ctx* ctx, hair_ws* ws, int32_t asset, int32_t level,
     HIP_TRY(ctx, launch_tess(base, cam_const(cam), max_px, max_sub, cnt, start, ws->sel_tmp.as<uint32_t>(), st),
             "k_tess_count");
     uint32_t nrows = 0;
-    HIP_TRY(ctx, hipMemcpyAsync(&nrows, start + n, 4, hipMemcpyDeviceToHost, st), "copy");
-    HIP_TRY(ctx, hipStreamSynchronize(st), "sync");
+    if ((rc = read_words(ctx, ws, start + n, 1, st, &nrows))) return rc;
     if ((rc = ws_need(ws, ws->sel, 4ull * std::max<uint32_t>(nrows, 1)))) return rc;
     HIP_TRY(ctx, launch_tess_fill(cnt, start, n, ws->sel.as<uint32_t>(), st), "k_tess_fill");
     LevelDev lv = base;
