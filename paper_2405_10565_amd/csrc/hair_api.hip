@@ -258,6 +258,24 @@ int need_device(hair_ctx* ctx) {
     return HAIR_OK;
 }
 
+// Whether [p, p + bytes) lies inside one allocation of the context's device.  (Other memory, a
+// peer's or the host's, and ranges that run past their allocation are left to the runtime's copy,
+// which serves the former and refuses the latter.)
+bool device_holds(const hair_ctx* ctx, const void* p, size_t bytes) {
+    hipPointerAttribute_t at;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    const bool ok = hipPointerGetAttributes(&at, p) == hipSuccess && at.type == hipMemoryTypeDevice &&
+                    at.device == ctx->device &&
+                    hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) == hipSuccess;
+    if (!ok) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const size_t off = (size_t)(static_cast<const char*>(p) - static_cast<const char*>(base));
+    return off <= size && bytes <= size - off;
+}
+
 int validate_material(const hair_material* m) {
     if (!m) return fail(HAIR_EINVAL, "null material");
     if (m->model == HAIR_MODEL_RTTD) {
@@ -1297,13 +1315,9 @@ int hair_set_cluster_params(hair_ctx* ctx, int32_t asset, int32_t level, const f
     hipStream_t st = (hipStream_t)stream;
     const Arrays3 copy{{L.axes.as<float>(), L.r.as<float>(), L.sig.as<float>()}, {axes, r, sigma_a},
                        {axes ? 2ull * L.K * L.S : 0, r ? (size_t)L.K : 0, sigma_a ? 3ull * L.K : 0}};
-    bool ours = true;   // arrays of this device; others (a peer's, the host's) are left to the runtime
-    for (const float* p : copy.src) {
-        hipPointerAttribute_t at;
-        if (!p || !ours) continue;
-        ours = hipPointerGetAttributes(&at, p) == hipSuccess && at.type == hipMemoryTypeDevice && at.device == ctx->device;
-        if (!ours) (void)hipGetLastError();
-    }
+    bool ours = true;   // one kernel copies arrays that lie whole in this device's memory
+    for (int k = 0; k < 3; ++k)
+        if (copy.src[k] && ours) ours = device_holds(ctx, copy.src[k], 4 * copy.n[k]);
     if (ours) {
         HIP_TRY(ctx, launch_set3(copy, st), "set_cluster_params");
         return HAIR_OK;
