@@ -137,14 +137,16 @@ int hair_ws_destroy(hair_ws* ws);
 /* Bytes the workspace holds on the device now and its limit (0 = none). */
 int hair_ws_memory(hair_ws* ws, uint64_t* held_bytes, uint64_t* max_bytes);
 /* Change the workspace's limit (0 = none) for its later calls; buffers it already holds are
- * kept, so held bytes may exceed a lowered limit until hair_ws_trim.  A call that would grow
- * the workspace beyond the limit fails with HAIR_ENOMEM. */
+ * kept, so held bytes may exceed a lowered limit until hair_ws_trim.  A frame that would grow
+ * the workspace beyond the limit starts over without the buffers that are there for speed alone,
+ * and fails with HAIR_ENOMEM where that does not suffice. */
 int hair_ws_set_limit(hair_ws* ws, uint64_t max_bytes);
 /* Free every buffer the workspace holds (its next frame sizes them afresh, as a first frame
  * does).  HAIR_EINVAL while it holds a frame of hair_render_async. */
 int hair_ws_trim(hair_ws* ws);
 /* Bytes a render of n_segments at width x height needs in a workspace (upper bound used
- * for admission control); pairs_estimate = expected (tile, segment) pairs (0 = 4 per segment). */
+ * for admission control); pairs_estimate = expected (tile, segment) pairs (0 = 4 per segment).
+ * Shadow maps are not in it (32 bytes per texel and directional light). */
 uint64_t hair_ws_estimate(int64_t n_segments, int32_t width, int32_t height, int64_t pairs_estimate);
 
 /* Upload a strand asset (Sec. 5.1 input: strand polylines, per-strand width and absorption).

@@ -111,13 +111,15 @@ struct hair_ws {
     uint64_t held = 0;
     DevBuf seg, shade, scan_tmp, tile_cnt, tile_start, bin_m, bin_blk, list, ctr, sel_cnt, sel_start, sel, sel_tmp;
     DevBuf pieces;                            // rows of a frame drawn with long segments as pieces
-    DevBuf items, item_start, item_tab, item_base, pix_cnt, pix_kmin, pix_kmax, pix_off, pix_thick, thick_list;
+    DevBuf items, item_start, item_tab, item_base, pix_kmin, pix_off, pix_thick, thick_list;
+    DevBuf pix_pair;                          // counts, then key maxima, of the pixels
     DevBuf tile_tot, frag_base, tile_nb, batch_mask, batch_start, batches, frags;
     DevBuf dom_tex, dom_grid, dom_part;      // shadow pass: texels, grids, bounds partials,
-    DevBuf dom_acc;                          // layer sums [tile][layer][texel]
+    DevBuf dom_acc;                          // layer sums [tile][layer][texel] (not when lean)
     int32_t dom_R = 0, dom_K = 0, dom_n = 0;  // last shadowed render: resolution, layers, maps
     int32_t dom_light[HAIR_MAX_LIGHTS] = {};  // map index of each light, -1 if unshadowed
     FrameCaps caps = {};                      // buffer capacities of warm frames (0: none yet)
+    bool lean = false;                        // memory ran out: no buffer that only speed asks for (ws_lean)
     hipEvent_t ev[7] = {};
     bool events = false;
     int64_t last_nseg = 0, last_ntiles = 0, last_pairs = 0;
@@ -195,10 +197,10 @@ void ctx_free(hair_ctx* ctx, DevBuf& b, hair_ws* ws = nullptr) {
 }
 
 // Every device buffer a workspace can hold.
-std::array<DevBuf*, 35> ws_buffers(hair_ws* ws) {
+std::array<DevBuf*, 34> ws_buffers(hair_ws* ws) {
     return {{&ws->seg, &ws->shade, &ws->scan_tmp, &ws->tile_cnt, &ws->tile_start, &ws->bin_m, &ws->bin_blk,
             &ws->sel_cnt, &ws->sel_start, &ws->sel, &ws->sel_tmp, &ws->list, &ws->ctr, &ws->items,
-            &ws->item_start, &ws->item_tab, &ws->item_base, &ws->pix_cnt, &ws->pix_kmin, &ws->pix_kmax, &ws->pix_off, &ws->pix_thick, &ws->thick_list,
+            &ws->item_start, &ws->item_tab, &ws->item_base, &ws->pix_pair, &ws->pix_kmin, &ws->pix_off, &ws->pix_thick, &ws->thick_list,
             &ws->tile_tot, &ws->frag_base, &ws->tile_nb, &ws->batch_mask, &ws->batch_start, &ws->batches,
             &ws->frags, &ws->dom_tex, &ws->dom_grid, &ws->dom_part, &ws->dom_acc, &ws->pieces}};
 }
@@ -217,12 +219,29 @@ int arena_take(hair_ws* ws, DevBuf& b, size_t bytes) {
     return HAIR_OK;
 }
 
-// Grow-only workspace buffer (25% headroom).
+// Grow-only workspace buffer (25% headroom).  Inside a frame (run_frame's passes), which starts over
+// when memory runs out; between frames ws_need_lean.
 int ws_need(hair_ws* ws, DevBuf& b, size_t bytes) {
     if (ws->arena) return arena_take(ws, b, bytes);
     if (b.bytes >= bytes && b.p) return HAIR_OK;
     ctx_free(ws->ctx, b, ws);
     return ctx_alloc(ws->ctx, b, bytes + bytes / 4 + 256, ws);
+}
+
+// Memory ran out (a workspace's limit, the context's budget or the device): give back the buffers
+// that are there for speed or larger than they have to be, and do without until the limit is set
+// anew or the workspace is trimmed.  Lean frames give the same results.  (hipFree waits for the
+// kernels of a frame that is given up.)
+void ws_lean(hair_ws* ws) {
+    ws->lean = true;
+    if (!ws->arena) ctx_free(ws->ctx, ws->dom_acc, ws);
+}
+
+int ws_need_lean(hair_ws* ws, DevBuf& b, size_t bytes) {
+    int rc = ws_need(ws, b, bytes);
+    if (rc != HAIR_ENOMEM || ws->lean || ws->arena) return rc;
+    ws_lean(ws);
+    return ws_need(ws, b, bytes);
 }
 
 void free_level(hair_ctx* ctx, Level& l) {
@@ -542,11 +561,10 @@ struct DomPass {
 // is rendered again cold.  The frame ends with one synchronisation for the counters.
 static uint32_t with_headroom(uint32_t n) { return n + n / 4 + 256; }
 
-int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, const hair_camera* cam,
-              const hair_light* lights, int n_lights, float* rgba, const DebugDump* dbg, hipStream_t st,
-              FrameOut* out, bool tiles_too = true, const GradOut* grad = nullptr, const HierDev* hier = nullptr,
-              const uint32_t* sel = nullptr, const DomPass* dom = nullptr, const DomView* views = nullptr,
-              const TessPass* tess = nullptr, bool cold = false, bool defer = false) {
+int frame_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, const hair_camera* cam,
+                 const hair_light* lights, int n_lights, float* rgba, const DebugDump* dbg, hipStream_t st,
+                 FrameOut* out, bool tiles_too, const GradOut* grad, const HierDev* hier, const uint32_t* sel,
+                 const DomPass* dom, const DomView* views, const TessPass* tess, bool cold, bool defer) {
     int rc;
     if (ws->pending.active)
         return fail(HAIR_EINVAL, "the workspace holds a frame of hair_render_async: call hair_ws_finish first");
@@ -637,13 +655,16 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     }
     if ((rc = ws_need(ws, ws->list, 4ull * caps.pairs))) return rc;
     if ((rc = ws_need(ws, ws->item_tab, 8ull * caps.items)) || (rc = ws_need(ws, ws->pix_kmin, 4 * TP))) return rc;
-    const size_t n_acc = dom ? (size_t)dom->K * TP : 0;
+    // a shadow map's layer sums: all layers at once in a buffer of their own, or (lean) one layer
+    // after the other where the camera's frame keeps its pixels' counts and key maxima
+    const int dom_nl = dom ? (ws->lean ? 1 : dom->K) : 0;
+    DevBuf& acc = ws->lean ? ws->pix_pair : ws->dom_acc;
+    const size_t n_acc = (size_t)dom_nl * TP;
     if (dom) {
-        if ((rc = ws_need(ws, ws->dom_acc, 8 * n_acc))) return rc;
+        if ((rc = ws_need(ws, acc, 8 * n_acc))) return rc;
     } else {
         if ((rc = ws_need(ws, ws->item_base, 4ull * kTilePix * caps.items))) return rc;
-        for (DevBuf* b : {&ws->pix_cnt, &ws->pix_kmax, &ws->pix_off})
-            if ((rc = ws_need(ws, *b, 4 * TP))) return rc;
+        if ((rc = ws_need(ws, ws->pix_pair, 8 * TP)) || (rc = ws_need(ws, ws->pix_off, 4 * TP))) return rc;
         if (lv.kind == 2 && (rc = ws_need(ws, ws->pix_thick, TP))) return rc;
         for (DevBuf* b : {&ws->tile_tot, &ws->tile_nb})
             if ((rc = ws_need(ws, *b, 4ull * T))) return rc;
@@ -664,9 +685,9 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     f.pix_kmin = ws->pix_kmin.as<uint32_t>();
     if (!dom) {
         f.item_base = ws->item_base.as<uint32_t>();
-        f.pix_cnt = ws->pix_cnt.as<uint32_t>();
+        f.pix_cnt = ws->pix_pair.as<uint32_t>();
         f.pix_off = ws->pix_off.as<uint32_t>();
-        f.pix_kmax = ws->pix_kmax.as<uint32_t>();
+        f.pix_kmax = f.pix_cnt + TP;
         f.pix_thick = lv.kind == 2 ? ws->pix_thick.as<uint8_t>() : nullptr;
     }
     // (shadow maps and debug dumps need every fragment)
@@ -686,7 +707,7 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     // (a static-scratch frame clears the image only once every buffer has been carved, so that
     // a frame too large for the scratch fails with the caller's image untouched)
     HIP_TRY(ctx, launch_scatter(f, lv.nseg, cc, plan, ws->bin_m.as<uint32_t>(), ws->list.as<uint32_t>(),
-                                ws->arena ? nullptr : rgba, dom ? ws->dom_acc.as<unsigned long long>() : nullptr, n_acc,
+                                ws->arena ? nullptr : rgba, dom ? acc.as<unsigned long long>() : nullptr, n_acc,
                                 ws->item_tab.as<uint2>(), caps.items, st),
             "k_scatter");
     const uint32_t item_grid = warm ? caps.items : n_items;
@@ -746,8 +767,8 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     if (views)
         for (int i = 0; i < n_lights; ++i) lc.dom[i] = views[i];
     if (dom) {
-        HIP_TRY(ctx, launch_dom_map(f, cc, lv, dom->rows, dom->grid, dom->K, dom->delta, rcp_of(dom->delta), item_grid,
-                                    ws->dom_acc.as<unsigned long long>(), dom->tex, st),
+        HIP_TRY(ctx, launch_dom_map(f, cc, lv, dom->rows, dom->grid, dom->K, dom_nl, dom->delta, rcp_of(dom->delta),
+                                    item_grid, acc.as<unsigned long long>(), dom->tex, st),
                 "k_dom_first");
     } else if (grad) {
         const Arrays3 zero{{grad->d_axes, grad->d_r, grad->d_sig}, {},
@@ -769,8 +790,8 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     out->ctr = *ws->ctr_host;
     if (out->ctr.cap_overflow) {
         if (!warm) return fail(HAIR_EDEVICE, "frame sizes exceeded the capacities read for them");
-        return run_frame(ctx, ws, a, lv, cam, lights, n_lights, rgba, dbg, st, out, tiles_too, grad, hier, sel, dom, views,
-                         tess, true);
+        return frame_passes(ctx, ws, a, lv, cam, lights, n_lights, rgba, dbg, st, out, tiles_too, grad, hier, sel, dom,
+                            views, tess, true, false);
     }
     ws->caps = caps;
     if ((rc = frame_result(ctx, ws, lv.nseg, T, out))) return rc;
@@ -784,6 +805,22 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
     return HAIR_OK;
 }
 
+// A frame; one that runs out of memory starts over on a lean workspace.
+int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, const hair_camera* cam,
+              const hair_light* lights, int n_lights, float* rgba, const DebugDump* dbg, hipStream_t st,
+              FrameOut* out, bool tiles_too = true, const GradOut* grad = nullptr, const HierDev* hier = nullptr,
+              const uint32_t* sel = nullptr, const DomPass* dom = nullptr, const DomView* views = nullptr,
+              const TessPass* tess = nullptr, bool cold = false, bool defer = false) {
+    auto passes = [&] {
+        return frame_passes(ctx, ws, a, lv, cam, lights, n_lights, rgba, dbg, st, out, tiles_too, grad, hier, sel, dom,
+                            views, tess, cold, defer);
+    };
+    int rc = passes();
+    if (rc != HAIR_ENOMEM || ws->lean || ws->arena) return rc;
+    ws_lean(ws);
+    return passes();
+}
+
 // Rows of a frame that draws the long segments of a level (or of a mixed frame's rows, hier
 // and sel given) as pieces, in ws->pieces with counts in ws->sel_cnt, and the pass and level
 // that render them.  Synchronises st once (the row count).
@@ -791,8 +828,8 @@ int split_rows(hair_ctx* ctx, hair_ws* ws, const LevelDev& lv, const hair_camera
                LevelDev* lv_out, const HierDev* hier = nullptr, const uint32_t* sel = nullptr) {
     int rc;
     const int n = lv.nseg;
-    if ((rc = ws_need(ws, ws->sel_cnt, 4ull * (n + 1))) || (rc = ws_need(ws, ws->sel_start, 4ull * (n + 1))) ||
-        (rc = ws_need(ws, ws->sel_tmp, 4 * exscan_scratch_words(n))))
+    if ((rc = ws_need_lean(ws, ws->sel_cnt, 4ull * (n + 1))) || (rc = ws_need_lean(ws, ws->sel_start, 4ull * (n + 1))) ||
+        (rc = ws_need_lean(ws, ws->sel_tmp, 4 * exscan_scratch_words(n))))
         return rc;
     uint32_t* cnt = ws->sel_cnt.as<uint32_t>();
     uint32_t* start = ws->sel_start.as<uint32_t>();
@@ -804,7 +841,7 @@ int split_rows(hair_ctx* ctx, hair_ws* ws, const LevelDev& lv, const hair_camera
     uint32_t nrows = 0;
     if ((rc = read_words(ctx, ws, start + n, 1, st, &nrows))) return rc;
     if (nrows >= (1u << 26)) return fail(HAIR_ERANGE, "%u pieces: the frame has 2^26 rows or more", nrows);
-    if ((rc = ws_need(ws, ws->pieces, 4ull * std::max<uint32_t>(nrows, 1)))) return rc;
+    if ((rc = ws_need_lean(ws, ws->pieces, 4ull * std::max<uint32_t>(nrows, 1)))) return rc;
     HIP_TRY(ctx, launch_split_fill(cnt, start, n, ws->pieces.as<uint32_t>(), st), "k_split_fill");
     tp->base = lv;
     tp->rows = ws->pieces.as<uint32_t>();
@@ -958,6 +995,7 @@ int hair_ws_set_limit(hair_ws* ws, uint64_t max_bytes) {
     if (!ws) return fail(HAIR_EINVAL, "null workspace");
     std::lock_guard<std::mutex> g(ws->mu);
     ws->max_bytes = max_bytes;
+    ws->lean = false;
     return HAIR_OK;
 }
 
@@ -972,6 +1010,7 @@ int hair_ws_trim(hair_ws* ws) {
     for (DevBuf* b : ws_buffers(ws)) ctx_free(ctx, *b, ws);
     ws->caps = FrameCaps{};
     ws->dom_n = 0;
+    ws->lean = false;
     return HAIR_OK;
 }
 
@@ -1572,9 +1611,9 @@ static int shadow_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const Level
     int n_dom = 0;
     for (int i = 0; i < n_lights; ++i) n_dom += lights[i].kind == 0;
     const size_t texels = (size_t)R * R;
-    if ((rc = ws_need(ws, ws->dom_tex, 32 * texels * std::max(n_dom, 1)))) return rc;
-    if ((rc = ws_need(ws, ws->dom_grid, sizeof(DomGrid) * HAIR_MAX_LIGHTS))) return rc;
-    if ((rc = ws_need(ws, ws->dom_part, 20ull * dom_bound_blocks(lv.nseg)))) return rc;
+    if ((rc = ws_need_lean(ws, ws->dom_tex, 32 * texels * std::max(n_dom, 1)))) return rc;
+    if ((rc = ws_need_lean(ws, ws->dom_grid, sizeof(DomGrid) * HAIR_MAX_LIGHTS))) return rc;
+    if ((rc = ws_need_lean(ws, ws->dom_part, 20ull * dom_bound_blocks(lv.nseg)))) return rc;
     hair_camera lcam = *cam;   // the light view's raster size; its projection is the light's own
     lcam.width = lcam.height = R;
     memset(views, 0, sizeof(DomView) * HAIR_MAX_LIGHTS);
@@ -1734,8 +1773,8 @@ static int render_mixed(hair_ctx* ctx, hair_ws* ws, int32_t asset, const hair_ca
     std::lock_guard<std::mutex> g(ws->mu);
     hipStream_t st = (hipStream_t)stream;
     const int GS = h.G * h.S;
-    if ((rc = ws_need(ws, ws->sel_cnt, 4ull * (GS + 1))) || (rc = ws_need(ws, ws->sel_start, 4ull * (GS + 2))) ||
-        (rc = ws_need(ws, ws->sel_tmp, 4 * exscan_scratch_words(GS))))
+    if ((rc = ws_need_lean(ws, ws->sel_cnt, 4ull * (GS + 1))) || (rc = ws_need_lean(ws, ws->sel_start, 4ull * (GS + 2))) ||
+        (rc = ws_need_lean(ws, ws->sel_tmp, 4 * exscan_scratch_words(GS))))
         return rc;
     HIP_TRY(ctx, launch_select(h, levels, ws->sel_cnt.as<uint32_t>(), ws->sel_start.as<uint32_t>(), ws->sel_tmp.as<uint32_t>(), st),
             "k_sel_count");
@@ -1743,7 +1782,7 @@ static int render_mixed(hair_ctx* ctx, hair_ws* ws, int32_t asset, const hair_ca
     if ((rc = read_words(ctx, ws, ws->sel_start.as<uint32_t>() + GS, 2, st, sizes))) return rc;
     const uint32_t nsel = sizes[0], bad = sizes[1];
     if (bad) return fail(HAIR_EINVAL, "%u entries of levels lie outside [0, %d]", bad, h.n_levels);
-    if ((rc = ws_need(ws, ws->sel, 4ull * std::max<uint32_t>(nsel, 1)))) return rc;
+    if ((rc = ws_need_lean(ws, ws->sel, 4ull * std::max<uint32_t>(nsel, 1)))) return rc;
     HIP_TRY(ctx, launch_select_fill(h, levels, ws->sel_start.as<uint32_t>(), ws->sel.as<uint32_t>(), st), "k_sel_fill");
     LevelDev lv;
     memset(&lv, 0, sizeof(lv));
@@ -1755,8 +1794,8 @@ static int render_mixed(hair_ctx* ctx, hair_ws* ws, int32_t asset, const hair_ca
     if (shadow) {
         // the rows' shading records (world endpoints and cross-sections) feed the shadow passes;
         // the camera frame projects them again into the same buffers
-        if ((rc = ws_need(ws, ws->seg, sizeof(SegRec) * (size_t)std::max<uint32_t>(nsel, 1))) ||
-            (rc = ws_need(ws, ws->shade, sizeof(ShadeRec) * (size_t)std::max<uint32_t>(nsel, 1))))
+        if ((rc = ws_need_lean(ws, ws->seg, sizeof(SegRec) * (size_t)std::max<uint32_t>(nsel, 1))) ||
+            (rc = ws_need_lean(ws, ws->shade, sizeof(ShadeRec) * (size_t)std::max<uint32_t>(nsel, 1))))
             return rc;
         HIP_TRY(ctx, launch_project_mixed(h, ws->sel.as<uint32_t>(), (int32_t)nsel, cam_const(cam),
                                           ws->seg.as<SegRec>(), ws->shade.as<ShadeRec>(), st),
@@ -1818,8 +1857,8 @@ int hair_render_curved(hair_ctx* ctx, hair_ws* ws, int32_t asset, int32_t level,
     std::lock_guard<std::mutex> g(ws->mu);
     const hipStream_t st = (hipStream_t)stream;
     const int n = base.nseg;
-    if ((rc = ws_need(ws, ws->sel_cnt, 4ull * (n + 1))) || (rc = ws_need(ws, ws->sel_start, 4ull * (n + 1))) ||
-        (rc = ws_need(ws, ws->sel_tmp, 4 * exscan_scratch_words(n))))
+    if ((rc = ws_need_lean(ws, ws->sel_cnt, 4ull * (n + 1))) || (rc = ws_need_lean(ws, ws->sel_start, 4ull * (n + 1))) ||
+        (rc = ws_need_lean(ws, ws->sel_tmp, 4 * exscan_scratch_words(n))))
         return rc;
     uint32_t* cnt = ws->sel_cnt.as<uint32_t>();
     uint32_t* start = ws->sel_start.as<uint32_t>();
@@ -1827,7 +1866,7 @@ int hair_render_curved(hair_ctx* ctx, hair_ws* ws, int32_t asset, int32_t level,
             "k_tess_count");
     uint32_t nrows = 0;
     if ((rc = read_words(ctx, ws, start + n, 1, st, &nrows))) return rc;
-    if ((rc = ws_need(ws, ws->sel, 4ull * std::max<uint32_t>(nrows, 1)))) return rc;
+    if ((rc = ws_need_lean(ws, ws->sel, 4ull * std::max<uint32_t>(nrows, 1)))) return rc;
     HIP_TRY(ctx, launch_tess_fill(cnt, start, n, ws->sel.as<uint32_t>(), st), "k_tess_fill");
     LevelDev lv = base;
     lv.nseg = (int32_t)nrows;

@@ -316,8 +316,9 @@ hipError_t launch_dom_grid(const LevelDev& lv, const ShadeRec* rows, const DomBa
                            hipStream_t st);
 hipError_t launch_project_light(const LevelDev& lv, const ShadeRec* rows, const DomGrid* grid, SegRec* seg,
                                 hipStream_t st);
+// The light view's texels.  nl: the layers that acc has room for, K (one pass) or 1 (K passes).
 hipError_t launch_dom_map(const FrameBufs& f, const CamConst& cam, const LevelDev& lv, const ShadeRec* rows,
-                          const DomGrid* grid, int32_t K, float delta, float rdelta, uint32_t n_items,
+                          const DomGrid* grid, int32_t K, int32_t nl, float delta, float rdelta, uint32_t n_items,
                           unsigned long long* acc, float4* tex, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t st);
 struct Arrays3 {

@@ -3583,12 +3583,13 @@ __global__ __launch_bounds__(kNT) void k_dom_first(FrameBufs f, CamConst cam, in
     if (s_z[t] < z0) atomicMin(&f.pix_kmin[q], s_z[t]);
 }
 
-// THICK: the level can hold thick hairs.  Dynamic LDS: K x kTilePix sums.
+// THICK: the level can hold thick hairs.  The launch adds the layers [l0, l0 + nl) of K, with acc as
+// [tile][nl][texel] (see launch_dom_map).  Dynamic LDS: nl x kTilePix sums.
 template <bool THICK>
 __global__ __launch_bounds__(kNT) void k_dom_layers(FrameBufs f, CamConst cam, LevelDev lv,
                                                     const ShadeRec* __restrict__ rows,
-                                                    const DomGrid* __restrict__ grid, int K, float delta, float rdelta,
-                                                    unsigned long long* __restrict__ acc, int group) {
+                                                    const DomGrid* __restrict__ grid, int K, int l0, int nl, float delta,
+                                                    float rdelta, unsigned long long* __restrict__ acc, int group) {
     extern __shared__ unsigned long long s_acc[];
     __shared__ float s_iz0[kTilePix];
     __shared__ float4 s_seg[kNT];                  // (iza, izb, hw, sqrt(t_den))
@@ -3604,7 +3605,7 @@ __global__ __launch_bounds__(kNT) void k_dom_layers(FrameBufs f, CamConst cam, L
     const int px0 = (tile % f.ntx) * kTile, py0 = (tile / f.ntx) * kTile;
     const uint32_t lstart = f.tile_start[tile], n = f.tile_start[tile + 1] - lstart;
     s_iz0[t] = iz_of_key(f.pix_kmin[(size_t)tile * kTilePix + t]);
-    for (int k = 0; k < K; ++k) s_acc[k * kTilePix + t] = 0ull;
+    for (int k = 0; k < nl; ++k) s_acc[k * kTilePix + t] = 0ull;
     for (uint32_t k = it.y; k < it.y + (uint32_t)group && k * kNT < n; ++k) {
         const uint32_t j = k * kNT + t;
         SegRec s{};
@@ -3636,7 +3637,8 @@ __global__ __launch_bounds__(kNT) void k_dom_layers(FrameBufs f, CamConst cam, L
             // (rounded like the keys of k_dom_first, so that the first hit itself lies in layer 0)
             const float tt = div_rcp((float)tnum, (float)tden, rc.y);
             const float iz = e.x + tt * (e.y - e.x);
-            const int layer = min(K - 1, (int)floorf(div_by(s_iz0[p] - iz, delta, rdelta)));
+            const int layer = min(K - 1, (int)floorf(div_by(s_iz0[p] - iz, delta, rdelta))) - l0;
+            if ((unsigned)layer >= (unsigned)nl) return;
             const float dl = div_rcp(fabsf((float)cr), e.w, rc.x) * (1.0f / 16.0f);
             const float hw = e.z;
             float c = fminf(fmaxf(fminf(dl + hw, 0.5f) - fmaxf(dl - hw, -0.5f), 0.0f), 1.0f);
@@ -3660,14 +3662,15 @@ __global__ __launch_bounds__(kNT) void k_dom_layers(FrameBufs f, CamConst cam, L
         });
         __syncthreads();
     }
-    for (int k = 0; k < K; ++k) {
+    for (int k = 0; k < nl; ++k) {
         const unsigned long long v = s_acc[k * kTilePix + t];
-        if (v) atomicAdd(&acc[((size_t)tile * K + k) * kTilePix + t], v);
+        if (v) atomicAdd(&acc[((size_t)tile * nl + k) * kTilePix + t], v);
     }
 }
 
-__global__ __launch_bounds__(kNT) void k_dom_texels(FrameBufs f, int R, int K, const unsigned long long* __restrict__ acc,
-                                                    float4* __restrict__ tex) {
+// (nl == K: whole texels; nl == 1: acc holds the sum of the layers 0 .. l0)
+__global__ __launch_bounds__(kNT) void k_dom_texels(FrameBufs f, int R, int K, int l0, int nl,
+                                                    const unsigned long long* __restrict__ acc, float4* __restrict__ tex) {
     if (f.ctr->cap_overflow) return;
     const int tile = blockIdx.x, t = threadIdx.x;
     const int px = (tile % f.ntx) * kTile + t % kTile, py = (tile / f.ntx) * kTile + t / kTile;
@@ -3678,12 +3681,18 @@ __global__ __launch_bounds__(kNT) void k_dom_texels(FrameBufs f, int R, int K, c
         unsigned long long run = 0;
 #pragma unroll
         for (int k = 0; k < kDomMaxLayers; ++k) {
-            if (k < K) run += acc[((size_t)tile * K + k) * kTilePix + t];
+            if (k < nl) run += acc[((size_t)tile * nl + k) * kTilePix + t];
             C[k] = (float)((double)run * (1.0 / 4294967296.0));
         }
     }
     if (px >= R || py >= R) return;
     const size_t o = 2 * ((size_t)py * R + px);
+    if (nl < K) {
+        float* texel = reinterpret_cast<float*>(tex + o);
+        if (l0 == 0) texel[0] = iz0;
+        for (int k = l0; k < (l0 + 1 < K ? l0 + 1 : kDomMaxLayers); ++k) texel[1 + k] = C[0];
+        return;
+    }
     tex[o] = make_float4(iz0, C[0], C[1], C[2]);
     tex[o + 1] = make_float4(C[3], C[4], C[5], C[6]);
 }
@@ -3783,23 +3792,20 @@ hipError_t launch_project_light(const LevelDev& lv, const ShadeRec* rows, const 
 }
 
 hipError_t launch_dom_map(const FrameBufs& f, const CamConst& cam, const LevelDev& lv, const ShadeRec* rows,
-                          const DomGrid* grid, int32_t K, float delta, float rdelta, uint32_t n_items,
+                          const DomGrid* grid, int32_t K, int32_t nl, float delta, float rdelta, uint32_t n_items,
                           unsigned long long* acc, float4* tex, hipStream_t st) {
     // a block takes four chunks of a tile's list, which saves three of four rounds of global atomics,
     // where that leaves the chip's 2048 block slots filled
     const int group = n_items >= 8192 ? 4 : 1;
-    const bool thick = rows || lv.kind != 0;
-    const int lds = 8 * kTilePix * K;
-    if (n_items) {
-        hipLaunchKernelGGL(k_dom_first, dim3(n_items), dim3(kNT), 0, st, f, cam, group);
-        if (thick)
-            hipLaunchKernelGGL(k_dom_layers<true>, dim3(n_items), dim3(kNT), lds, st, f, cam, lv, rows, grid, K, delta,
-                               rdelta, acc, group);
-        else
-            hipLaunchKernelGGL(k_dom_layers<false>, dim3(n_items), dim3(kNT), lds, st, f, cam, lv, rows, grid, K, delta,
-                               rdelta, acc, group);
+    auto layers = rows || lv.kind != 0 ? &k_dom_layers<true> : &k_dom_layers<false>;
+    if (n_items) hipLaunchKernelGGL(k_dom_first, dim3(n_items), dim3(kNT), 0, st, f, cam, group);
+    // all layers in one pass, or one after the other into the same sums (which then run on)
+    for (int l0 = 0; l0 < K; l0 += nl) {
+        if (n_items)
+            hipLaunchKernelGGL(layers, dim3(n_items), dim3(kNT), 8 * kTilePix * nl, st, f, cam, lv, rows, grid, K, l0, nl,
+                               delta, rdelta, acc, group);
+        hipLaunchKernelGGL(k_dom_texels, dim3(f.T), dim3(kNT), 0, st, f, cam.W, K, l0, nl, acc, tex);
     }
-    hipLaunchKernelGGL(k_dom_texels, dim3(f.T), dim3(kNT), 0, st, f, cam.W, K, acc, tex);
     return hipGetLastError();
 }
 
