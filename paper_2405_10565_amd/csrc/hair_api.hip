@@ -119,7 +119,7 @@ struct hair_ws {
     int32_t dom_R = 0, dom_K = 0, dom_n = 0;  // last shadowed render: resolution, layers, maps
     int32_t dom_light[HAIR_MAX_LIGHTS] = {};  // map index of each light, -1 if unshadowed
     FrameCaps caps = {};                      // buffer capacities of warm frames (0: none yet)
-    bool lean = false;                        // memory ran out: no buffer that only speed asks for (ws_lean)
+    bool lean = false;                        // memory ran out: buffers no larger than they have to be (ws_lean)
     hipEvent_t ev[7] = {};
     bool events = false;
     int64_t last_nseg = 0, last_ntiles = 0, last_pairs = 0;
@@ -219,27 +219,38 @@ int arena_take(hair_ws* ws, DevBuf& b, size_t bytes) {
     return HAIR_OK;
 }
 
-// Grow-only workspace buffer (25% headroom).  Inside a frame (run_frame's passes), which starts over
-// when memory runs out; between frames ws_need_lean.
+// Grow-only workspace buffer (25% headroom; none when lean).  Inside a frame (run_frame's passes),
+// which starts over when memory runs out; between frames ws_need_lean.
 int ws_need(hair_ws* ws, DevBuf& b, size_t bytes) {
     if (ws->arena) return arena_take(ws, b, bytes);
     if (b.bytes >= bytes && b.p) return HAIR_OK;
     ctx_free(ws->ctx, b, ws);
-    return ctx_alloc(ws->ctx, b, bytes + bytes / 4 + 256, ws);
+    return ctx_alloc(ws->ctx, b, ws->lean ? bytes : bytes + bytes / 4 + 256, ws);
 }
 
-// Memory ran out (a workspace's limit, the context's budget or the device): give back the buffers
-// that are there for speed or larger than they have to be, and do without until the limit is set
-// anew or the workspace is trimmed.  Lean frames give the same results.  (hipFree waits for the
-// kernels of a frame that is given up.)
+// Memory ran out (a workspace's limit, the context's budget or the device): give back the frame's
+// buffers, and until the limit is set anew or the workspace is trimmed make them no larger than
+// they have to be.  What a frame holds for speed alone is less than the headroom left out (small
+// batches add up to 16 bytes of table per 128 fragments of 8 bytes each) or is left out too (the
+// layer sums of a shadow map).  Lean frames give the same results, bit for bit.  (Rows, segment
+// records and shadow maps stay: they may be a frame's inputs.  hipFree waits for the kernels of a
+// frame that is given up.)
 void ws_lean(hair_ws* ws) {
     ws->lean = true;
-    if (!ws->arena) ctx_free(ws->ctx, ws->dom_acc, ws);
+    if (ws->arena) return;
+    ws->caps = FrameCaps{};
+    for (DevBuf* b : ws_buffers(ws)) {
+        bool keep = false;
+        for (const DevBuf* k : {&ws->seg, &ws->shade, &ws->sel_cnt, &ws->sel_start, &ws->sel, &ws->sel_tmp, &ws->pieces,
+                                &ws->dom_tex, &ws->dom_grid, &ws->dom_part})
+            keep = keep || b == k;
+        if (!keep) ctx_free(ws->ctx, *b, ws);
+    }
 }
 
 int ws_need_lean(hair_ws* ws, DevBuf& b, size_t bytes) {
     int rc = ws_need(ws, b, bytes);
-    if (rc != HAIR_ENOMEM || ws->lean || ws->arena) return rc;
+    if (rc != HAIR_ENOMEM || ws->lean || ws->pending.active) return rc;
     ws_lean(ws);
     return ws_need(ws, b, bytes);
 }
@@ -691,6 +702,7 @@ int frame_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv,
         f.pix_thick = lv.kind == 2 ? ws->pix_thick.as<uint8_t>() : nullptr;
     }
     // (shadow maps and debug dumps need every fragment)
+    f.full_batches = ws->arena && ws->lean;
     f.trim = !dom && !dbg && lv.nseg >= kTrimRows;
     // (strand levels have opaque fragments only where a strand is wider than a pixel: no pass for them)
     f.opaque = !dom && !dbg && lv.kind != 0;
@@ -749,6 +761,8 @@ int frame_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv,
             caps.batches = std::max(caps.batches, cap_of(n_batches));
         }
         if ((rc = ws_need(ws, ws->frags, 8ull * caps.frags))) return rc;
+        // (the static scratch's binning matrix has served its purpose, and holds most frames' batches)
+        if (ws->arena && ws->bin_m.bytes >= 16ull * caps.batches) ws->batches = ws->bin_m;
         if ((rc = ws_need(ws, ws->batches, 16ull * caps.batches))) return rc;
         if (lv.kind == 2 && (rc = ws_need(ws, ws->thick_list, 4ull * caps.batches))) return rc;
         f.frags = ws->frags.as<uint2>();
@@ -805,7 +819,10 @@ int frame_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv,
     return HAIR_OK;
 }
 
-// A frame; one that runs out of memory starts over on a lean workspace.
+// A frame; one that runs out of memory starts over on a lean workspace.  (The static scratch has no
+// headroom to leave out: where its binning matrix is too small for the batch table, as with a few
+// very wide segments, the frame that does not fit is packed into full batches, which may round a
+// pixel's composite differently.)
 int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, const hair_camera* cam,
               const hair_light* lights, int n_lights, float* rgba, const DebugDump* dbg, hipStream_t st,
               FrameOut* out, bool tiles_too = true, const GradOut* grad = nullptr, const HierDev* hier = nullptr,
@@ -816,9 +833,11 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
                             views, tess, cold, defer);
     };
     int rc = passes();
-    if (rc != HAIR_ENOMEM || ws->lean || ws->arena) return rc;
+    if (rc != HAIR_ENOMEM || ws->lean) return rc;
     ws_lean(ws);
-    return passes();
+    rc = passes();
+    if (ws->arena) ws->lean = false;   // (each frame of the static scratch is sized for itself)
+    return rc;
 }
 
 // Rows of a frame that draws the long segments of a level (or of a mixed frame's rows, hier

@@ -214,6 +214,7 @@ struct FrameBufs {
     int32_t gid;                  // fragment records hold the global segment id (frames of fewer than
                                   // 2^24 rows, forward passes) instead of the index in the tile's list
     int32_t trim;                 // fragments whose alpha is exactly 0 are not stored (kTrimRows)
+    int32_t full_batches;         // the static scratch has no room for a table of smaller ones (see batch_cap)
     int32_t opaque;               // the frame can hold thick hairs: it has an opaque pass (k_opaque)
 };
 // (offsets stay below it: at most 2^24 segments of a tile that are not opaque cover under 2^7

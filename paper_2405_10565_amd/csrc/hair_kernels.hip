@@ -1825,7 +1825,7 @@ __global__ __launch_bounds__(kNT) void k_tile_prep(FrameBufs f) {
         }
         s_nxt[t] = (uint16_t)lo;
     }
-    const uint32_t cap = batch_cap(total, f.ctr->sizes[0]);
+    const uint32_t cap = f.full_batches ? (uint32_t)kCap : batch_cap(total, f.ctr->sizes[0]);
     if (c > cap) {
         s_end[t] = (uint16_t)(t + 1);
     } else {   // the largest p1 with s_off[p1] - s_off[t] <= cap

@@ -1,10 +1,13 @@
 """Frames on workspaces that hold just what the frame cannot do without.  Some buffers are there
-for speed (a shadow map's layer sums of all layers at once); where they do not fit the
-workspace's limit, the frame starts over without them and gives the same result, bit for bit,
-as on a workspace without a limit.
+for speed (a shadow map's layer sums of all layers at once) or larger for it (the table of small
+batches); where they do not fit the workspace's limit or the context's budget, the frame starts
+over without headroom and without the layer sums, and gives the same result, bit for bit, as
+without a limit.  The static scratch keeps the batch table where the binning matrix was, and
+falls back to full batches where that is too small.
 
-The limits of the strand and mixed frames are what a workspace holds whose light views have the
-per-pixel tables of a camera frame and nothing more."""
+The limits of the shadowed strand and mixed frames are what a workspace holds whose light views
+have the per-pixel tables of a camera frame and nothing more, those of plain frames what it holds
+with full batches."""
 import numpy as np
 import pytest
 import torch
@@ -77,3 +80,86 @@ def test_shadowed_frames_within_a_limit(hip, scene, kind):
     assert e.value.code == hip.HAIR_ENOMEM
     for w in (free, ws, small):
         w.close()
+
+
+def _first(asset, n):
+    x = np.asarray(asset.xyz).reshape(3, asset.n_strands, asset.segs + 1)[:, :n]
+    return hs.Asset(n, asset.segs, np.ascontiguousarray(x.reshape(3, -1)), np.asarray(asset.width)[:n].copy(),
+                    np.ascontiguousarray(np.asarray(asset.sigma_a)[:, :n]))
+
+
+FULL_BATCHES = 67_072_229
+
+
+@pytest.mark.parametrize("what", ["workspace", "budget"])
+def test_plain_frames_within_a_limit(hip, what):
+    print(f"case: 20,000 strands at 400 x 400, limited {what}", flush=True)
+    asset = hs.make_asset(20000, 16, 90.0, seed=3)
+    cam, lights = hs.camera_for(asset, 400, 400), hs.default_lights(asset, with_point=True)
+    ctx = hip.Context(0)
+    aid = ctx.upload_asset(asset)
+    used = ctx.memory()[0]
+    free = ctx.workspace()
+    ref, st, _ = ctx.render(aid, 0, cam, lights, ws=free)
+    assert free.memory()[0] > FULL_BATCHES
+    if what == "budget":
+        tight = hip.Context(0, used + FULL_BATCHES)
+        aid2, ws = tight.upload_asset(asset), tight.workspace()
+    else:
+        tight, aid2, ws = ctx, aid, ctx.workspace(FULL_BATCHES)
+    for _ in range(3):
+        img, st2, _ = tight.render(aid2, 0, cam, lights, ws=ws)
+        assert _same(img, ref)
+        assert all(st2[k] == st[k] for k in ("batches", "fragments", "pairs", "deep_pixels"))
+        assert ws.memory()[0] <= FULL_BATCHES
+    # the deferred frame on the same workspace
+    out = torch.empty_like(ref)
+    tight.render_async(aid2, 0, cam, lights, out, ws)
+    ws.finish()
+    assert _same(out, ref)
+    ws.close()
+    free.close()
+    if tight is not ctx:
+        tight.close()
+    ctx.close()
+
+
+def test_static_scratch_keeps_the_batch_table_in_the_binning_matrix(hip):
+    """20,062 strands at 896 x 640 fill the scratch to within a few hundred bytes."""
+    asset = _first(hs.make_asset(21000, 16, 90.0, seed=3), 20062)
+    lights = hs.default_lights(asset, with_point=False)
+    cam = hs.camera_for(hs.make_asset(21000, 16, 90.0, seed=3), 896, 640)
+    ctx = hip.Context(0)
+    out = torch.empty((640, 896, 4), device="cuda:0")
+    aid = ctx.upload_asset(asset)
+    print("case: 20,062 strands at 896 x 640 in the static scratch", flush=True)
+    _, st, rc = ctx.render_noalloc(aid, 0, cam, lights, out, raise_on_error=False)
+    assert rc == hip.HAIR_OK
+    ref, st2, _ = ctx.render(aid, 0, cam, lights)
+    assert _same(out, ref) and st["batches"] == st2["batches"]
+    ctx.close()
+
+
+@pytest.mark.parametrize("n", [3900, 3970])
+def test_static_scratch_with_few_wide_segments(hip, n):
+    """One-segment strands some 40 px wide: 6.8 M fragments, a binning matrix of 74 KB, and small
+    batches whose table (34 k) does not fit beside 3,970 of them."""
+    whole = hs.make_asset(4000, 1, 90.0, seed=3)
+    asset = _first(whole, n)
+    asset.width[:] = 6e-2
+    lights = hs.default_lights(asset, with_point=False)
+    cam = hs.camera_for(whole, 900, 700)
+    ctx = hip.Context(0)
+    out = torch.empty((700, 900, 4), device="cuda:0")
+    aid = ctx.upload_asset(asset)
+    print(f"case: {n} wide segments in the static scratch", flush=True)
+    _, st, rc = ctx.render_noalloc(aid, 0, cam, lights, out, raise_on_error=False)
+    assert rc == hip.HAIR_OK
+    ref, st2, _ = ctx.render(aid, 0, cam, lights)
+    assert st["fragments"] == st2["fragments"]
+    if n == 3900:
+        assert _same(out, ref) and st["batches"] == st2["batches"]
+    else:
+        assert st["batches"] < st2["batches"]
+        assert torch.allclose(out, ref, rtol=1e-4, atol=1e-7)
+    ctx.close()
