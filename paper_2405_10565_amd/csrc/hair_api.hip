@@ -583,8 +583,8 @@ int frame_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv,
     const int ntx = (cam->width + kTile - 1) / kTile, nty = (cam->height + kTile - 1) / kTile;
     const int T = ntx * nty;
     const size_t TP = (size_t)T * kTilePix;
-    // (workspaces of a given size keep the smaller count matrix)
-    const BinPlan plan = bin_plan(lv.nseg, T, lv.kind == 1 && !ws->arena && ws->max_bytes == 0);
+    // (workspaces of a given size, or short of memory, keep the smaller count matrix)
+    const BinPlan plan = bin_plan(lv.nseg, T, lv.kind == 1 && !ws->arena && !ws->lean && ws->max_bytes == 0);
     if (ws->arena) {   // static scratch: every frame is sized afresh from its own counts
         for (DevBuf* b : ws_buffers(ws)) *b = DevBuf{};
         ws->arena_off = 0;

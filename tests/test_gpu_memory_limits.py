@@ -163,3 +163,25 @@ def test_static_scratch_with_few_wide_segments(hip, n):
         assert st["batches"] < st2["batches"]
         assert torch.allclose(out, ref, rtol=1e-4, atol=1e-7)
     ctx.close()
+
+
+def test_thick_hairs_within_a_budget(hip):
+    """2,000 x 16 narrow thick-hair segments at 1280 x 720: binned by eight lanes each where memory
+    allows (a count matrix of 9 MB), by one lane where it does not (2.3 MB)."""
+    asset = hs.make_asset(2000, 16, 90.0, seed=3)
+    cam, lights = hs.camera_for(asset, 1280, 720), hs.default_lights(asset, with_point=True)
+    held = []
+    for budget in (0, 30_087_522):
+        print(f"case: 2,000 thick hairs, budget {budget}", flush=True)
+        ctx = hip.Context(0, budget)
+        aid = ctx.upload_asset(asset)
+        ctx.build_lod(aid, [np.arange(2000).astype(np.int32)])
+        ws = ctx.workspace()
+        for _ in range(2):
+            img, st, _ = ctx.render(aid, 1, cam, lights, ws=ws)
+            if not budget:
+                ref = img
+            assert _same(img, ref)
+        held.append(ws.memory()[0])
+        ctx.close()
+    assert held[1] < held[0] - 4 * (500 - 62) * 80 * 45
