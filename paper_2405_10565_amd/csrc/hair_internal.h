@@ -194,10 +194,10 @@ struct FrameBufs {
     uint32_t* tile_all;           // [T] all fragments of the tile, stored or not
     uint32_t* pix_cnt;            // [T][kTilePix] stored fragments per pixel
     uint32_t* pix_kmin;           // [T][kTilePix] smallest depth key per pixel
-    uint32_t* pix_kmax;           // [T][kTilePix] largest depth key per pixel (until k_tile_prep, in frames
-                                  // with an opaque pass: the smallest key of an opaque fragment, ~0: none)
-    uint32_t* pix_off;            // [T][kTilePix] exclusive prefix of pix_cnt within the tile, with kHidesBit:
-                                  // an opaque fragment hides what lies behind pix_kmax (until
+    uint32_t* pix_kmax;           // [T][kTilePix] largest depth key per pixel, as kmax_seen states (until
+                                  // k_tile_prep, in frames with an opaque pass: the smallest key of an
+                                  // opaque fragment, ~0: none)
+    uint32_t* pix_off;            // [T][kTilePix] exclusive prefix of pix_cnt within the tile (until
                                   // k_tile_prep: the pixel's fragments that are not stored)
     uint8_t* pix_thick;           // [T][kTilePix] mixed frames: the pixel holds a thick-hair fragment
                                   // (nullptr in frames of one level)
@@ -217,9 +217,15 @@ struct FrameBufs {
     int32_t full_batches;         // the static scratch has no room for a table of smaller ones (see batch_cap)
     int32_t opaque;               // the frame can hold thick hairs: it has an opaque pass (k_opaque)
 };
-// (offsets stay below it: at most 2^24 segments of a tile that are not opaque cover under 2^7
-// of its pixels each, and a pixel behind an opaque fragment stores no more)
-constexpr uint32_t kHidesBit = 0x80000000u;
+// A depth key is ~0 minus the bits of an inverse depth that is not negative, so its top bit is always
+// set, and the table of the pixels' key maxima keeps something else there: a pixel whose opaque
+// fragment hides what lies behind holds that fragment's key, which is its maximum from the start,
+// and the other pixels hold theirs without the top bit.  (Offsets have no bit to spare: a tile's
+// 2^24 segments of 256 pixels each fill 32.)
+constexpr uint32_t kKeyTop = 0x80000000u;
+__host__ __device__ constexpr uint32_t kmax_seen(uint32_t key) { return key & ~kKeyTop; }
+__host__ __device__ constexpr bool kmax_hides(uint32_t word) { return (word & kKeyTop) != 0; }
+__host__ __device__ constexpr uint32_t kmax_key(uint32_t word) { return word | kKeyTop; }
 // A segment's integer radius ceil(16 hw) + 8 reaches past its footprint hw + 1/2, so 5 to 9% of
 // the fragments of a strand frame have alpha exactly 0.  Leaving them out costs the count pass
 // 14% (each fragment is tested) and saves as large a part of the emit and shading passes as

@@ -1619,7 +1619,7 @@ __device__ inline bool line_hidden(const H& h, uint32_t nearest, int p, int n, b
 // whole tile (a stale read only costs work: keys fall, never rise) is skipped.  The keys live in
 // pix_kmax, which the emit pass needs only later: a pixel with an opaque fragment stores it as
 // its farthest one, so its key maximum is that key already, and k_tile_prep clears the others
-// (and flags the pixels in pix_off, kHidesBit, so that the emit pass can tell them apart).
+// (see kmax_seen for how the emit pass tells them apart).
 // 150k x 64 strands as 1000 thick hairs at 1080p: 99.7% of its 43 M fragments are hidden, and the
 // frame takes 0.32 ms instead of 3.49 (this pass 0.07, the shading 0.03 instead of 1.97).  A
 // combed groom at a middle view, where strands and thick hairs mix and a third of the fragments
@@ -1806,13 +1806,9 @@ __global__ __launch_bounds__(kNT) void k_tile_prep(FrameBufs f) {
     }
     if (t == 0) f.tile_all[tile] = total + all;
     if ((t & 63) == 0 && deep) atomicAdd(&f.ctr->deep_pixels, (uint32_t)__popcll(deep));
-    uint32_t flag = 0;
-    if (f.opaque) {
-        if (f.pix_kmax[q] != 0xFFFFFFFFu) flag = kHidesBit;
-        else f.pix_kmax[q] = 0u;
-    }
+    if (f.opaque && f.pix_kmax[q] == 0xFFFFFFFFu) f.pix_kmax[q] = 0u;
     s_off[t] = ex;
-    f.pix_off[q] = ex | flag;
+    f.pix_off[q] = ex;
     if (t == 0) s_off[kTilePix] = total;
     if (t < kTilePix / 32) s_mask[t] = 0u;
     __syncthreads();
@@ -1921,8 +1917,8 @@ __device__ inline void batch_records(const FrameBufs& f, int tile, uint32_t* s_m
     }
     const size_t tq = (size_t)tile * kTilePix;
     const bool oversized = f.pix_cnt[tq + t] > (uint32_t)kCap;
-    const uint32_t off0 = f.pix_off[tq + t] & ~kHidesBit;
-    const uint32_t off1 = end < kTilePix ? f.pix_off[tq + end] & ~kHidesBit : f.tile_tot[tile];
+    const uint32_t off0 = f.pix_off[tq + t];
+    const uint32_t off1 = end < kTilePix ? f.pix_off[tq + end] : f.tile_tot[tile];
     bool thick = false;   // a thick-hair fragment in pixels [t, end)
     for (int k = w; k <= (end - 1) >> 5; ++k) {
         uint32_t m = s_thk[k];
@@ -1968,8 +1964,7 @@ __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
     s_kmin[t] = 0xFFFFFFFFu;
     s_kmax[t] = 0;
     s_thk[t] = 0;
-    const uint32_t off = f.pix_off[q];
-    s_pos[t] = f.frag_base[tile] + (off & ~kHidesBit) + f.item_base[(size_t)item * kTilePix + t];
+    s_pos[t] = f.frag_base[tile] + f.pix_off[q] + f.item_base[(size_t)item * kTilePix + t];
     __syncthreads();
     const int px0 = (tile % f.ntx) * kTile, py0 = (tile / f.ntx) * kTile;
     const uint32_t lstart = f.tile_start[tile];
@@ -1987,7 +1982,7 @@ __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
     s_iz[t].w = __uint_as_float((f.gid ? gseg : j) | (MIXED && (s.hwfx & kFlagThick) ? 0x80000000u : 0u));
     const bool valid = j < n;
     if constexpr (ZC) {
-        const uint32_t z0 = off & kHidesBit ? f.pix_kmax[q] : 0xFFFFFFFFu;
+        const uint32_t km = f.pix_kmax[q], z0 = kmax_hides(km) ? km : 0xFFFFFFFFu;
         const int gx = px0 + (t % kTile), gy = py0 + (t / kTile);
         hide_setup(s_hide[0], gx < cam.W && gy < cam.H ? z0 : 0u);
     }
@@ -2013,7 +2008,7 @@ __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
     __syncthreads();
     if (s_cur[t]) {
         atomicMin(&f.pix_kmin[q], s_kmin[t]);
-        atomicMax(&f.pix_kmax[q], s_kmax[t]);
+        atomicMax(&f.pix_kmax[q], kmax_seen(s_kmax[t]));
         if (MIXED && s_thk[t]) f.pix_thick[q] = 1;
     }
     // the tile's batch records, by the block of its first chunk (s_pos is free once the waves pass the
@@ -2558,13 +2553,13 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu((KIND == 0 
             const uint32_t i = t + qq * kNT;
             rec[qq] = i < Fb ? src[i] : make_uint2(0u, 0u);
         }
-        const uint32_t tile_off0 = f.pix_off[(size_t)tile * kTilePix + p0] & ~kHidesBit;
+        const uint32_t tile_off0 = f.pix_off[(size_t)tile * kTilePix + p0];
         if (t >= p0 && t < p1) {
             const uint32_t cnt = f.pix_cnt[q], kmn = f.pix_kmin[q];
             s_cnt[t] = cnt;
             s_kmin[t] = kmn;
-            s_scale[t] = bucket_scale(cnt, kmn, f.pix_kmax[q]);
-            s_off[t] = (f.pix_off[q] & ~kHidesBit) - tile_off0;
+            s_scale[t] = bucket_scale(cnt, kmn, kmax_key(f.pix_kmax[q]));
+            s_off[t] = f.pix_off[q] - tile_off0;
         }
         if (t == 0) s_off[p1] = Fb;
         for (uint32_t i = t; i < Fb; i += kNT) L_.s_bk[i] = 0;
@@ -2577,7 +2572,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu((KIND == 0 
     const int p = p0;
     const size_t qp = (size_t)tile * kTilePix + p;
     const uint32_t k = b.nfrag;
-    const unsigned long long key_end = (unsigned long long)f.pix_kmax[qp] + 1ull;
+    const unsigned long long key_end = (unsigned long long)kmax_key(f.pix_kmax[qp]) + 1ull;
     unsigned long long lo = f.pix_kmin[qp];
     float C0 = 0.f, C1 = 0.f, C2 = 0.f, T = 1.f;   // carried composite (thread 0)
     uint32_t done = 0;
@@ -2756,12 +2751,12 @@ __global__ __launch_bounds__(kNT) void k_batch_bwd(FrameBufs f, ShadeArgs a, Gra
     const uint32_t n = f.tile_start[tile + 1] - lstart;
     const uint32_t* list = f.list + lstart;
     const size_t q = (size_t)tile * kTilePix + t;
-    const uint32_t tile_off0 = f.pix_off[(size_t)tile * kTilePix + p0] & ~kHidesBit;
+    const uint32_t tile_off0 = f.pix_off[(size_t)tile * kTilePix + p0];
     if (t >= p0 && t < p1) {
         s_cnt[t] = f.pix_cnt[q];
         s_kmin[t] = f.pix_kmin[q];
-        s_kmax[t] = f.pix_kmax[q];
-        s_off[t] = (f.pix_off[q] & ~kHidesBit) - tile_off0;
+        s_kmax[t] = kmax_key(f.pix_kmax[q]);
+        s_off[t] = f.pix_off[q] - tile_off0;
         const int gx = px0 + (t % kTile), gy = py0 + (t / kTile);
         const bool in = gx < W && gy < H;
         const float4 dp = in ? reinterpret_cast<const float4*>(g.d_rgba)[(size_t)gy * W + gx] : make_float4(0, 0, 0, 0);
