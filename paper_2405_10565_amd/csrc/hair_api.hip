@@ -544,8 +544,6 @@ struct TessPass {
     bool split = false;
 };
 
-float rcp_of(float b) { return b >= 0x1p-100f && b <= 0x1p100f ? 1.0f / b : 0.0f; }   // see div_by
-
 struct DomPass {
     const DomGrid* grid;
     int32_t K;

@@ -72,6 +72,8 @@ struct DomGrid {
     int32_t R;
 };
 constexpr int kDomMaxLayers = 7;
+// 1 / b for div_by, 0 where it takes the general division.
+__host__ __device__ inline float rcp_of(float b) { return b >= 0x1p-60f && b <= 0x1p60f ? 1.0f / b : 0.0f; }
 // What shading reads per light; grid == nullptr: unshadowed.
 struct DomView {
     const DomGrid* grid;

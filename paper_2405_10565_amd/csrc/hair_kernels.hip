@@ -1181,8 +1181,9 @@ __device__ inline void wave_coverage(const CovSetup* s_cov, const uint8_t* s_own
 
 // a / b, correctly rounded, from the correctly rounded reciprocal rb of a divisor that many
 // fragments share (Markstein: a quotient within one ulp, which the first correction gives, and one
-// more step with the exact remainder): 5 instructions instead of the general division's 11.  rb = 0
-// (a divisor outside [2^-100, 2^100]) takes the general one.
+// more step with the exact remainder): 5 instructions instead of the general division's 11.  The
+// steps need a finite quotient (an infinite one comes out NaN), so rb = 0, a divisor outside
+// [2^-60, 2^60], takes the general one: no scene is 2^67 across, squared lengths overflow first.
 __device__ inline float div_rcp(float a, float b, float rb) {
     float q = a * rb;
     q = __builtin_fmaf(__builtin_fmaf(-q, b, a), rb, q);
@@ -3467,7 +3468,7 @@ __global__ __launch_bounds__(kDomBoundThreads) void k_dom_grid(const float* __re
         gr.s = ext / (float)(R - 2);
         gr.u0 = umin - gr.s;
         gr.v0 = vmin - gr.s;
-        gr.rs = gr.s >= 0x1p-100f && gr.s <= 0x1p100f ? 1.0f / gr.s : 0.0f;
+        gr.rs = rcp_of(gr.s);
         gr.k16 = 16.0f / gr.s;
         gr.z_ref = zmax + 1.0f;
         gr.R = R;
