@@ -1670,7 +1670,8 @@ __global__ __launch_bounds__(kNT) void k_opaque(FrameBufs f, CamConst cam, int f
         return line_hidden(s_hide, nearest_key(iz), p, n, steep);
     });
     __syncthreads();
-    if (s_z[t] < z0) atomicMin(&f.pix_kmax[q], s_z[t]);
+    // (kmax_key: whatever the key, the count and emit passes take the same word for hiding)
+    if (s_z[t] < z0) atomicMin(&f.pix_kmax[q], kmax_key(s_z[t]));
 }
 
 // Count pass: per pixel the fragments that the frame stores and, in pix_off until k_tile_prep

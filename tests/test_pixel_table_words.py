@@ -46,6 +46,10 @@ int main() {
         }
         if (kmax_key(word) != far) return printf("maximum lost\n");
     }
+    // an opaque fragment's word hides whatever its key is (a NaN's may lack the top bit): the count
+    // and the emit pass then leave out the same fragments
+    for (uint32_t key : {0x003FFFFFu, 0x803FFFFFu, 0u, 0x7FFFFFFFu})
+        if (!kmax_hides(kmax_key(key)) || kmax_key(key) < key) return printf("word of %08x\n", key);
     // offsets of a tile: 256 pixels of 2^24 - 1 fragments
     uint32_t off = 0;
     for (int p = 0; p < kTilePix; ++p) {
@@ -79,3 +83,9 @@ def test_offsets_are_read_whole():
     reads = [line for line in text.splitlines() if "pix_off[" in line]
     assert len(reads) >= 6
     assert not [line for line in reads if "&" in line.split("pix_off[", 1)[1].replace("&f.", "")]
+
+
+def test_the_opaque_pass_stores_words_that_hide():
+    text = open(os.path.join(ROOT, "paper_2405_10565_amd", "csrc", "hair_kernels.hip")).read()
+    stores = [line for line in text.splitlines() if "atomicMin(&f.pix_kmax[" in line]
+    assert stores and all("kmax_key(" in line for line in stores)
