@@ -366,6 +366,14 @@ int hair_debug_bins(hair_ws* ws, int64_t n_tiles, uint32_t* tile_start, int64_t 
  * HAIR_EINVAL when that light had no map. */
 int hair_debug_dom(hair_ws* ws, int32_t light, float* texels, float* grid);
 
+/* Test hook: frames of `rows` rows and more on `ws` (NULL: the context's default workspace) leave
+ * out the fragments without coverage; 2^21 unless set here.  HAIR_EINVAL when rows < 0. */
+int hair_debug_trim_rows(hair_ctx* ctx, hair_ws* ws, int64_t rows);
+
+/* Test export: the fragments that the last frame on `ws` stored, ordered and shaded, of those that
+ * its stats count (the others lie behind an opaque fragment or have no coverage). */
+int hair_debug_stored(hair_ws* ws, uint64_t* fragments);
+
 /* Test export of composited fragment lists: renders like hair_render and, for pixels in
  * [x0, x0 + w) x [y0, y0 + h), writes per pixel its fragment count (host uint[h][w]) and
  * its fragments in compositing order (host arrays of cap entries, pixels row-major):

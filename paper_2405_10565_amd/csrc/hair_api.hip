@@ -122,7 +122,8 @@ struct hair_ws {
     bool lean = false;                        // memory ran out: buffers no larger than they have to be (ws_lean)
     hipEvent_t ev[7] = {};
     bool events = false;
-    int64_t last_nseg = 0, last_ntiles = 0, last_pairs = 0;
+    int64_t last_nseg = 0, last_ntiles = 0, last_pairs = 0, last_stored = 0;
+    int64_t trim_rows = kTrimRows;            // (see kTrimRows)
     // a frame enqueued by hair_render_async and not yet finished: what a rerun needs, and
     // (done) the result of a frame that already ran to completion
     struct Pending {
@@ -522,6 +523,7 @@ int frame_result(hair_ctx* ctx, hair_ws* ws, int64_t nseg, int T, FrameOut* out)
     ws->last_nseg = nseg;
     ws->last_ntiles = T;
     ws->last_pairs = pairs;
+    ws->last_stored = out->ctr.sizes[2];
     out->pairs = pairs;
     out->n_batches = out->ctr.sizes[3];
     // three timing markers only: each costs the stream a few microseconds of idle time
@@ -701,7 +703,7 @@ int frame_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv,
     }
     // (shadow maps and debug dumps need every fragment)
     f.full_batches = ws->arena && ws->lean;
-    f.trim = !dom && !dbg && lv.nseg >= kTrimRows;
+    f.trim = !dom && !dbg && lv.nseg >= ws->trim_rows;
     // (strand levels have opaque fragments only where a strand is wider than a pixel: no pass for them)
     f.opaque = !dom && !dbg && lv.kind != 0;
     f.tile_all = ws->tile_cnt.as<uint32_t>();   // (the binning's tile totals are in tile_start by now)
@@ -1945,6 +1947,23 @@ int hair_debug_issue_rate(hair_ctx* ctx, int32_t kind, int32_t iters, double* op
     float ms = 0.0f;
     HIP_TRY(ctx, hipEventElapsedTime(&ms, ws->ev[0], ws->ev[6]), "elapsed");
     *ops_per_s = (double)blocks * 256.0 * 8.0 * (double)iters / (ms * 1e-3);
+    return HAIR_OK;
+}
+
+int hair_debug_trim_rows(hair_ctx* ctx, hair_ws* ws, int64_t rows) {
+    int rc;
+    if ((rc = check_ctx(ctx))) return rc;
+    if (rows < 0) return fail(HAIR_EINVAL, "rows %lld", (long long)rows);
+    ws = ws_or_default(ctx, ws);
+    std::lock_guard<std::mutex> g(ws->mu);
+    ws->trim_rows = rows;
+    return HAIR_OK;
+}
+
+int hair_debug_stored(hair_ws* ws, uint64_t* fragments) {
+    if (!ws || !fragments) return fail(HAIR_EINVAL, "null argument");
+    std::lock_guard<std::mutex> g(ws->mu);
+    *fragments = (uint64_t)ws->last_stored;
     return HAIR_OK;
 }
 
