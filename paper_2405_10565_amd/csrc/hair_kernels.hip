@@ -3538,13 +3538,18 @@ __global__ __launch_bounds__(256) void k_project_light(LevelDev lv, const ShadeR
 // its box coverage alpha, a thick hair alpha rho kappa l_max sqrt(1 - h^2) (Sec. 4, hair number; the
 // chord along the light at the texel's offset h = delta / hw).  The counts are 32.32 fixed-point
 // sums (they commute, so the atomics give the same sums in any order; counts are far below 2^31
-// hairs), in LDS for `group` chunks of a tile's list and added to the texels' sums in acc
+// hairs), in LDS for dom_group chunks of a tile's list and added to the texels' sums in acc
 // ([tile][layer][texel]) once.  k_dom_texels writes (iz0, C_0 .. C_6) with C the cumulative counts;
 // iz0 = 0 marks a texel without hair.  Bound by the coverage arithmetic (VALU), done twice; storing
 // the fragments in between cost more (100k strands, 1024^2 map, 34 M fragments: count + emit +
 // resolve 145 + 280 + 305 us -> 230 + 356).  A pass over a
 // sample of each list, so that the first one could skip what lies behind, gained nothing.
-__global__ __launch_bounds__(kNT) void k_dom_first(FrameBufs f, CamConst cam, int group) {
+__device__ inline uint32_t dom_group(uint32_t n_items) {
+    // a block takes four chunks of a tile's list, which saves three of four rounds of global atomics,
+    // where the light view has the items to keep the chip's 2048 block slots filled that way
+    return n_items >= 8192 ? 4u : 1u;
+}
+__global__ __launch_bounds__(kNT) void k_dom_first(FrameBufs f, CamConst cam) {
     __shared__ uint32_t s_z[kTilePix];
     __shared__ float4 s_iz[kNT];
     __shared__ CovSetup s_cov[kNT];
@@ -3552,14 +3557,15 @@ __global__ __launch_bounds__(kNT) void k_dom_first(FrameBufs f, CamConst cam, in
     const uint32_t n_items = f.item_start[f.T];
     if (blockIdx.x >= n_items || f.ctr->cap_overflow) return;
     const uint2 it = f.item_tab[xcd_contiguous(blockIdx.x, n_items)];
-    if (it.y % (uint32_t)group) return;
+    const uint32_t group = dom_group(n_items);
+    if (it.y % group) return;
     const int t = threadIdx.x, tile = (int)it.x;
     const int px0 = (tile % f.ntx) * kTile, py0 = (tile / f.ntx) * kTile;
     const uint32_t lstart = f.tile_start[tile], n = f.tile_start[tile + 1] - lstart;
     const size_t q = (size_t)tile * kTilePix + t;
     const uint32_t z0 = f.pix_kmin[q];
     s_z[t] = z0;
-    for (uint32_t k = it.y; k < it.y + (uint32_t)group && k * kNT < n; ++k) {
+    for (uint32_t k = it.y; k < it.y + group && k * kNT < n; ++k) {
         const uint32_t j = k * kNT + t;
         SegRec s{};
         if (j < n) s = f.seg[f.list[lstart + j]];
@@ -3586,7 +3592,7 @@ template <bool THICK>
 __global__ __launch_bounds__(kNT) void k_dom_layers(FrameBufs f, CamConst cam, LevelDev lv,
                                                     const ShadeRec* __restrict__ rows,
                                                     const DomGrid* __restrict__ grid, int K, int l0, int nl, float delta,
-                                                    float rdelta, unsigned long long* __restrict__ acc, int group) {
+                                                    float rdelta, unsigned long long* __restrict__ acc) {
     extern __shared__ unsigned long long s_acc[];
     __shared__ float s_iz0[kTilePix];
     __shared__ float4 s_seg[kNT];                  // (iza, izb, hw, sqrt(t_den))
@@ -3597,13 +3603,14 @@ __global__ __launch_bounds__(kNT) void k_dom_layers(FrameBufs f, CamConst cam, L
     const uint32_t n_items = f.item_start[f.T];
     if (blockIdx.x >= n_items || f.ctr->cap_overflow) return;
     const uint2 it = f.item_tab[xcd_contiguous(blockIdx.x, n_items)];
-    if (it.y % (uint32_t)group) return;
+    const uint32_t group = dom_group(n_items);
+    if (it.y % group) return;
     const int t = threadIdx.x, tile = (int)it.x;
     const int px0 = (tile % f.ntx) * kTile, py0 = (tile / f.ntx) * kTile;
     const uint32_t lstart = f.tile_start[tile], n = f.tile_start[tile + 1] - lstart;
     s_iz0[t] = iz_of_key(f.pix_kmin[(size_t)tile * kTilePix + t]);
     for (int k = 0; k < nl; ++k) s_acc[k * kTilePix + t] = 0ull;
-    for (uint32_t k = it.y; k < it.y + (uint32_t)group && k * kNT < n; ++k) {
+    for (uint32_t k = it.y; k < it.y + group && k * kNT < n; ++k) {
         const uint32_t j = k * kNT + t;
         SegRec s{};
         if (j < n) {
@@ -3791,16 +3798,14 @@ hipError_t launch_project_light(const LevelDev& lv, const ShadeRec* rows, const 
 hipError_t launch_dom_map(const FrameBufs& f, const CamConst& cam, const LevelDev& lv, const ShadeRec* rows,
                           const DomGrid* grid, int32_t K, int32_t nl, float delta, float rdelta, uint32_t n_items,
                           unsigned long long* acc, float4* tex, hipStream_t st) {
-    // a block takes four chunks of a tile's list, which saves three of four rounds of global atomics,
-    // where that leaves the chip's 2048 block slots filled
-    const int group = n_items >= 8192 ? 4 : 1;
+    // n_items: the grid (at least the view's items, which the kernels read)
     auto layers = rows || lv.kind != 0 ? &k_dom_layers<true> : &k_dom_layers<false>;
-    if (n_items) hipLaunchKernelGGL(k_dom_first, dim3(n_items), dim3(kNT), 0, st, f, cam, group);
+    if (n_items) hipLaunchKernelGGL(k_dom_first, dim3(n_items), dim3(kNT), 0, st, f, cam);
     // all layers in one pass, or one after the other into the same sums (which then run on)
     for (int l0 = 0; l0 < K; l0 += nl) {
         if (n_items)
             hipLaunchKernelGGL(layers, dim3(n_items), dim3(kNT), 8 * kTilePix * nl, st, f, cam, lv, rows, grid, K, l0, nl,
-                               delta, rdelta, acc, group);
+                               delta, rdelta, acc);
         hipLaunchKernelGGL(k_dom_texels, dim3(f.T), dim3(kNT), 0, st, f, cam.W, K, l0, nl, acc, tex);
     }
     return hipGetLastError();
