@@ -1,5 +1,6 @@
 """Writes hair_fastmath_coef.h: polynomial coefficients of the shading kernels' arcsine and
-arctangent and hyperbolic tangent, and the 8-point Gauss-Legendre rule with the refraction constants of its nodes.
+arctangent and hyperbolic tangent, and the 8-point Gauss-Legendre rule with the refraction
+constants of its nodes.
 
     python paper_2405_10565_amd/csrc/gen_fastmath.py [--check]
 
@@ -8,7 +9,7 @@ Chebyshev nodes):
   asin(z) = z + z^3 P(z^2)     z in [0, 1/2], P of degree 4, relative error of asin < 1e-8
   asin(z) = z + z^3 W(z^2)     z in [0, 0.68], W of degree 7, relative error of asin < 1e-8
   atan(a) = a Q(a^2)           a in [0, 1],   Q of degree 8, absolute error < 1e-8
-                               (also as Q / 2 and as Q / 2 pi: the angle in turns)
+                               (written as Q / 2 and as Q / 2 pi: half the angle, and turns)
   tanh(x) = x + x^3 H(x^2)     x in [0, 5/8], H of degree 4, relative error of tanh < 1e-8
 The kernels reduce |x| > 1/2 by asin(x) = pi/2 - 2 asin(sqrt((1 - x) / 2)) and atan2 to
 [0, 1] by octant symmetry.  --check only verifies that the header on disk is current.
@@ -63,8 +64,7 @@ namespace hair {{
 
 // asin(z) = z + z^3 P(z^2) on [0, 1/2]; P ascending, relative error {c['asin_err']:.1e}
 constexpr float kAsinP[5] = {{{fmt(c['asin_p'])}}};
-// atan(a) = a Q(a^2) on [0, 1]; Q ascending, absolute error {c['atan_err']:.1e}
-constexpr float kAtanQ[9] = {{{fmt(c['atan_q'])}}};
+// atan(a) = a Q(a^2) on [0, 1]; Q ascending, absolute error {c['atan_err']:.1e}; as Q / 2 and Q / 2 pi
 constexpr float kAtanHalfQ[9] = {{{fmt(c['atan_q'] / 2)}}};
 constexpr float kAtanTurnsQ[9] = {{{fmt(c['atan_q'] / (2 * np.pi))}}};
 // asin(z) = z + z^3 W(z^2) on [0, 0.68]; W ascending, relative error {c['asin_w_err']:.1e}

@@ -1620,7 +1620,7 @@ static int validate_shadow(const hair_shadow* shadow) {
 }
 
 // One shadow pass per directional light over the level lv (or, with rows, over a mixed
-// frame's rows): grid, light-view raster, per-texel resolve; fills views[] for the camera
+// frame's rows): grid, light-view raster, the two map passes; fills views[] for the camera
 // pass and adds the passes' GPU time to *ms.  The caller holds ws->mu.
 static int shadow_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, const ShadeRec* rows,
                          const hair_camera* cam, const hair_light* lights, int n_lights, const hair_shadow* shadow,

@@ -1133,11 +1133,8 @@ __device__ inline uint32_t cov_setup(const SegRec& s, bool valid, int px0, int p
 // its sign).  total and the staging from cov_setup.  line(owner, p, n, steep) sees each line first
 // (its first pixel and number of pixels, along the row when steep, else along the column) and may
 // take it whole by returning true.
-struct NoLine {
-    __device__ bool operator()(int, int, int, bool) const { return false; }
-};
-template <class F, class L = NoLine>
-__device__ inline void wave_coverage(const CovSetup* s_cov, const uint8_t* s_own, uint32_t total, F&& f, L&& line = L{}) {
+template <class F, class L>
+__device__ inline void wave_coverage(const CovSetup* s_cov, const uint8_t* s_own, uint32_t total, F&& f, L&& line) {
     const int t = threadIdx.x, lane = t & 63, wbase = t & ~63;
     const uint8_t* own = s_own + (t >> 6) * kCovLinesPerWave;
     for (uint32_t g = (uint32_t)lane; g < total; g += 64) {
@@ -3379,8 +3376,8 @@ __global__ __launch_bounds__(256) void k_project_split_mixed(HierDev h, const ui
 // ---------------------------------------------------------------------------------------
 // Shadow pass: deep opacity map toward a directional light (Sec. 5.2 shadow pass; its count
 // feeds the forward lobes of Sec. 4).  The light view is an orthographic raster with the
-// camera pass's integer coverage rule, so binning, counting and emission are the camera
-// kernels; only the projection and the per-texel resolve are the light's own.  Every float
+// camera pass's integer coverage rule, so binning and the coverage arithmetic are the camera
+// kernels'; the projection and the two map passes are the light's own.  Every float
 // step that decides an integer (bounds, grid, snapping, depth) is a single rounding per
 // operation in a fixed order (this file is compiled without contraction).
 
@@ -3532,6 +3529,12 @@ __global__ __launch_bounds__(256) void k_project_light(LevelDev lv, const ShadeR
     seg[g] = r;
 }
 
+// A block of the map passes takes four chunks of a tile's list, which saves three of four rounds of
+// global atomics, where the light view has the items to keep the chip's 2048 block slots filled that
+// way (a warm frame's grid may be larger: the view's own count decides.  20k strands, map 256, on a
+// workspace that has drawn a large frame: 0.285 ms a frame by the grid, 0.254 by the count).
+__device__ inline uint32_t dom_group(uint32_t n_items) { return n_items >= 8192 ? 4u : 1u; }
+
 // The shadow map of a light view is two passes over the tiles' lists, with no fragment stored:
 // k_dom_first finds per texel the first hit iz0 (the smallest depth key), k_dom_layers adds every
 // fragment's expected hair count to its layer floor((iz0 - iz) / delta) (clamped to K - 1): a strand
@@ -3542,13 +3545,8 @@ __global__ __launch_bounds__(256) void k_project_light(LevelDev lv, const ShadeR
 // ([tile][layer][texel]) once.  k_dom_texels writes (iz0, C_0 .. C_6) with C the cumulative counts;
 // iz0 = 0 marks a texel without hair.  Bound by the coverage arithmetic (VALU), done twice; storing
 // the fragments in between cost more (100k strands, 1024^2 map, 34 M fragments: count + emit +
-// resolve 145 + 280 + 305 us -> 230 + 356).  A pass over a
-// sample of each list, so that the first one could skip what lies behind, gained nothing.
-__device__ inline uint32_t dom_group(uint32_t n_items) {
-    // a block takes four chunks of a tile's list, which saves three of four rounds of global atomics,
-    // where the light view has the items to keep the chip's 2048 block slots filled that way
-    return n_items >= 8192 ? 4u : 1u;
-}
+// resolve 145 + 280 + 305 us -> 230 + 356).  A pass over a sample of each list, so that the first one
+// could skip what lies behind, gained nothing.
 __global__ __launch_bounds__(kNT) void k_dom_first(FrameBufs f, CamConst cam) {
     __shared__ uint32_t s_z[kTilePix];
     __shared__ float4 s_iz[kNT];
