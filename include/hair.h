@@ -370,6 +370,10 @@ int hair_debug_dom(hair_ws* ws, int32_t light, float* texels, float* grid);
  * out the fragments without coverage; 2^21 unless set here.  HAIR_EINVAL when rows < 0. */
 int hair_debug_trim_rows(hair_ctx* ctx, hair_ws* ws, int64_t rows);
 
+/* Test hook: frames of thick hairs and mixed frames on `ws` (NULL: the context's default workspace)
+ * look for what opaque fragments hide never (0), always (1), or where it pays (-1, the default). */
+int hair_debug_opaque(hair_ctx* ctx, hair_ws* ws, int32_t mode);
+
 /* Test export: the fragments that the last frame on `ws` stored, ordered and shaded, of those that
  * its stats count (the others lie behind an opaque fragment or have no coverage). */
 int hair_debug_stored(hair_ws* ws, uint64_t* fragments);

@@ -29,7 +29,7 @@ EXPORTS = [
     "hair_select_level", "hair_render", "hair_render_backward", "hair_debug_segments", "hair_debug_bins",
     "hair_debug_fragments", "hair_lod_groups", "hair_lod_init", "hair_render_mixed", "hair_render_shadowed",
     "hair_debug_dom", "hair_render_curved", "hair_render_async", "hair_ws_finish", "hair_render_noalloc",
-    "hair_noalloc_scratch_bytes", "hair_debug_issue_rate", "hair_debug_trim_rows", "hair_debug_stored",
+    "hair_noalloc_scratch_bytes", "hair_debug_issue_rate", "hair_debug_trim_rows", "hair_debug_opaque", "hair_debug_stored",
     "hair_render_mixed_shadowed",
 ]
 
@@ -129,6 +129,7 @@ def _load():
         "hair_noalloc_scratch_bytes": ([], U64),
         "hair_debug_issue_rate": ([P, I32, I32, C.POINTER(C.c_double)], C.c_int),
         "hair_debug_trim_rows": ([P, P, I64], C.c_int),
+        "hair_debug_opaque": ([P, P, I32], C.c_int),
         "hair_debug_stored": ([P, C.POINTER(U64)], C.c_int),
         "hair_render_backward": ([P, P, I32, I32, C.POINTER(hair_camera), C.POINTER(hair_light), I32, P, P, P, P, P],
                                  C.c_int),
@@ -510,6 +511,9 @@ class Context:
 
     def debug_trim_rows(self, rows: int, ws: Workspace | None = None):
         check(lib.hair_debug_trim_rows(self.handle, ws.handle if ws else None, int(rows)))
+
+    def debug_opaque(self, mode: int, ws: Workspace | None = None):
+        check(lib.hair_debug_opaque(self.handle, ws.handle if ws else None, int(mode)))
 
     def debug_stored(self, ws: Workspace) -> int:
         """Fragments that the last frame on ws stored and shaded, of those its stats count."""

@@ -124,6 +124,7 @@ struct hair_ws {
     bool events = false;
     int64_t last_nseg = 0, last_ntiles = 0, last_pairs = 0, last_stored = 0;
     int64_t trim_rows = kTrimRows;            // (see kTrimRows)
+    int32_t opaque = -1;                      // opaque pass: where it pays (-1), never (0), always (1)
     // a frame enqueued by hair_render_async and not yet finished: what a rerun needs, and
     // (done) the result of a frame that already ran to completion
     struct Pending {
@@ -559,7 +560,7 @@ struct DomPass {
 //   k_bin_count, k_bin_offsets        per-block tile counts, their column scan
 //   k_lists_scan                      list offsets and work items (list chunks) per tile
 //   k_scatter                         tile lists (per-block LDS cursors); counters and image cleared
-//   k_opaque                          nearest opaque keys (frames that can hold thick hairs)
+//   k_opaque                          nearest opaque keys (thick hairs, and mixed frames where it pays)
 //   k_count, k_tile_prep, k_tile_scans  per-pixel counts, offsets, batches
 //   k_emit                            fragment buffer, per-pixel key ranges, batch table (mixed
 //                                     frames: k_batch_records)
@@ -601,7 +602,7 @@ int frame_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv,
     if ((rc = ws_need(ws, ws->tile_cnt, 4ull * T))) return rc;
     if ((rc = ws_need(ws, ws->tile_start, 4ull * (T + 1)))) return rc;
     if ((rc = ws_need(ws, ws->bin_m, 4ull * plan.nb * T))) return rc;
-    if ((rc = ws_need(ws, ws->bin_blk, 16ull * plan.nb))) return rc;
+    if ((rc = ws_need(ws, ws->bin_blk, sizeof(BlockStats) * plan.nb))) return rc;
     if ((rc = ws_need(ws, ws->ctr, sizeof(Counters)))) return rc;
     if ((rc = ws_need(ws, ws->items, 4ull * T))) return rc;
     if ((rc = ws_need(ws, ws->item_start, 4ull * (T + 1)))) return rc;
@@ -627,7 +628,7 @@ int frame_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv,
                 "k_project_tess");
     else
         HIP_TRY(ctx, launch_project(lv, cc, ws->seg.as<SegRec>(), ws->shade.as<ShadeRec>(), st), "k_project");
-    HIP_TRY(ctx, launch_bins(ws->seg.as<SegRec>(), lv.nseg, cc, plan, ws->bin_m.as<uint32_t>(), ws->bin_blk.as<uint4>(),
+    HIP_TRY(ctx, launch_bins(ws->seg.as<SegRec>(), lv.nseg, cc, plan, lv.kind == 2 && lv.thick && !dom, ws->bin_m.as<uint32_t>(), ws->bin_blk.as<BlockStats>(),
                              ws->tile_cnt.as<uint32_t>(), ws->ctr.as<Counters>(), st),
             "k_bin_count");
     // frames of up to 2^16 tiles scan and check their sizes in single-block kernels
@@ -640,7 +641,7 @@ int frame_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv,
                 "k_lists_scan");
     } else {
         HIP_TRY(ctx, launch_exscan(ws->tile_cnt.as<uint32_t>(), tile_start, T, scan_tmp, st), "k_scan");
-        HIP_TRY(ctx, launch_tile_items(tile_start, T, ws->items.as<uint32_t>(), st), "k_tile_items");
+        HIP_TRY(ctx, launch_tile_items(tile_start, T, ws->items.as<uint32_t>(), ws->ctr.as<Counters>(), st), "k_tile_items");
         HIP_TRY(ctx, launch_exscan(ws->items.as<uint32_t>(), ws->item_start.as<uint32_t>(), T, scan_tmp, st), "k_scan");
     }
     FrameCaps caps = ws->caps;
@@ -705,7 +706,8 @@ int frame_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv,
     f.full_batches = ws->arena && ws->lean;
     f.trim = !dom && !dbg && lv.nseg >= ws->trim_rows;
     // (strand levels have opaque fragments only where a strand is wider than a pixel: no pass for them)
-    f.opaque = !dom && !dbg && lv.kind != 0;
+    // (in mixed frames the device decides, see opaque_pays)
+    f.opaque = dom || dbg || lv.kind == 0 ? 0 : ws->opaque >= 0 ? ws->opaque : lv.kind == 2 && !lv.thick ? 0 : lv.kind;
     f.tile_all = ws->tile_cnt.as<uint32_t>();   // (the binning's tile totals are in tile_start by now)
     f.tile_tot = ws->tile_tot.as<uint32_t>();
     f.tile_nb = ws->tile_nb.as<uint32_t>();
@@ -725,7 +727,7 @@ int frame_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv,
     const uint32_t item_grid = warm ? caps.items : n_items;
     uint32_t n_batches = 0, batch_grid = 0;
     if (!dom) {
-        HIP_TRY(ctx, launch_count(f, cc, item_grid, st), "k_count");
+        HIP_TRY(ctx, launch_count(f, cc, item_grid, lv.nseg, st), "k_count");
         HIP_TRY(ctx, launch_tile_prep(f, st), "k_tile_prep");
         if (fused) {
             HIP_TRY(ctx, launch_tile_scans(f, ws->frag_base.as<uint32_t>(), ws->batch_start.as<uint32_t>(),
@@ -1792,13 +1794,13 @@ static int render_mixed(hair_ctx* ctx, hair_ws* ws, int32_t asset, const hair_ca
     std::lock_guard<std::mutex> g(ws->mu);
     hipStream_t st = (hipStream_t)stream;
     const int GS = h.G * h.S;
-    if ((rc = ws_need_lean(ws, ws->sel_cnt, 4ull * (GS + 1))) || (rc = ws_need_lean(ws, ws->sel_start, 4ull * (GS + 2))) ||
+    if ((rc = ws_need_lean(ws, ws->sel_cnt, 4ull * (GS + 1))) || (rc = ws_need_lean(ws, ws->sel_start, 4ull * (GS + 3))) ||
         (rc = ws_need_lean(ws, ws->sel_tmp, 4 * exscan_scratch_words(GS))))
         return rc;
     HIP_TRY(ctx, launch_select(h, levels, ws->sel_cnt.as<uint32_t>(), ws->sel_start.as<uint32_t>(), ws->sel_tmp.as<uint32_t>(), st),
             "k_sel_count");
-    uint32_t sizes[2];
-    if ((rc = read_words(ctx, ws, ws->sel_start.as<uint32_t>() + GS, 2, st, sizes))) return rc;
+    uint32_t sizes[3];
+    if ((rc = read_words(ctx, ws, ws->sel_start.as<uint32_t>() + GS, 3, st, sizes))) return rc;
     const uint32_t nsel = sizes[0], bad = sizes[1];
     if (bad) return fail(HAIR_EINVAL, "%u entries of levels lie outside [0, %d]", bad, h.n_levels);
     if ((rc = ws_need_lean(ws, ws->sel, 4ull * std::max<uint32_t>(nsel, 1)))) return rc;
@@ -1808,6 +1810,9 @@ static int render_mixed(hair_ctx* ctx, hair_ws* ws, int32_t asset, const hair_ca
     lv.kind = 2;
     lv.nseg = (int32_t)nsel;
     lv.S = a->S;
+    // (a sixteenth of the groom as thick hairs: below, none of the views that opaque_pays was measured
+    // on chose the opaque pass, and the frame is spared the launches that decide)
+    lv.thick = sizes[2] < h.lv[0].nseg - h.lv[0].nseg / 16;
     DomView views[HAIR_MAX_LIGHTS];
     float ms_dom = 0.0f;
     if (shadow) {
@@ -1957,6 +1962,16 @@ int hair_debug_trim_rows(hair_ctx* ctx, hair_ws* ws, int64_t rows) {
     ws = ws_or_default(ctx, ws);
     std::lock_guard<std::mutex> g(ws->mu);
     ws->trim_rows = rows;
+    return HAIR_OK;
+}
+
+int hair_debug_opaque(hair_ctx* ctx, hair_ws* ws, int32_t mode) {
+    int rc;
+    if ((rc = check_ctx(ctx))) return rc;
+    if (mode < -1 || mode > 1) return fail(HAIR_EINVAL, "mode %d outside [-1, 1]", mode);
+    ws = ws_or_default(ctx, ws);
+    std::lock_guard<std::mutex> g(ws->mu);
+    ws->opaque = mode;
     return HAIR_OK;
 }
 

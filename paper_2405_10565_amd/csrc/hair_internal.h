@@ -129,6 +129,7 @@ struct LevelDev {
     const float* axes;       // thick hairs: (|a|, |b|) [nseg][2]
     const int32_t* n_total;  // thick hairs: member count [n_owner]
     const float* r;          // thick hairs: hair radius [n_owner]
+    int32_t thick;           // a mixed frame (kind 2): enough of it is thick hairs for an opaque pass
 };
 
 // A nested LoD hierarchy for per-group, per-segment level choice: levels 0 (strands) ..
@@ -154,6 +155,9 @@ struct Counters {
     uint32_t cap_overflow;   // a frame size exceeded its buffer: the later passes did nothing
     uint32_t split_needed;   // segments culled as too long that pieces can draw (the frame is drawn again)
     uint32_t sizes[4];       // list entries, work items, stored fragments, batches of the frame
+    uint32_t tiles;          // tiles with segments (frames whose scans are not single-block)
+    uint32_t hides;          // mixed frames: the frame has an opaque pass (opaque_pays)
+    unsigned long long area_opaque, area_all;   // mixed frames: see BlockStats
     uint32_t thick_batches;  // mixed frames: batches holding thick-hair fragments (listed in thick_list)
     unsigned long long phase[8];  // per-phase cycle sums (instrumented builds only)
 };
@@ -217,7 +221,8 @@ struct FrameBufs {
                                   // 2^24 rows, forward passes) instead of the index in the tile's list
     int32_t trim;                 // fragments whose alpha is exactly 0 are not stored (kTrimRows)
     int32_t full_batches;         // the static scratch has no room for a table of smaller ones (see batch_cap)
-    int32_t opaque;               // the frame can hold thick hairs: it has an opaque pass (k_opaque)
+    int32_t opaque;               // an opaque pass (k_opaque): 1 (levels of thick hairs), 0 (none), or
+                                  // 2 (mixed frames): where ctr->hides says
 };
 // A depth key is ~0 minus the bits of an inverse depth that is not negative, so its top bit is always
 // set, and the table of the pixels' key maxima keeps something else there: a pixel whose opaque
@@ -250,11 +255,17 @@ struct BinPlan {
     int nb, per_block, range, lanes;
 };
 BinPlan bin_plan(int32_t nseg, int32_t T, bool wide = false);
+// A binning block's segments: visible, culled as too long, largest visible half-width, to be drawn as
+// pieces; and with areas, in 1/256 square pixels, what the opaque cores (alpha 1) and the whole
+// footprints of those that reach the image cover of it.
+struct BlockStats {
+    uint32_t visible, culled_long, max_hw_bits, split;
+    unsigned long long area_opaque, area_all;
+};
 // M (nb * T words), blk (nb entries), tot (T words): per-block counts and segment statistics and
-// the tiles' list lengths of the projected segments; ctr is cleared and receives the visible /
-// culled counts and the largest half-width.
-hipError_t launch_bins(const SegRec* seg, int32_t nseg, const CamConst& cam, const BinPlan& p, uint32_t* M,
-                       uint4* blk, uint32_t* tot, Counters* ctr, hipStream_t st);
+// the tiles' list lengths of the projected segments; ctr is cleared and receives the statistics.
+hipError_t launch_bins(const SegRec* seg, int32_t nseg, const CamConst& cam, const BinPlan& p, bool areas, uint32_t* M,
+                       BlockStats* blk, uint32_t* tot, Counters* ctr, hipStream_t st);
 // The tile lists, and everything the later passes expect cleared: the frame's per-pixel counters,
 // the work-item table and (when given) the image, transparent black.
 hipError_t launch_scatter(const FrameBufs& f, int32_t nseg, const CamConst& cam, const BinPlan& p, const uint32_t* M,
@@ -264,7 +275,7 @@ hipError_t launch_scatter(const FrameBufs& f, int32_t nseg, const CamConst& cam,
 // capacity (stage 1: list entries and work items; stage 2: fragments and batches).  Every
 // later pass that would fill a sized buffer does nothing once the flag is set.
 hipError_t launch_check_caps(const FrameBufs& f, const FrameCaps& caps, int stage, hipStream_t st);
-hipError_t launch_tile_items(const uint32_t* tile_start, int T, uint32_t* items, hipStream_t st);
+hipError_t launch_tile_items(const uint32_t* tile_start, int T, uint32_t* items, Counters* ctr, hipStream_t st);
 hipError_t launch_sum_tiles(const FrameBufs& f, hipStream_t st);   // ctr->fragments of larger frames
 // Fused single-block forms for frames of at most kScanOneBlockTiles tiles: list offsets and work
 // items with the first capacity check; the fragment and batch offsets with the second.
@@ -284,7 +295,7 @@ hipError_t launch_select_fill(const HierDev& h, const int32_t* levels, const uin
 hipError_t launch_project_mixed(const HierDev& h, const uint32_t* sel, int32_t nsel, const CamConst& cam, SegRec* seg,
                                 ShadeRec* shade, hipStream_t st);
 // grid: blocks to launch (>= the frame's work items / batches, read on the device)
-hipError_t launch_count(const FrameBufs& f, const CamConst& cam, uint32_t grid, hipStream_t st);
+hipError_t launch_count(const FrameBufs& f, const CamConst& cam, uint32_t grid, int32_t rows, hipStream_t st);
 hipError_t launch_tile_prep(const FrameBufs& f, hipStream_t st);
 hipError_t launch_batch_records(const FrameBufs& f, hipStream_t st);
 hipError_t launch_emit(const FrameBufs& f, const CamConst& cam, uint32_t grid, hipStream_t st);

@@ -314,8 +314,8 @@ __global__ __launch_bounds__(256) void k_project(LevelDev lv, CamConst cam, SegR
 // level l is the largest 2 hw over the visible k-th segments of level l's owners in g (0 if
 // none is visible).  One wave per (g, k).
 
-// Level of (g, k); levels outside [0, n_levels] are read as 0 (the selection counts them in
-// start[G S + 1], which the caller checks before rendering).
+// Level of (g, k); levels outside [0, n_levels] are read as 0 (the selection counts them, and the
+// caller checks before rendering).
 __device__ inline int level_at(const HierDev& h, const int32_t* levels, int gk) {
     const int L = levels[gk];
     return (L < 0 || L > h.n_levels) ? 0 : L;
@@ -400,20 +400,24 @@ __global__ __launch_bounds__(256) void k_lod_update(HierDev h, CamConst cam, flo
 
 // Selection of a mixed frame: for every (g, k) the k-th segments of the owners of level
 // L(g, k) in g, in (g, k, owner) order; entry = level << 28 | segment id of that level.  start[G S] is
-// the number of rows, start[G S + 1] that of entries of levels out of range.
-__device__ inline uint32_t selected(const HierDev& h, const int32_t* levels, int gk, uint32_t& bad) {
+// the number of rows, start[G S + 1] that of entries of levels out of range, start[G S + 2] that of the
+// rows that are strands.
+__device__ inline uint32_t selected(const HierDev& h, const int32_t* levels, int gk, uint32_t& bad, uint32_t& strands) {
     const int g = gk / h.S, raw = levels[gk], L = level_at(h, levels, gk);
     if (raw != L) ++bad;
-    return (uint32_t)(h.grp_start[L][g + 1] - h.grp_start[L][g]);
+    const uint32_t n = (uint32_t)(h.grp_start[L][g + 1] - h.grp_start[L][g]);
+    if (L == 0) strands += n;
+    return n;
 }
-// (more than kScanOneBlock (g, k): *bad is zeroed before)
+// (more than kScanOneBlock (g, k): sums, the last two words of start, is zeroed before)
 __global__ __launch_bounds__(256) void k_sel_count(HierDev h, const int32_t* __restrict__ levels,
-                                                   uint32_t* __restrict__ cnt, uint32_t* __restrict__ bad) {
+                                                   uint32_t* __restrict__ cnt, uint32_t* __restrict__ sums) {
     const int gk = blockIdx.x * blockDim.x + threadIdx.x;
-    if (gk >= h.G * h.S) return;
-    uint32_t b = 0;
-    cnt[gk] = selected(h, levels, gk, b);
-    if (b) atomicAdd(bad, 1u);
+    uint32_t bad = 0, strands = 0;
+    if (gk < h.G * h.S) cnt[gk] = selected(h, levels, gk, bad, strands);
+    if (bad) atomicAdd(&sums[0], 1u);
+    strands = wave_inclusive_sum(strands);
+    if ((threadIdx.x & 63) == 63 && strands) atomicAdd(&sums[1], strands);
 }
 
 __global__ __launch_bounds__(256) void k_sel_fill(HierDev h, const int32_t* __restrict__ levels,
@@ -536,21 +540,49 @@ __device__ inline uint32_t block_scan_1024(int n, G get, P put, uint32_t* s_w) {
 }
 
 // The selection's counts and their scan in one block (up to kScanOneBlock (g, k)): one launch
-// instead of a clear, a count and a scan, and one 8-byte readback instead of two.
+// instead of a clear, a count and a scan, and one readback instead of two.
 __global__ __launch_bounds__(1024) void k_select(HierDev h, const int32_t* __restrict__ levels,
                                                  uint32_t* __restrict__ start) {
-    __shared__ uint32_t s_w[16], s_bad;
-    if (threadIdx.x == 0) s_bad = 0u;
+    __shared__ uint32_t s_w[16], s_bad, s_strands;
+    if (threadIdx.x == 0) s_bad = s_strands = 0u;
     __syncthreads();
     const int n = h.G * h.S;
-    uint32_t bad = 0;
+    uint32_t bad = 0, strands = 0;
     const uint32_t total = block_scan_1024(
-        n, [&](int i) { return selected(h, levels, i, bad); }, [&](int i, uint32_t x) { start[i] = x; }, s_w);
+        n, [&](int i) { return selected(h, levels, i, bad, strands); }, [&](int i, uint32_t x) { start[i] = x; }, s_w);
     if (bad) atomicAdd(&s_bad, bad);
+    strands = wave_inclusive_sum(strands);
+    if ((threadIdx.x & 63) == 63) atomicAdd(&s_strands, strands);
     __syncthreads();
     if (threadIdx.x == 0) {
         start[n] = total;
         start[n + 1] = s_bad;
+        start[n + 2] = s_strands;
+    }
+}
+
+// Whether a mixed frame looks for what opaque fragments hide.  Hairs whose opaque cores cover the tiles
+// that hold any segment m times over hide, lying anywhere in the depth of the groom, a fraction
+// 1 - (1 - e^-m) / m of the fragments.  The pass costs a frame what a quarter of its fragments cost the
+// later passes (100k strands in locks that fill half the screen, 3% of them hidden: 1.68 ms without it,
+// 1.91 with it), and 12 us at least, so: m >= 1/2, and 180,000 hidden fragments.  249 views of five
+// grooms with thick hairs up to 1.5 .. 25 px wide take, in the geometric mean, 0.947 of the time that they
+// take without the pass (0.34 at best, 13 us more at worst) and 0.944 of that with it in every view
+// (0.75 at best, 30 us more at worst).
+__device__ inline bool opaque_pays(unsigned long long area_opaque, unsigned long long area_all, uint32_t tiles) {
+    const float m = (float)area_opaque * (1.0f / 65536.0f) / (float)max(tiles, 1u);
+    if (!(m >= 0.5f)) return false;
+    const float hidden = 1.0f - (1.0f - expf(-m)) / m;
+    return hidden * ((float)area_all * (1.0f / 256.0f)) >= 180000.0f;
+}
+// The items of a block of the opaque and count passes (with: for frames with an opaque pass; see
+// launch_count).
+template <class F> __device__ inline void for_each_item(const FrameBufs& f, bool with, F&& item) {
+    const uint32_t n_items = f.item_start[f.T];
+    if (blockIdx.x >= n_items || f.ctr->cap_overflow || (f.opaque == 2 && (f.ctr->hides != 0) != with)) return;
+    for (uint32_t b = blockIdx.x; b < n_items; b += gridDim.x) {
+        if (b != blockIdx.x) __syncthreads();
+        item(xcd_contiguous(b, n_items));
     }
 }
 
@@ -562,16 +594,27 @@ __global__ __launch_bounds__(1024) void k_lists_scan(const uint32_t* __restrict_
                                                      uint32_t* __restrict__ tile_start,
                                                      uint32_t* __restrict__ item_start, Counters* ctr, uint32_t cap_pairs,
                                                      uint32_t cap_items) {
-    __shared__ uint32_t s_w[16];
+    __shared__ uint32_t s_w[16], s_tiles;
     const bool items = blockIdx.x == 1;
     uint32_t* start = items ? item_start : tile_start;
+    uint32_t tiles = 0;   // that hold any segment
+    if (threadIdx.x == 0) s_tiles = 0u;
     const uint32_t n = block_scan_1024(
-        T, [&](int i) { return items ? (tot[i] + kNT - 1) / kNT : tot[i]; },
+        T, [&](int i) {
+            tiles += tot[i] != 0u;
+            return items ? (tot[i] + kNT - 1) / kNT : tot[i];
+        },
         [&](int i, uint32_t v) { start[i] = v; }, s_w);
+    if (items) {
+        tiles = wave_inclusive_sum(tiles);
+        if ((threadIdx.x & 63) == 63) atomicAdd(&s_tiles, tiles);
+        __syncthreads();
+    }
     if (threadIdx.x == 0) {
         start[T] = n;
         ctr->sizes[items ? 1 : 0] = n;
         if (n > (items ? cap_items : cap_pairs)) ctr->cap_overflow = 1u;
+        if (items) ctr->hides = opaque_pays(ctr->area_opaque, ctr->area_all, s_tiles);
     }
 }
 
@@ -772,17 +815,21 @@ __device__ inline void for_each_tile_in_range(const SegRec& r, int ntx, int nty,
     }
 }
 
-// The first pass also leaves per-block segment statistics in blk[b] = (visible, culled as too
-// long, bits of the largest visible half-width) for k_bin_offsets to reduce.
+// (alpha is exactly 1 at delta <= hw - 1/2 - kOpaqueMargin, see strip_opaque)
+constexpr float kOpaqueMargin = 0x1p-6f;
+// The first pass also leaves per-block segment statistics in blk[b] for k_bin_offsets to reduce.
+// AREAS: with the areas that decide about a mixed frame's opaque pass (whole numbers, so that their sums
+// and the decision do not depend on an order).
 //
 // LANES: lanes that share a segment, one tile row each in turn.  One for strands (a strand's box has
 // a row or two).  A thick-hair level has few segments of many rows: with one lane each, 16 k of them
 // fill 32 blocks, and each lane walks a dozen rows (count and scatter of 1000 hairs of 64 segments at
 // 1080p with one and with eight lanes: 32 + 43 -> 20 + 30 us, k_bin_offsets 6 -> 12).
-template <int LANES>
+template <int LANES, bool AREAS>
 __global__ __launch_bounds__(kBinThreads) void k_bin_count(const SegRec* __restrict__ seg, int nseg, int per_block,
                                                            int ntx, int nty, int t0, int nt,
-                                                           uint32_t* __restrict__ M, uint4* __restrict__ blk) {
+                                                           uint32_t* __restrict__ M, BlockStats* __restrict__ blk) {
+    static_assert(!AREAS || LANES == 1, "");
     extern __shared__ uint32_t s_tc[];
     __shared__ uint32_t s_maxhw;
     const int T = ntx * nty;
@@ -791,6 +838,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_count(const SegRec* __restr
     __syncthreads();
     const int g0 = blockIdx.x * per_block, g1 = min(nseg, g0 + per_block);
     uint32_t nvis = 0, nlong = 0, nsplit = 0, maxhw = 0;
+    unsigned long long core = 0, all = 0;
     const int row0 = (int)threadIdx.x % LANES;
     for (int g = g0 + (int)threadIdx.x / LANES; g < g1; g += kBinThreads / LANES) {
         const SegRec r = seg[g];
@@ -802,7 +850,39 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_count(const SegRec* __restr
             nlong += (r.hwfx & kFlagCulledLong) ? 1u : 0u;
             nsplit += (r.hwfx & kFlagSplit) ? 1u : 0u;
         }
-        for_each_tile_in_range(r, ntx, nty, t0, nt, row0, LANES, [&](int l) { atomicAdd(&s_tc[l], 1u); });
+        int tiles = 0;
+        for_each_tile_in_range(r, ntx, nty, t0, nt, row0, LANES, [&](int l) {
+            atomicAdd(&s_tc[l], 1u);
+            if (AREAS) ++tiles;
+        });
+        if (AREAS && tiles) {   // (2^-8 pixels; at most the tiles' own area)
+            const float dx = (float)(r.xb - r.xa), dy = (float)(r.yb - r.ya);
+            const float len = 16.0f * __builtin_amdgcn_sqrtf(dx * dx + dy * dy);
+            const float cap = 65536.0f * (float)min(tiles, 1 << 15);
+            core += (uint32_t)fminf(2.0f * fmaxf(r.hw - 0.5f - kOpaqueMargin, 0.0f) * len, cap);
+            all += (uint32_t)fminf((2.0f * r.hw + 1.0f) * len, cap);
+        }
+    }
+    if (AREAS) {
+        __shared__ unsigned long long s_core[kBinThreads / 64], s_all[kBinThreads / 64];
+        for (int off = 32; off >= 1; off >>= 1) {
+            core += (unsigned long long)__shfl_xor((long long)core, off);
+            all += (unsigned long long)__shfl_xor((long long)all, off);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            s_core[threadIdx.x >> 6] = core;
+            s_all[threadIdx.x >> 6] = all;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < kBinThreads / 64; ++w) {
+                core += s_core[w];
+                all += s_all[w];
+            }
+            // (one range of tiles after the other)
+            blk[blockIdx.x].area_opaque = core + (t0 ? blk[blockIdx.x].area_opaque : 0ull);
+            blk[blockIdx.x].area_all = all + (t0 ? blk[blockIdx.x].area_all : 0ull);
+        }
     }
     if (t0 == 0) {
         if (maxhw) atomicMax(&s_maxhw, maxhw);
@@ -826,7 +906,11 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_count(const SegRec* __restr
                 tc += s_c[w];
                 ts += s_sp[w];
             }
-            blk[blockIdx.x] = make_uint4(tv, tc, s_maxhw, ts);
+            BlockStats& b = blk[blockIdx.x];
+            b.visible = tv;
+            b.culled_long = tc;
+            b.max_hw_bits = s_maxhw;
+            b.split = ts;
         }
     }
     __syncthreads();
@@ -840,8 +924,8 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_count(const SegRec* __restr
 // Block 0 also clears the frame's counters (nothing before uses them) and reduces the per-block
 // segment statistics into them.
 __global__ __launch_bounds__(1024) void k_bin_offsets(uint32_t* __restrict__ M, int nb, int T,
-                                                      uint32_t* __restrict__ tot, const uint4* __restrict__ blk,
-                                                      Counters* __restrict__ ctr) {
+                                                      uint32_t* __restrict__ tot, const BlockStats* __restrict__ blk,
+                                                      Counters* __restrict__ ctr, bool areas) {
     __shared__ uint32_t s_part[16][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int t = blockIdx.x * 64 + lane;
@@ -872,20 +956,28 @@ __global__ __launch_bounds__(1024) void k_bin_offsets(uint32_t* __restrict__ M, 
     }
     if (blockIdx.x == 0 && w == 0) {
         uint32_t v = 0, c = 0, m = 0, sp = 0;
+        unsigned long long core = 0, all = 0;
         for (int b = lane; b < nb; b += 64) {
-            const uint4 x = blk[b];
-            v += x.x;
-            c += x.y;
-            m = max(m, x.z);
-            sp += x.w;
+            v += blk[b].visible;
+            c += blk[b].culled_long;
+            m = max(m, blk[b].max_hw_bits);
+            sp += blk[b].split;
+            if (areas) {
+                core += blk[b].area_opaque;
+                all += blk[b].area_all;
+            }
         }
         for (int off = 32; off >= 1; off >>= 1) {
             v += __shfl_xor(v, off);
             c += __shfl_xor(c, off);
             m = max(m, (uint32_t)__shfl_xor((int)m, off));
             sp += __shfl_xor(sp, off);
+            core += (unsigned long long)__shfl_xor((long long)core, off);
+            all += (unsigned long long)__shfl_xor((long long)all, off);
         }
         if (lane == 0) {
+            ctr->area_opaque = core;
+            ctr->area_all = all;
             ctr->visible = v;
             ctr->culled_long = c;
             ctr->max_hw_bits = m;
@@ -967,6 +1059,7 @@ __global__ void k_check_caps(FrameBufs f, FrameCaps caps, int stage) {
         f.ctr->sizes[0] = pairs;
         f.ctr->sizes[1] = items;
         over = (pairs > caps.pairs) || (items > caps.items);
+        f.ctr->hides = opaque_pays(f.ctr->area_opaque, f.ctr->area_all, f.ctr->tiles);
     } else {
         const uint32_t frags = f.frag_base[f.T], batches = f.batch_start[f.T];
         f.ctr->sizes[2] = frags;
@@ -1036,7 +1129,6 @@ constexpr int kCovLinesPerWave = 64 * kTile;   // a segment has at most kTile li
 // |cross| <= strip_opaque only fragments whose alpha is exactly 1 (delta <= hw - 1/2 - 2^-6;
 // negative where the segment has none).  Both are float estimates with their error (a few
 // 2^-24 relative) on the safe side.
-constexpr float kOpaqueMargin = 0x1p-6f;
 __device__ inline int strip_vis(float hw, int tden, int smax) {
     const float s = (hw + 0.5f) * 16.0f * __builtin_amdgcn_sqrtf((float)tden) * (1.0f + 0x1p-18f) + 1.0f;
     return min((int)fminf(s, 2147483520.0f), smax);   // (the largest float below 2^31)
@@ -1551,11 +1643,12 @@ __device__ inline uint32_t block_exscan_u32(uint32_t v, uint32_t* s_tmp, uint32_
 
 // Work items of the count and emit kernels: chunks of kNT consecutive entries of a tile list.
 __global__ __launch_bounds__(256) void k_tile_items(const uint32_t* __restrict__ tile_start, int T,
-                                                    uint32_t* __restrict__ items) {
+                                                    uint32_t* __restrict__ items, Counters* ctr) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T) return;
-    const uint32_t n = tile_start[t + 1] - tile_start[t];
-    items[t] = (n + kNT - 1) / kNT;
+    const uint32_t n = t < T ? tile_start[t + 1] - tile_start[t] : 0u;
+    const unsigned long long full = __ballot(n > 0u);
+    if ((threadIdx.x & 63) == 0 && full) atomicAdd(&ctr->tiles, (uint32_t)__popcll(full));
+    if (t < T) items[t] = (n + kNT - 1) / kNT;
 }
 
 // What is known to hide in a tile: each pixel's opaque key and the largest key of every run of four
@@ -1619,23 +1712,20 @@ __device__ inline bool line_hidden(const H& h, uint32_t nearest, int p, int n, b
 // its farthest one, so its key maximum is that key already, and k_tile_prep clears the others
 // (see kmax_seen for how the emit pass tells them apart).
 // 150k x 64 strands as 1000 thick hairs at 1080p: 99.7% of its 43 M fragments are hidden, and the
-// frame takes 0.32 ms instead of 3.49 (this pass 0.07, the shading 0.03 instead of 1.97).  A
-// combed groom at a middle view, where strands and thick hairs mix and a third of the fragments
-// is hidden: 1.01 instead of 1.14 ms.  Bound by the per-line coverage arithmetic (VALU).
+// frame takes 0.27 ms instead of 3.5 (this pass 0.06, the shading 0.03 instead of 1.97).  Mixed
+// frames have the pass where opaque_pays says so: locks of 100k strands at a middle view, thick
+// hairs up to 4 px wide, 78% of 12 M fragments hidden: 0.53 instead of 0.81 ms.  Bound by the
+// per-line coverage arithmetic (VALU).
 // first: only 4 kFirstLanes segments of every tile, spread over its list (a contiguous run of it
 // would hold the segments of a few neighbouring hairs, which may lie at the back).  A block is
 // bound by the latency of its lines' pixels, so this launch is short, and what it finds hides most
 // segments of the second one, which takes them all: 43 M fragments in 5 k chunks, 119 -> 20 + 45 us.
 constexpr int kFirstLanes = 16;
-__global__ __launch_bounds__(kNT) void k_opaque(FrameBufs f, CamConst cam, int first) {
+__device__ inline void opaque_item(const FrameBufs& f, const CamConst& cam, int first, uint32_t item) {
     __shared__ HideLds s_hide;
     __shared__ CovSetup s_cov[kNT];
     __shared__ uint8_t s_own[kNT / 64 * kCovLinesPerWave];
     __shared__ float4 s_iz[kNT];
-    const uint32_t n_items = f.item_start[f.T];
-    if (blockIdx.x >= n_items || f.ctr->cap_overflow) return;
-    if (!(__uint_as_float(f.ctr->max_hw_bits) > 0.5f + kOpaqueMargin)) return;
-    const uint32_t item = xcd_contiguous(blockIdx.x, n_items);
     const int t = threadIdx.x;
     const uint2 it = f.item_tab[item];
     if (first && it.y > 0) return;
@@ -1670,15 +1760,19 @@ __global__ __launch_bounds__(kNT) void k_opaque(FrameBufs f, CamConst cam, int f
     // (kmax_key: whatever the key, the count and emit passes take the same word for hiding)
     if (s_z[t] < z0) atomicMin(&f.pix_kmax[q], kmax_key(s_z[t]));
 }
+__global__ __launch_bounds__(kNT) void k_opaque(FrameBufs f, CamConst cam, int first) {
+    if (!(__uint_as_float(f.ctr->max_hw_bits) > 0.5f + kOpaqueMargin)) return;
+    for_each_item(f, true, [&](uint32_t item) { opaque_item(f, cam, first, item); });
+}
 
 // Count pass: per pixel the fragments that the frame stores and, in pix_off until k_tile_prep
 // writes the offsets, those it leaves out.  Each item adds its LDS-aggregated counts (stored in
 // the low half word, left out in the high one: an item has at most kNT fragments per pixel) to
 // the tile's pixels and keeps the returned base (its slice of every pixel's range).
-// ZC: the frame has an opaque pass, and leaves out what an opaque fragment hides.
+// ZC: the frame has an opaque pass, and leaves out what an opaque fragment hides (see launch_count).
 // TRIM: fragments without coverage are left out too (FrameBufs::trim).
 template <bool TRIM, bool ZC>
-__global__ __launch_bounds__(kNT) void k_count(FrameBufs f, CamConst cam) {
+__device__ inline void count_item(const FrameBufs& f, const CamConst& cam, uint32_t item) {
     __shared__ uint32_t s_cnt[kTilePix];
     __shared__ HideOf<ZC> s_hide[1];
     __shared__ uint32_t s_dr[ZC ? kTilePix : 1], s_dc[ZC ? kTilePix : 1];   // see below
@@ -1687,9 +1781,6 @@ __global__ __launch_bounds__(kNT) void k_count(FrameBufs f, CamConst cam) {
     __shared__ int s_vis[TRIM ? kNT : 1];   // |cross| up to which the segment's fragments have coverage
     __shared__ uint8_t s_own[kNT / 64 * kCovLinesPerWave];
     PHASE_BEGIN();
-    const uint32_t n_items = f.item_start[f.T];
-    if (blockIdx.x >= n_items || f.ctr->cap_overflow) return;
-    const uint32_t item = xcd_contiguous(blockIdx.x, n_items);
     const int t = threadIdx.x;
     const uint2 it = f.item_tab[item];
     const int tile = (int)it.x;
@@ -1749,6 +1840,10 @@ __global__ __launch_bounds__(kNT) void k_count(FrameBufs f, CamConst cam) {
     if (c) base = atomicAdd(&f.pix_cnt[q], c);
     f.item_base[(size_t)item * kTilePix + t] = base;
     PHASE_END(f.ctr, 0);
+}
+template <bool TRIM, bool ZC>
+__global__ __launch_bounds__(kNT) void k_count(FrameBufs f, CamConst cam) {
+    for_each_item(f, ZC, [&](uint32_t item) { count_item<TRIM, ZC>(f, cam, item); });
 }
 
 // The fragments a batch of a tile may take (a multiple of kNT, up to kCap).  A large frame fills
@@ -1942,7 +2037,8 @@ __global__ __launch_bounds__(kNT) void k_batch_records(FrameBufs f) {
 // frag_base[tile] + pix_off[pixel] + (the item's slice of the pixel) + local slot, and each
 // pixel's depth-key range (LDS-aggregated per item).
 // MIXED: a mixed-level frame, whose thick-hair pixels are marked in f.pix_thick.  ZC: the frame
-// has an opaque pass; the fragments stored are exactly those that the count pass counted.
+// has an opaque pass, or may have one (f.opaque == 2, where ctr->hides says: one kernel, its LDS has
+// room for both); the fragments stored are exactly those that the count pass counted.
 template <bool MIXED, bool ZC>
 __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
     __shared__ uint32_t s_cur[kTilePix], s_pos[kTilePix], s_kmin[kTilePix], s_kmax[kTilePix];
@@ -1954,6 +2050,7 @@ __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
     PHASE_BEGIN();
     const uint32_t n_items = f.item_start[f.T];
     if (blockIdx.x >= n_items || f.ctr->cap_overflow) return;
+    const bool hides = ZC && (f.opaque != 2 || f.ctr->hides != 0);
     const uint32_t item = xcd_contiguous(blockIdx.x, n_items);
     const int t = threadIdx.x;
     const uint2 it = f.item_tab[item];
@@ -1983,17 +2080,17 @@ __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
     if constexpr (ZC) {
         const uint32_t km = f.pix_kmax[q], z0 = kmax_hides(km) ? km : 0xFFFFFFFFu;
         const int gx = px0 + (t % kTile), gy = py0 + (t / kTile);
-        hide_setup(s_hide[0], gx < cam.W && gy < cam.H ? z0 : 0u);
+        if (hides) hide_setup(s_hide[0], gx < cam.W && gy < cam.H ? z0 : 0u);
     }
     auto drop = [&](int i0, int i1, int j0, int j1) {
-        return ZC && box_hidden(s_hide[0], nearest_key(s), i0, i1, j0, j1);
+        return hides && box_hidden(s_hide[0], nearest_key(s), i0, i1, j0, j1);
     };
     const uint32_t total = f.trim ? cov_setup<kVisible>(s, valid, px0, py0, cam.W, cam.H, s_cov, s_own, drop)
                                   : cov_setup<kAll>(s, valid, px0, py0, cam.W, cam.H, s_cov, s_own, drop);
     float4 iz;   // (the line's segment)
     wave_coverage(s_cov, s_own, total, [&](int p, int tnum, int tden, int, int) {
         const uint32_t key = depth_key_iz(iz.x, iz.y, tnum, tden, iz.z);
-        if (ZC && key > s_hide[0].z[ZC ? p : 0]) return;
+        if (hides && key > s_hide[0].z[ZC ? p : 0]) return;
         const uint32_t slot = atomicAdd(&s_cur[p], 1u);
         atomicMin(&s_kmin[p], key);
         atomicMax(&s_kmax[p], key);
@@ -2002,7 +2099,7 @@ __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
         f.frags[s_pos[p] + slot] = make_uint2(key, (id & 0xFFFFFFu) | ((uint32_t)p << 24));
     }, [&](int o, int p, int n, bool steep) {
         iz = s_iz[o];
-        return ZC && line_hidden(s_hide[0], nearest_key(iz), p, n, steep);
+        return hides && line_hidden(s_hide[0], nearest_key(iz), p, n, steep);
     });
     __syncthreads();
     if (s_cur[t]) {
@@ -3831,10 +3928,10 @@ static hipError_t allow_lds(const void* fn, int bytes) {
     return hipSuccess;
 }
 
-hipError_t launch_bins(const SegRec* seg, int32_t nseg, const CamConst& cam, const BinPlan& p, uint32_t* M,
-                       uint4* blk, uint32_t* tot, Counters* ctr, hipStream_t st) {
+hipError_t launch_bins(const SegRec* seg, int32_t nseg, const CamConst& cam, const BinPlan& p, bool areas, uint32_t* M,
+                       BlockStats* blk, uint32_t* tot, Counters* ctr, hipStream_t st) {
     const int ntx = (cam.W + kTile - 1) / kTile, nty = (cam.H + kTile - 1) / kTile, T = ntx * nty;
-    auto kernel = p.lanes > 1 ? &k_bin_count<kBinLanes> : &k_bin_count<1>;
+    auto kernel = p.lanes > 1 ? &k_bin_count<kBinLanes, false> : areas ? &k_bin_count<1, true> : &k_bin_count<1, false>;
     hipError_t e = allow_lds(reinterpret_cast<const void*>(kernel), 4 * p.range);
     if (e != hipSuccess) return e;
     for (int t0 = 0; t0 < T; t0 += p.range) {
@@ -3842,7 +3939,7 @@ hipError_t launch_bins(const SegRec* seg, int32_t nseg, const CamConst& cam, con
         hipLaunchKernelGGL(kernel, dim3(p.nb), dim3(kBinThreads), 4 * nt, st, seg, nseg, p.per_block, ntx, nty,
                            t0, nt, M, blk);
     }
-    hipLaunchKernelGGL(k_bin_offsets, dim3(blocks_for(T, 64)), dim3(1024), 0, st, M, p.nb, T, tot, blk, ctr);
+    hipLaunchKernelGGL(k_bin_offsets, dim3(blocks_for(T, 64)), dim3(1024), 0, st, M, p.nb, T, tot, blk, ctr, areas);
     return hipGetLastError();
 }
 
@@ -3902,22 +3999,32 @@ hipError_t launch_sum_tiles(const FrameBufs& f, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_tile_items(const uint32_t* tile_start, int T, uint32_t* items, hipStream_t st) {
-    hipLaunchKernelGGL(k_tile_items, dim3(blocks_for(T, 256)), dim3(256), 0, st, tile_start, T, items);
+hipError_t launch_tile_items(const uint32_t* tile_start, int T, uint32_t* items, Counters* ctr, hipStream_t st) {
+    hipLaunchKernelGGL(k_tile_items, dim3(blocks_for(T, 256)), dim3(256), 0, st, tile_start, T, items, ctr);
     return hipGetLastError();
 }
 
-hipError_t launch_count(const FrameBufs& f, const CamConst& cam, uint32_t grid, hipStream_t st) {
+// Mixed frames (f.opaque == 2) launch both variants, and the device chooses: the passes not chosen only
+// leave.  Their blocks take items in turn, so that there are few to leave (a warm grid has the size of the
+// largest frame so far: 20 k blocks that leave took 8 us, 4608 take 3), and enough for items of very
+// different cost (2048 blocks for the 22 k items of a frame of 3 M rows: 130 us more, 8192: 4 us).
+hipError_t launch_count(const FrameBufs& f, const CamConst& cam, uint32_t grid, int32_t rows, hipStream_t st) {
     if (grid == 0) return hipSuccess;
+    const dim3 b(kNT);
+    auto blocks = [&](uint32_t most) {
+        return f.opaque == 2 ? std::min(grid, std::min(most, std::max(1024u, (uint32_t)rows / 16))) : grid;
+    };
     if (f.opaque) {
-        hipLaunchKernelGGL(k_opaque, dim3(grid), dim3(kNT), 0, st, f, cam, 1);
-        hipLaunchKernelGGL(k_opaque, dim3(grid), dim3(kNT), 0, st, f, cam, 0);
-        if (f.trim) hipLaunchKernelGGL((k_count<true, true>), dim3(grid), dim3(kNT), 0, st, f, cam);
-        else hipLaunchKernelGGL((k_count<false, true>), dim3(grid), dim3(kNT), 0, st, f, cam);
-    } else if (f.trim) {
-        hipLaunchKernelGGL((k_count<true, false>), dim3(grid), dim3(kNT), 0, st, f, cam);
-    } else {
-        hipLaunchKernelGGL((k_count<false, false>), dim3(grid), dim3(kNT), 0, st, f, cam);
+        const dim3 g(blocks(4608));
+        hipLaunchKernelGGL(k_opaque, g, b, 0, st, f, cam, 1);
+        hipLaunchKernelGGL(k_opaque, g, b, 0, st, f, cam, 0);
+        if (f.trim) hipLaunchKernelGGL((k_count<true, true>), g, b, 0, st, f, cam);
+        else hipLaunchKernelGGL((k_count<false, true>), g, b, 0, st, f, cam);
+    }
+    if (f.opaque != 1) {
+        const dim3 g(blocks(8192));
+        if (f.trim) hipLaunchKernelGGL((k_count<true, false>), g, b, 0, st, f, cam);
+        else hipLaunchKernelGGL((k_count<false, false>), g, b, 0, st, f, cam);
     }
     return hipGetLastError();
 }
@@ -4017,7 +4124,7 @@ hipError_t launch_select(const HierDev& h, const int32_t* levels, uint32_t* cnt,
         hipLaunchKernelGGL(k_select, dim3(1), dim3(1024), 0, st, h, levels, sel_start);
         return hipGetLastError();
     }
-    hipError_t e = launch_fill_u32(sel_start + gk + 1, 0u, 1, st);
+    hipError_t e = launch_fill_u32(sel_start + gk + 1, 0u, 2, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_sel_count, dim3(blocks_for(gk, 256)), dim3(256), 0, st, h, levels, cnt, sel_start + gk + 1);
     if ((e = hipGetLastError()) != hipSuccess) return e;

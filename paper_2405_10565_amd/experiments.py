@@ -80,6 +80,7 @@ def lod_sweep(hctx: B.Context, scale: float = 1.0, repeats: int = 20):
         rmse, psnr = _rgb_error(img, ref)
         out["levels"].append({"level": level, "clusters": None if level == 0 else int(counts[level]),
                               "segments": int(st["segments"]), "fragments": int(st["fragments"]),
+                              "stored": hctx.debug_stored(ws),
                               "frame_ms_p50": round(float(np.percentile(ms, 50)), 4),
                               "shading_ms_p50": round(float(np.percentile(tile, 50)), 4),
                               "rmse": round(rmse, 6), "psnr_db": round(psnr, 2)})
