@@ -567,22 +567,28 @@ __global__ __launch_bounds__(1024) void k_select(HierDev h, const int32_t* __res
 // later passes (100k strands in locks that fill half the screen, 3% of them hidden: 1.68 ms without it,
 // 1.91 with it), and 12 us at least, so: m >= 1/2, and 180,000 hidden fragments.  249 views of five
 // grooms with thick hairs up to 1.5 .. 25 px wide take, in the geometric mean, 0.947 of the time that they
-// take without the pass (0.34 at best, 13 us more at worst) and 0.944 of that with it in every view
-// (0.75 at best, 30 us more at worst).
+// take without the pass (0.34 at best, 18 us more at worst) and 0.946 of that with it in every view
+// (0.74 at best, 35 us of 2.1 ms more at worst).
 __device__ inline bool opaque_pays(unsigned long long area_opaque, unsigned long long area_all, uint32_t tiles) {
     const float m = (float)area_opaque * (1.0f / 65536.0f) / (float)max(tiles, 1u);
     if (!(m >= 0.5f)) return false;
     const float hidden = 1.0f - (1.0f - expf(-m)) / m;
     return hidden * ((float)area_all * (1.0f / 256.0f)) >= 180000.0f;
 }
-// The items of a block of the opaque and count passes (with: for frames with an opaque pass; see
-// launch_count).
-template <class F> __device__ inline void for_each_item(const FrameBufs& f, bool with, F&& item) {
+// The items of a block of the opaque and count passes: one, or (GATED, f.opaque == 2) where the device
+// chose the variant (with: for frames with an opaque pass) several in turn, see launch_count.  (The loop
+// takes 18 more VGPRs and a tenth of the time of a count pass that has one item per block.)
+template <bool GATED, class F> __device__ inline void for_each_item(const FrameBufs& f, bool with, F&& item) {
     const uint32_t n_items = f.item_start[f.T];
-    if (blockIdx.x >= n_items || f.ctr->cap_overflow || (f.opaque == 2 && (f.ctr->hides != 0) != with)) return;
-    for (uint32_t b = blockIdx.x; b < n_items; b += gridDim.x) {
-        if (b != blockIdx.x) __syncthreads();
-        item(xcd_contiguous(b, n_items));
+    if (blockIdx.x >= n_items || f.ctr->cap_overflow) return;
+    if constexpr (!GATED) {
+        item(xcd_contiguous(blockIdx.x, n_items));
+    } else {
+        if ((f.ctr->hides != 0) != with) return;
+        for (uint32_t b = blockIdx.x; b < n_items; b += gridDim.x) {
+            if (b != blockIdx.x) __syncthreads();
+            item(xcd_contiguous(b, n_items));
+        }
     }
 }
 
@@ -1760,9 +1766,9 @@ __device__ inline void opaque_item(const FrameBufs& f, const CamConst& cam, int 
     // (kmax_key: whatever the key, the count and emit passes take the same word for hiding)
     if (s_z[t] < z0) atomicMin(&f.pix_kmax[q], kmax_key(s_z[t]));
 }
-__global__ __launch_bounds__(kNT) void k_opaque(FrameBufs f, CamConst cam, int first) {
+template <bool GATED> __global__ __launch_bounds__(kNT) void k_opaque(FrameBufs f, CamConst cam, int first) {
     if (!(__uint_as_float(f.ctr->max_hw_bits) > 0.5f + kOpaqueMargin)) return;
-    for_each_item(f, true, [&](uint32_t item) { opaque_item(f, cam, first, item); });
+    for_each_item<GATED>(f, true, [&](uint32_t item) { opaque_item(f, cam, first, item); });
 }
 
 // Count pass: per pixel the fragments that the frame stores and, in pix_off until k_tile_prep
@@ -1841,9 +1847,9 @@ __device__ inline void count_item(const FrameBufs& f, const CamConst& cam, uint3
     f.item_base[(size_t)item * kTilePix + t] = base;
     PHASE_END(f.ctr, 0);
 }
-template <bool TRIM, bool ZC>
+template <bool TRIM, bool ZC, bool GATED>
 __global__ __launch_bounds__(kNT) void k_count(FrameBufs f, CamConst cam) {
-    for_each_item(f, ZC, [&](uint32_t item) { count_item<TRIM, ZC>(f, cam, item); });
+    for_each_item<GATED>(f, ZC, [&](uint32_t item) { count_item<TRIM, ZC>(f, cam, item); });
 }
 
 // The fragments a batch of a tile may take (a multiple of kNT, up to kCap).  A large frame fills
@@ -2050,7 +2056,7 @@ __global__ __launch_bounds__(kNT) void k_emit(FrameBufs f, CamConst cam) {
     PHASE_BEGIN();
     const uint32_t n_items = f.item_start[f.T];
     if (blockIdx.x >= n_items || f.ctr->cap_overflow) return;
-    const bool hides = ZC && (f.opaque != 2 || f.ctr->hides != 0);
+    const bool hides = ZC && (!MIXED || f.opaque != 2 || f.ctr->hides != 0);
     const uint32_t item = xcd_contiguous(blockIdx.x, n_items);
     const int t = threadIdx.x;
     const uint2 it = f.item_tab[item];
@@ -3681,9 +3687,9 @@ __global__ __launch_bounds__(kNT) void k_dom_first(FrameBufs f, CamConst cam) {
     if (s_z[t] < z0) atomicMin(&f.pix_kmin[q], s_z[t]);
 }
 
-// THICK: the level can hold thick hairs.  The launch adds the layers [l0, l0 + nl) of K, with acc as
-// [tile][nl][texel] (see launch_dom_map).  Dynamic LDS: nl x kTilePix sums.
-template <bool THICK>
+// THICK: the level can hold thick hairs.  The launch adds the layers [l0, l0 + nl) of K (ALL: l0 = 0, nl = K),
+// with acc as [tile][nl][texel] (see launch_dom_map).  Dynamic LDS: nl x kTilePix sums.
+template <bool THICK, bool ALL>
 __global__ __launch_bounds__(kNT) void k_dom_layers(FrameBufs f, CamConst cam, LevelDev lv,
                                                     const ShadeRec* __restrict__ rows,
                                                     const DomGrid* __restrict__ grid, int K, int l0, int nl, float delta,
@@ -3736,8 +3742,11 @@ __global__ __launch_bounds__(kNT) void k_dom_layers(FrameBufs f, CamConst cam, L
             // (rounded like the keys of k_dom_first, so that the first hit itself lies in layer 0)
             const float tt = div_rcp((float)tnum, (float)tden, rc.y);
             const float iz = e.x + tt * (e.y - e.x);
-            const int layer = min(K - 1, (int)floorf(div_by(s_iz0[p] - iz, delta, rdelta))) - l0;
-            if ((unsigned)layer >= (unsigned)nl) return;
+            int layer = min(K - 1, (int)floorf(div_by(s_iz0[p] - iz, delta, rdelta)));
+            if (!ALL) {
+                layer -= l0;
+                if ((unsigned)layer >= (unsigned)nl) return;
+            }
             const float dl = div_rcp(fabsf((float)cr), e.w, rc.x) * (1.0f / 16.0f);
             const float hw = e.z;
             float c = fminf(fmaxf(fminf(dl + hw, 0.5f) - fmaxf(dl - hw, -0.5f), 0.0f), 1.0f);
@@ -3894,7 +3903,9 @@ hipError_t launch_dom_map(const FrameBufs& f, const CamConst& cam, const LevelDe
                           const DomGrid* grid, int32_t K, int32_t nl, float delta, float rdelta, uint32_t n_items,
                           unsigned long long* acc, float4* tex, hipStream_t st) {
     // n_items: the grid (at least the view's items, which the kernels read)
-    auto layers = rows || lv.kind != 0 ? &k_dom_layers<true> : &k_dom_layers<false>;
+    const bool thick = rows || lv.kind != 0;
+    auto layers = nl == K ? (thick ? &k_dom_layers<true, true> : &k_dom_layers<false, true>)
+                          : (thick ? &k_dom_layers<true, false> : &k_dom_layers<false, false>);
     if (n_items) hipLaunchKernelGGL(k_dom_first, dim3(n_items), dim3(kNT), 0, st, f, cam);
     // all layers in one pass, or one after the other into the same sums (which then run on)
     for (int l0 = 0; l0 < K; l0 += nl) {
@@ -4004,28 +4015,32 @@ hipError_t launch_tile_items(const uint32_t* tile_start, int T, uint32_t* items,
     return hipGetLastError();
 }
 
+template <bool TRIM>
+static void launch_count_trim(const FrameBufs& f, const CamConst& cam, uint32_t grid, uint32_t most, hipStream_t st) {
+    const dim3 b(kNT);
+    if (f.opaque == 0) {
+        hipLaunchKernelGGL((k_count<TRIM, false, false>), dim3(grid), b, 0, st, f, cam);
+    } else if (f.opaque == 1) {
+        hipLaunchKernelGGL(k_opaque<false>, dim3(grid), b, 0, st, f, cam, 1);
+        hipLaunchKernelGGL(k_opaque<false>, dim3(grid), b, 0, st, f, cam, 0);
+        hipLaunchKernelGGL((k_count<TRIM, true, false>), dim3(grid), b, 0, st, f, cam);
+    } else {
+        const dim3 with(std::min(grid, std::min(most, 4608u))), without(std::min(grid, std::min(most, 8192u)));
+        hipLaunchKernelGGL(k_opaque<true>, with, b, 0, st, f, cam, 1);
+        hipLaunchKernelGGL(k_opaque<true>, with, b, 0, st, f, cam, 0);
+        hipLaunchKernelGGL((k_count<TRIM, true, true>), with, b, 0, st, f, cam);
+        hipLaunchKernelGGL((k_count<TRIM, false, true>), without, b, 0, st, f, cam);
+    }
+}
 // Mixed frames (f.opaque == 2) launch both variants, and the device chooses: the passes not chosen only
 // leave.  Their blocks take items in turn, so that there are few to leave (a warm grid has the size of the
 // largest frame so far: 20 k blocks that leave took 8 us, 4608 take 3), and enough for items of very
 // different cost (2048 blocks for the 22 k items of a frame of 3 M rows: 130 us more, 8192: 4 us).
 hipError_t launch_count(const FrameBufs& f, const CamConst& cam, uint32_t grid, int32_t rows, hipStream_t st) {
     if (grid == 0) return hipSuccess;
-    const dim3 b(kNT);
-    auto blocks = [&](uint32_t most) {
-        return f.opaque == 2 ? std::min(grid, std::min(most, std::max(1024u, (uint32_t)rows / 16))) : grid;
-    };
-    if (f.opaque) {
-        const dim3 g(blocks(4608));
-        hipLaunchKernelGGL(k_opaque, g, b, 0, st, f, cam, 1);
-        hipLaunchKernelGGL(k_opaque, g, b, 0, st, f, cam, 0);
-        if (f.trim) hipLaunchKernelGGL((k_count<true, true>), g, b, 0, st, f, cam);
-        else hipLaunchKernelGGL((k_count<false, true>), g, b, 0, st, f, cam);
-    }
-    if (f.opaque != 1) {
-        const dim3 g(blocks(8192));
-        if (f.trim) hipLaunchKernelGGL((k_count<true, false>), g, b, 0, st, f, cam);
-        else hipLaunchKernelGGL((k_count<false, false>), g, b, 0, st, f, cam);
-    }
+    const uint32_t most = std::max(1024u, (uint32_t)rows / 16);
+    if (f.trim) launch_count_trim<true>(f, cam, grid, most, st);
+    else launch_count_trim<false>(f, cam, grid, most, st);
     return hipGetLastError();
 }
 
