@@ -18,7 +18,10 @@
  *   - `stream` is a hipStream_t (NULL = the legacy default stream).  Every kernel of a call
  *     runs on it; calls that read results back to the host synchronise it.
  *   - memory the library allocates (assets, LoD levels, workspaces) counts against the
- *     context's HBM budget; exceeding it returns HAIR_ENOMEM and allocates nothing.
+ *     context's HBM budget; exceeding it returns HAIR_ENOMEM and allocates nothing.  Before
+ *     that the context's other workspaces give back what they hold for speed alone, until
+ *     hair_ws_set_limit or hair_ws_trim (one in another thread's call at that call's end; one
+ *     with a frame of hair_render_async keeps it).
  *   - a context may be used from several threads; renders on distinct workspaces may run
  *     concurrently.  One workspace serves one call at a time, and a workspace holding a frame
  *     of hair_render_async serves no other call until hair_ws_finish.

@@ -3,6 +3,8 @@
 // orchestration around the kernels of hair_kernels.hip.
 #include <algorithm>
 #include <array>
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -11,6 +13,7 @@
 #include <memory>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "hair_fastmath_coef.h"
@@ -35,6 +38,7 @@ int fail(int code, const char* fmt, ...) {
 struct DevBuf {
     void* p = nullptr;
     size_t bytes = 0;
+    size_t need = 0;   // the most that a frame has asked for since the allocation (workspaces)
     template <class T> T* as() const { return static_cast<T*>(p); }
 };
 
@@ -103,6 +107,9 @@ struct hair_ctx {
     int next_id = 1;
     hair_ws* default_ws = nullptr;
     hair_ws* fixed_ws = nullptr;   // frames of hair_render_noalloc (buffers in the static scratch)
+    std::mutex ws_mu;              // taken after a workspace's mu and before mu
+    std::vector<hair_ws*> workspaces;   // all but fixed_ws (reclaim_idle)
+    std::atomic<int> starved{0};   // allocations that wait for other workspaces' memory
 };
 
 struct hair_ws {
@@ -119,7 +126,8 @@ struct hair_ws {
     int32_t dom_R = 0, dom_K = 0, dom_n = 0;  // last shadowed render: resolution, layers, maps
     int32_t dom_light[HAIR_MAX_LIGHTS] = {};  // map index of each light, -1 if unshadowed
     FrameCaps caps = {};                      // buffer capacities of warm frames (0: none yet)
-    bool lean = false;                        // memory ran out: buffers no larger than they have to be (ws_lean)
+    size_t lean_bin = 0, lean_pair = 0;       // what lean frames need of bin_m and pix_pair
+    std::atomic<bool> lean{false};            // memory ran out: buffers no larger than they have to be (ws_lean)
     hipEvent_t ev[7] = {};
     bool events = false;
     int64_t last_nseg = 0, last_ntiles = 0, last_pairs = 0, last_stored = 0;
@@ -161,7 +169,7 @@ int dev_fail(hair_ctx* ctx, hipError_t e, const char* what) {
         if (_e != hipSuccess) return dev_fail(ctx, _e, what); \
     } while (0)
 
-int ctx_alloc(hair_ctx* ctx, DevBuf& b, size_t bytes, hair_ws* ws = nullptr) {
+int dev_alloc(hair_ctx* ctx, DevBuf& b, size_t bytes, hair_ws* ws) {
     if (bytes == 0) bytes = 4;
     {
         std::lock_guard<std::mutex> g(ctx->mu);
@@ -194,9 +202,10 @@ void ctx_free(hair_ctx* ctx, DevBuf& b, hair_ws* ws = nullptr) {
     std::lock_guard<std::mutex> g(ctx->mu);
     ctx->used -= b.bytes;
     if (ws) ws->held -= b.bytes;
-    b.p = nullptr;
-    b.bytes = 0;
+    b = DevBuf{};
 }
+
+int ctx_alloc(hair_ctx* ctx, DevBuf& b, size_t bytes, hair_ws* ws = nullptr, const hair_ws* held = nullptr);
 
 // Every device buffer a workspace can hold.
 std::array<DevBuf*, 34> ws_buffers(hair_ws* ws) {
@@ -225,29 +234,113 @@ int arena_take(hair_ws* ws, DevBuf& b, size_t bytes) {
 // which starts over when memory runs out; between frames ws_need_lean.
 int ws_need(hair_ws* ws, DevBuf& b, size_t bytes) {
     if (ws->arena) return arena_take(ws, b, bytes);
-    if (b.bytes >= bytes && b.p) return HAIR_OK;
-    ctx_free(ws->ctx, b, ws);
-    return ctx_alloc(ws->ctx, b, ws->lean ? bytes : bytes + bytes / 4 + 256, ws);
+    if (b.bytes < bytes || !b.p) {
+        ctx_free(ws->ctx, b, ws);
+        const int rc = ctx_alloc(ws->ctx, b, ws->lean ? bytes : bytes + bytes / 4 + 256, ws);
+        if (rc) return rc;
+    }
+    b.need = std::max({b.need, bytes, size_t(4)});
+    return HAIR_OK;
+}
+
+// The buffers that a frame fills before it reads them.  (Rows, segment records and shadow maps may be
+// a frame's inputs.)
+std::vector<DevBuf*> ws_frame_buffers(hair_ws* ws) {
+    std::vector<DevBuf*> v;
+    for (DevBuf* b : ws_buffers(ws)) {
+        bool keep = false;
+        for (const DevBuf* k : {&ws->seg, &ws->shade, &ws->sel_cnt, &ws->sel_start, &ws->sel, &ws->sel_tmp, &ws->pieces,
+                                &ws->dom_tex, &ws->dom_grid, &ws->dom_part})
+            keep = keep || b == k;
+        if (!keep) v.push_back(b);
+    }
+    return v;
 }
 
 // Memory ran out (a workspace's limit, the context's budget or the device): give back the frame's
 // buffers, and until the limit is set anew or the workspace is trimmed make them no larger than
 // they have to be.  What a frame holds for speed alone is less than the headroom left out (small
 // batches add up to 16 bytes of table per 128 fragments of 8 bytes each) or is left out too (the
-// layer sums of a shadow map).  Lean frames give the same results, bit for bit.  (Rows, segment
-// records and shadow maps stay: they may be a frame's inputs.  hipFree waits for the kernels of a
-// frame that is given up.)
+// layer sums of a shadow map).  Lean frames give the same results, bit for bit.  (hipFree waits for
+// the kernels of a frame that is given up.)
 void ws_lean(hair_ws* ws) {
     ws->lean = true;
     if (ws->arena) return;
     ws->caps = FrameCaps{};
-    for (DevBuf* b : ws_buffers(ws)) {
-        bool keep = false;
-        for (const DevBuf* k : {&ws->seg, &ws->shade, &ws->sel_cnt, &ws->sel_start, &ws->sel, &ws->sel_tmp, &ws->pieces,
-                                &ws->dom_tex, &ws->dom_grid, &ws->dom_part})
-            keep = keep || b == k;
-        if (!keep) ctx_free(ws->ctx, *b, ws);
+    ws->lean_bin = ws->lean_pair = 0;
+    for (DevBuf* b : ws_frame_buffers(ws)) ctx_free(ws->ctx, *b, ws);
+}
+
+// Another workspace or an asset of the context is short of memory: make this one lean, and give back
+// what its frames so far do not need then.  What they need it keeps, and the budget counts the
+// smaller sizes throughout, so that nobody else takes them meanwhile.
+void ws_give(hair_ctx* ctx, hair_ws* ws) {
+    ws->lean = true;
+    std::vector<std::pair<DevBuf*, size_t>> sizes;
+    size_t had = 0, keep = 0;
+    for (DevBuf* b : ws_frame_buffers(ws)) {
+        if (!b->p && !(b == &ws->pix_pair && ws->dom_acc.p)) continue;
+        const size_t n = b == &ws->dom_acc ? 0 : b == &ws->bin_m ? ws->lean_bin : b == &ws->pix_pair ? ws->lean_pair : b->need;
+        sizes.emplace_back(b, n);
+        had += b->bytes;
+        keep += n;
     }
+    if (keep >= had) return;
+    {
+        std::lock_guard<std::mutex> g(ctx->mu);
+        ctx->used -= had - keep;
+        ws->held -= had - keep;
+    }
+    for (auto& [b, n] : sizes) {
+        if (b->bytes == n) continue;
+        (void)hipFree(b->p);
+        *b = DevBuf{};
+        if (n == 0) continue;
+        if (hipMalloc(&b->p, n) == hipSuccess) {
+            b->bytes = b->need = n;
+            continue;
+        }
+        (void)hipGetLastError();
+        b->p = nullptr;
+        std::lock_guard<std::mutex> g(ctx->mu);
+        ctx->used -= n;
+        ws->held -= n;
+    }
+}
+
+// The context's workspaces give back what they hold for speed (one with a deferred frame keeps it).
+// Whether a workspace that could give something is in another thread's call.
+bool reclaim_idle(hair_ctx* ctx, const hair_ws* held) {
+    std::lock_guard<std::mutex> g(ctx->ws_mu);
+    bool busy = false;
+    for (hair_ws* ws : ctx->workspaces) {
+        if (ws == held || ws->lean) continue;
+        std::unique_lock<std::mutex> lock(ws->mu, std::try_to_lock);
+        if (!lock.owns_lock()) busy = true;
+        else if (!ws->pending.active) ws_give(ctx, ws);
+    }
+    return busy;
+}
+
+// An allocation of an asset, or (ws) of a workspace's buffer; held: the workspace whose lock the
+// caller has.  Where the budget or the device has no more, the other workspaces' memory is tried (for
+// a workspace only once it is lean itself): the idle ones' at once, that of another thread's at the
+// end of its call or when its next frame begins (run_frame).  Lean workspaces have nothing to give,
+// so two never wait for each other.
+int ctx_alloc(hair_ctx* ctx, DevBuf& b, size_t bytes, hair_ws* ws, const hair_ws* held) {
+    int rc = dev_alloc(ctx, b, bytes, ws);
+    const bool own_limit = ws && ws->max_bytes && ws->held + bytes > ws->max_bytes;
+    if (rc != HAIR_ENOMEM || own_limit || (ws && !ws->lean)) return rc;
+    const auto end = std::chrono::steady_clock::now() + std::chrono::seconds(2);
+    ctx->starved.fetch_add(1);
+    for (;;) {
+        const bool busy = reclaim_idle(ctx, ws ? ws : held);
+        rc = dev_alloc(ctx, b, bytes, ws);
+        if (rc != HAIR_ENOMEM || !busy || std::chrono::steady_clock::now() > end) break;
+        std::this_thread::sleep_for(std::chrono::microseconds(100));
+    }
+    ctx->starved.fetch_sub(1);
+    return rc;
 }
 
 int ws_need_lean(hair_ws* ws, DevBuf& b, size_t bytes) {
@@ -478,10 +571,12 @@ int find_level(hair_ctx* ctx, int32_t asset, int32_t level, Asset** a_out, Level
 
 hair_ws* ws_or_default(hair_ctx* ctx, hair_ws* ws) {
     if (ws) return ws;
+    std::lock_guard<std::mutex> gw(ctx->ws_mu);
     std::lock_guard<std::mutex> g(ctx->mu);
     if (!ctx->default_ws) {
         ctx->default_ws = new hair_ws();
         ctx->default_ws->ctx = ctx;
+        ctx->workspaces.push_back(ctx->default_ws);
     }
     return ctx->default_ws;
 }
@@ -601,6 +696,8 @@ int frame_passes(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv,
     if ((rc = ws_need(ws, ws->scan_tmp, 4 * exscan_scratch_words(T)))) return rc;
     if ((rc = ws_need(ws, ws->tile_cnt, 4ull * T))) return rc;
     if ((rc = ws_need(ws, ws->tile_start, 4ull * (T + 1)))) return rc;
+    ws->lean_bin = std::max<size_t>(ws->lean_bin, 4ull * bin_plan(lv.nseg, T).nb * T);
+    ws->lean_pair = std::max<size_t>(ws->lean_pair, 8 * TP);
     if ((rc = ws_need(ws, ws->bin_m, 4ull * plan.nb * T))) return rc;
     if ((rc = ws_need(ws, ws->bin_blk, sizeof(BlockStats) * plan.nb))) return rc;
     if ((rc = ws_need(ws, ws->ctr, sizeof(Counters)))) return rc;
@@ -838,6 +935,7 @@ int run_frame(hair_ctx* ctx, hair_ws* ws, const Asset& a, const LevelDev& lv, co
         return frame_passes(ctx, ws, a, lv, cam, lights, n_lights, rgba, dbg, st, out, tiles_too, grad, hier, sel, dom,
                             views, tess, cold, defer);
     };
+    if (ctx->starved && !ws->lean && !ws->arena && !ws->pending.active) ws_give(ctx, ws);   // (another thread is short of memory)
     int rc = passes();
     if (rc != HAIR_ENOMEM || ws->lean) return rc;
     ws_lean(ws);
@@ -987,6 +1085,10 @@ int hair_ws_create(hair_ctx* ctx, uint64_t max_bytes, hair_ws** out) {
     hair_ws* ws = new hair_ws();
     ws->ctx = ctx;
     ws->max_bytes = max_bytes;
+    {
+        std::lock_guard<std::mutex> g(ctx->ws_mu);
+        ctx->workspaces.push_back(ws);
+    }
     *out = ws;
     return HAIR_OK;
 }
@@ -994,6 +1096,10 @@ int hair_ws_create(hair_ctx* ctx, uint64_t max_bytes, hair_ws** out) {
 int hair_ws_destroy(hair_ws* ws) {
     if (!ws) return fail(HAIR_EINVAL, "null workspace");
     hair_ctx* ctx = ws->ctx;
+    {
+        std::lock_guard<std::mutex> g(ctx->ws_mu);
+        ctx->workspaces.erase(std::remove(ctx->workspaces.begin(), ctx->workspaces.end(), ws), ctx->workspaces.end());
+    }
     if (ctx->device >= 0) (void)hipSetDevice(ctx->device);
     // a frame of hair_render_async still reads and writes the buffers: let it end first
     if (ws->pending.active && !ws->pending.done && ws->events) (void)hipEventSynchronize(ws->ev[1]);
@@ -1034,6 +1140,7 @@ int hair_ws_trim(hair_ws* ws) {
     if (ctx->device >= 0) HIP_TRY(ctx, hipSetDevice(ctx->device), "hipSetDevice");
     for (DevBuf* b : ws_buffers(ws)) ctx_free(ctx, *b, ws);
     ws->caps = FrameCaps{};
+    ws->lean_bin = ws->lean_pair = 0;
     ws->dom_n = 0;
     ws->lean = false;
     return HAIR_OK;
@@ -2039,9 +2146,9 @@ int hair_debug_fragments(hair_ctx* ctx, hair_ws* ws, int32_t asset, int32_t leve
     DevBuf img, dc, dk, ds, da, dh;
     const size_t ent = (size_t)npx * stride;
     auto cleanup = [&]() { for (DevBuf* b : {&img, &dc, &dk, &ds, &da, &dh}) ctx_free(ctx, *b); };
-    if ((rc = ctx_alloc(ctx, img, 16ull * cam->width * cam->height)) || (rc = ctx_alloc(ctx, dc, 4ull * npx)) ||
-        (rc = ctx_alloc(ctx, dk, 4 * ent)) || (rc = ctx_alloc(ctx, ds, 4 * ent)) || (rc = ctx_alloc(ctx, da, 4 * ent)) ||
-        (rc = ctx_alloc(ctx, dh, 4 * ent))) {
+    auto need = [&](DevBuf& b, size_t bytes) { return ctx_alloc(ctx, b, bytes, nullptr, ws); };
+    if ((rc = need(img, 16ull * cam->width * cam->height)) || (rc = need(dc, 4ull * npx)) || (rc = need(dk, 4 * ent)) ||
+        (rc = need(ds, 4 * ent)) || (rc = need(da, 4 * ent)) || (rc = need(dh, 4 * ent))) {
         cleanup();
         return rc;
     }
