@@ -566,9 +566,9 @@ __global__ __launch_bounds__(1024) void k_select(HierDev h, const int32_t* __res
 // 1 - (1 - e^-m) / m of the fragments.  The pass costs a frame what a quarter of its fragments cost the
 // later passes (100k strands in locks that fill half the screen, 3% of them hidden: 1.68 ms without it,
 // 1.91 with it), and 12 us at least, so: m >= 1/2, and 180,000 hidden fragments.  249 views of five
-// grooms with thick hairs up to 1.5 .. 25 px wide take, in the geometric mean, 0.947 of the time that they
-// take without the pass (0.34 at best, 18 us more at worst) and 0.946 of that with it in every view
-// (0.74 at best, 35 us of 2.1 ms more at worst).
+// grooms with thick hairs up to 1.5 .. 25 px wide take, in the geometric mean, 0.948 of the time that they
+// take without the pass (0.35 at best, 20 us more at worst) and 0.944 of that with it in every view
+// (0.72 at best, 11 us more at worst).
 __device__ inline bool opaque_pays(unsigned long long area_opaque, unsigned long long area_all, uint32_t tiles) {
     const float m = (float)area_opaque * (1.0f / 65536.0f) / (float)max(tiles, 1u);
     if (!(m >= 0.5f)) return false;
@@ -4025,7 +4025,7 @@ static void launch_count_trim(const FrameBufs& f, const CamConst& cam, uint32_t 
         hipLaunchKernelGGL(k_opaque<false>, dim3(grid), b, 0, st, f, cam, 0);
         hipLaunchKernelGGL((k_count<TRIM, true, false>), dim3(grid), b, 0, st, f, cam);
     } else {
-        const dim3 with(std::min(grid, std::min(most, 4608u))), without(std::min(grid, std::min(most, 8192u)));
+        const dim3 with(std::min(grid, std::min(most, 12288u))), without(std::min(grid, std::min(most, 8192u)));
         hipLaunchKernelGGL(k_opaque<true>, with, b, 0, st, f, cam, 1);
         hipLaunchKernelGGL(k_opaque<true>, with, b, 0, st, f, cam, 0);
         hipLaunchKernelGGL((k_count<TRIM, true, true>), with, b, 0, st, f, cam);
@@ -4034,8 +4034,9 @@ static void launch_count_trim(const FrameBufs& f, const CamConst& cam, uint32_t 
 }
 // Mixed frames (f.opaque == 2) launch both variants, and the device chooses: the passes not chosen only
 // leave.  Their blocks take items in turn, so that there are few to leave (a warm grid has the size of the
-// largest frame so far: 20 k blocks that leave took 8 us, 4608 take 3), and enough for items of very
-// different cost (2048 blocks for the 22 k items of a frame of 3 M rows: 130 us more, 8192: 4 us).
+// largest frame so far: 20 k blocks that leave took 8 us, 12288 take 4.6), and enough for items of very
+// different cost (2048 blocks for the 22 k items of a frame of 3 M rows: 130 us more, 8192: 4 us; the two
+// opaque launches of a frame of 14 k items: 4608 blocks 57 us, 12288 50, a block each without a choice 45).
 hipError_t launch_count(const FrameBufs& f, const CamConst& cam, uint32_t grid, int32_t rows, hipStream_t st) {
     if (grid == 0) return hipSuccess;
     const uint32_t most = std::max(1024u, (uint32_t)rows / 16);
