@@ -566,32 +566,15 @@ __global__ __launch_bounds__(1024) void k_select(HierDev h, const int32_t* __res
 // 1 - (1 - e^-m) / m of the fragments.  The pass costs a frame what a quarter of its fragments cost the
 // later passes (100k strands in locks that fill half the screen, 3% of them hidden: 1.68 ms without it,
 // 1.91 with it), and 12 us at least, so: m >= 1/2, and 180,000 hidden fragments.  249 views of five
-// grooms with thick hairs up to 1.5 .. 25 px wide take, in the geometric mean, 0.948 of the time that they
-// take without the pass (0.35 at best, 20 us more at worst) and 0.944 of that with it in every view
-// (0.72 at best, 11 us more at worst).
+// grooms with thick hairs up to 1.5 .. 25 px wide take, in the geometric mean, 0.940 of the time that they
+// take without the pass (0.35 at best, 29 us of 1.09 ms more at worst) and 0.938 of that with it in every
+// view (0.74 at best, 9 us more at worst).
 __device__ inline bool opaque_pays(unsigned long long area_opaque, unsigned long long area_all, uint32_t tiles) {
     const float m = (float)area_opaque * (1.0f / 65536.0f) / (float)max(tiles, 1u);
     if (!(m >= 0.5f)) return false;
     const float hidden = 1.0f - (1.0f - expf(-m)) / m;
     return hidden * ((float)area_all * (1.0f / 256.0f)) >= 180000.0f;
 }
-// The items of a block of the opaque and count passes: one, or (GATED, f.opaque == 2) where the device
-// chose the variant (with: for frames with an opaque pass) several in turn, see launch_count.  (The loop
-// takes 18 more VGPRs and a tenth of the time of a count pass that has one item per block.)
-template <bool GATED, class F> __device__ inline void for_each_item(const FrameBufs& f, bool with, F&& item) {
-    const uint32_t n_items = f.item_start[f.T];
-    if (blockIdx.x >= n_items || f.ctr->cap_overflow) return;
-    if constexpr (!GATED) {
-        item(xcd_contiguous(blockIdx.x, n_items));
-    } else {
-        if ((f.ctr->hides != 0) != with) return;
-        for (uint32_t b = blockIdx.x; b < n_items; b += gridDim.x) {
-            if (b != blockIdx.x) __syncthreads();
-            item(xcd_contiguous(b, n_items));
-        }
-    }
-}
-
 // The tiles' list offsets (exclusive scan of their list lengths, block 0) and their work items of
 // the count and emit passes (kNT list entries each, scanned by block 1), each with its part of the
 // first capacity check: the work of k_tile_items, k_scan1 twice and k_check_caps stage 1 for up to
@@ -1766,9 +1749,21 @@ __device__ inline void opaque_item(const FrameBufs& f, const CamConst& cam, int 
     // (kmax_key: whatever the key, the count and emit passes take the same word for hiding)
     if (s_z[t] < z0) atomicMin(&f.pix_kmax[q], kmax_key(s_z[t]));
 }
-template <bool GATED> __global__ __launch_bounds__(kNT) void k_opaque(FrameBufs f, CamConst cam, int first) {
+// An item per block, or (CHOICE: the device chose whether the frame has the pass, f.opaque == 2) several in
+// turn, see launch_count.
+template <bool CHOICE> __global__ __launch_bounds__(kNT) void k_opaque(FrameBufs f, CamConst cam, int first) {
     if (!(__uint_as_float(f.ctr->max_hw_bits) > 0.5f + kOpaqueMargin)) return;
-    for_each_item<GATED>(f, true, [&](uint32_t item) { opaque_item(f, cam, first, item); });
+    const uint32_t n_items = f.item_start[f.T];
+    if (blockIdx.x >= n_items || f.ctr->cap_overflow) return;
+    if constexpr (!CHOICE) {
+        opaque_item(f, cam, first, xcd_contiguous(blockIdx.x, n_items));
+    } else {
+        if (!f.ctr->hides) return;
+        for (uint32_t b = blockIdx.x; b < n_items; b += gridDim.x) {
+            if (b != blockIdx.x) __syncthreads();
+            opaque_item(f, cam, first, xcd_contiguous(b, n_items));
+        }
+    }
 }
 
 // Count pass: per pixel the fragments that the frame stores and, in pix_off until k_tile_prep
@@ -1777,8 +1772,9 @@ template <bool GATED> __global__ __launch_bounds__(kNT) void k_opaque(FrameBufs 
 // the tile's pixels and keeps the returned base (its slice of every pixel's range).
 // ZC: the frame has an opaque pass, and leaves out what an opaque fragment hides (see launch_count).
 // TRIM: fragments without coverage are left out too (FrameBufs::trim).
-template <bool TRIM, bool ZC>
-__device__ inline void count_item(const FrameBufs& f, const CamConst& cam, uint32_t item) {
+// CHOICE: the device has chosen whether it has (f.opaque == 2).
+template <bool TRIM, bool ZC, bool CHOICE>
+__global__ __launch_bounds__(kNT) void k_count(FrameBufs f, CamConst cam) {
     __shared__ uint32_t s_cnt[kTilePix];
     __shared__ HideOf<ZC> s_hide[1];
     __shared__ uint32_t s_dr[ZC ? kTilePix : 1], s_dc[ZC ? kTilePix : 1];   // see below
@@ -1787,6 +1783,10 @@ __device__ inline void count_item(const FrameBufs& f, const CamConst& cam, uint3
     __shared__ int s_vis[TRIM ? kNT : 1];   // |cross| up to which the segment's fragments have coverage
     __shared__ uint8_t s_own[kNT / 64 * kCovLinesPerWave];
     PHASE_BEGIN();
+    const uint32_t n_items = f.item_start[f.T];
+    if (blockIdx.x >= n_items || f.ctr->cap_overflow) return;
+    const bool hides = ZC && (!CHOICE || f.ctr->hides != 0);
+    const uint32_t item = xcd_contiguous(blockIdx.x, n_items);
     const int t = threadIdx.x;
     const uint2 it = f.item_tab[item];
     const int tile = (int)it.x;
@@ -1799,10 +1799,12 @@ __device__ inline void count_item(const FrameBufs& f, const CamConst& cam, uint3
     if (j < n) s = f.seg[f.list[lstart + j]];
     const size_t q = (size_t)tile * kTilePix + t;
     if constexpr (ZC) {
-        s_dr[t] = s_dc[t] = 0u;
-        s_iz[t] = key_inputs(s);
-        const int gx = px0 + (t % kTile), gy = py0 + (t / kTile);
-        hide_setup(s_hide[0], gx < cam.W && gy < cam.H ? f.pix_kmax[q] : 0u);
+        if (hides) {
+            s_dr[t] = s_dc[t] = 0u;
+            s_iz[t] = key_inputs(s);
+            const int gx = px0 + (t % kTile), gy = py0 + (t / kTile);
+            hide_setup(s_hide[0], gx < cam.W && gy < cam.H ? f.pix_kmax[q] : 0u);
+        }
     }
     if constexpr (TRIM) {
         const int dx = s.xb - s.xa, dy = s.yb - s.ya;
@@ -1815,15 +1817,16 @@ __device__ inline void count_item(const FrameBufs& f, const CamConst& cam, uint3
         bool stored = true;
         if constexpr (TRIM) stored = abs(cr) <= vis;
         if constexpr (ZC) {
-            if (stored) stored = depth_key_iz(iz.x, iz.y, tnum, tden, iz.z) <= s_hide[0].z[p];
+            if (hides && stored) stored = depth_key_iz(iz.x, iz.y, tnum, tden, iz.z) <= s_hide[0].z[p];
         }
         atomicAdd(&s_cnt[p], stored ? 1u : 0x10000u);
     }, [&](int o, int p, int n, bool steep) {
         // a line hidden as a whole: its pixels are only counted, as differences along the line (+1
         // where it begins, -1 behind its end) that two row sums add up below
-        if constexpr (ZC) iz = s_iz[o];
         if constexpr (TRIM) vis = s_vis[o];
-        if (!ZC || !line_hidden(s_hide[0], nearest_key(iz), p, n, steep)) return false;
+        if (!hides) return false;
+        if constexpr (ZC) iz = s_iz[o];
+        if (!line_hidden(s_hide[0], nearest_key(iz), p, n, steep)) return false;
         uint32_t* d = steep ? s_dr : s_dc;
         const int i = steep ? p : ((p & 15) << 4 | p >> 4);   // (columns are kept transposed)
         atomicAdd(&d[ZC ? i : 0], 1u);
@@ -1831,7 +1834,7 @@ __device__ inline void count_item(const FrameBufs& f, const CamConst& cam, uint3
         return true;
     });
     __syncthreads();
-    if constexpr (ZC) {
+    if (hides) {
         const uint32_t r = row_inclusive_sum(s_dr[t]), v = row_inclusive_sum(s_dc[t]);
         if (r) atomicAdd(&s_cnt[t], r << 16);
         if (v) atomicAdd(&s_cnt[(t & 15) << 4 | t >> 4], v << 16);
@@ -1846,10 +1849,6 @@ __device__ inline void count_item(const FrameBufs& f, const CamConst& cam, uint3
     if (c) base = atomicAdd(&f.pix_cnt[q], c);
     f.item_base[(size_t)item * kTilePix + t] = base;
     PHASE_END(f.ctr, 0);
-}
-template <bool TRIM, bool ZC, bool GATED>
-__global__ __launch_bounds__(kNT) void k_count(FrameBufs f, CamConst cam) {
-    for_each_item<GATED>(f, ZC, [&](uint32_t item) { count_item<TRIM, ZC>(f, cam, item); });
 }
 
 // The fragments a batch of a tile may take (a multiple of kNT, up to kCap).  A large frame fills
@@ -4025,18 +4024,19 @@ static void launch_count_trim(const FrameBufs& f, const CamConst& cam, uint32_t 
         hipLaunchKernelGGL(k_opaque<false>, dim3(grid), b, 0, st, f, cam, 0);
         hipLaunchKernelGGL((k_count<TRIM, true, false>), dim3(grid), b, 0, st, f, cam);
     } else {
-        const dim3 with(std::min(grid, std::min(most, 12288u))), without(std::min(grid, std::min(most, 8192u)));
-        hipLaunchKernelGGL(k_opaque<true>, with, b, 0, st, f, cam, 1);
-        hipLaunchKernelGGL(k_opaque<true>, with, b, 0, st, f, cam, 0);
-        hipLaunchKernelGGL((k_count<TRIM, true, true>), with, b, 0, st, f, cam);
-        hipLaunchKernelGGL((k_count<TRIM, false, true>), without, b, 0, st, f, cam);
+        const dim3 few(std::min(grid, std::min(most, 12288u)));
+        hipLaunchKernelGGL(k_opaque<true>, few, b, 0, st, f, cam, 1);
+        hipLaunchKernelGGL(k_opaque<true>, few, b, 0, st, f, cam, 0);
+        hipLaunchKernelGGL((k_count<TRIM, true, true>), dim3(grid), b, 0, st, f, cam);
     }
 }
-// Mixed frames (f.opaque == 2) launch both variants, and the device chooses: the passes not chosen only
-// leave.  Their blocks take items in turn, so that there are few to leave (a warm grid has the size of the
-// largest frame so far: 20 k blocks that leave took 8 us, 12288 take 4.6), and enough for items of very
-// different cost (2048 blocks for the 22 k items of a frame of 3 M rows: 130 us more, 8192: 4 us; the two
-// opaque launches of a frame of 14 k items: 4608 blocks 57 us, 12288 50, a block each without a choice 45).
+// Mixed frames (f.opaque == 2) launch the opaque pass, and the device chooses whether it only leaves.  Its
+// blocks then take items in turn, so that there are few to leave (a warm grid has the size of the largest
+// frame so far: 20 k blocks that leave took 8 us, 12288 take 4.6), and enough for items of very different
+// cost (both launches of a frame of 14 k items: 4608 blocks 57 us, 12288 50, a block each without a choice
+// 45).  The count pass is one kernel for both, with the LDS of frames that hide: a frame of 18 M fragments
+// that does not takes 10 us more than with a kernel of its own (six blocks per CU instead of eight), one
+// that does is spared that kernel's launch, 5 us.
 hipError_t launch_count(const FrameBufs& f, const CamConst& cam, uint32_t grid, int32_t rows, hipStream_t st) {
     if (grid == 0) return hipSuccess;
     const uint32_t most = std::max(1024u, (uint32_t)rows / 16);
